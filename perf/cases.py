@@ -69,7 +69,7 @@ def draw(rng):
         return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
 
     kind = rng.choice(["precond", "product", "solve", "solve", "step", "step", "loads", "inverse", "many"])
-    c = dict(kind=kind, crack=rng.choice(["edge", "penny", "penny"]), sigma=rng.choice([0.0, 0.5, 0.5]))
+    c = dict(kind=kind, crack=rng.choice(["edge", "penny", "penny"]), sigma=round(max(0.0, rng.uniform(-0.1, 0.6)), 3))
     if kind == "precond":
         c["ne"] = size(8, 30)
     elif kind == "product":
