@@ -50,6 +50,8 @@ void carve_workspace(dpcg_ctx *c, Workspace &w, char *base) {
     w.cpart = (double *)(base + off);
     off += up256(8 * nt * nt * kCoarseTile);
     w.hdp = (double *)(base + off);
+    // by rows: more partials than tile rows, and no tile contributions to hold
+    if (coarse_by_rows(c->k)) w.hdp = w.cpart;
     off += up256(8 * nt);
     w.st = (State *)(base + off);
 }
@@ -678,7 +680,10 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         d.hdp = w.hdp;
         d.st = w.st;
         const int n_ph[kMsPhases] = {round8(c->spmv.nwg), 1, round8(c->bj_nwg), std::max(1, c->k),
-                                     c->k > 0 ? (int)coarse_tile_count(c->coarse_nt) : 0, c->coarse_nt,
+                                     c->k == 0                ? 0
+                                     : coarse_by_rows(c->k) ? coarse_parts(c->k, c->coarse_nt)
+                                                            : (int)coarse_tile_count(c->coarse_nt),
+                                     coarse_by_rows(c->k) ? 0 : c->coarse_nt,
                                      round8(c->vec_nwg)};
         for (int ph = 0; ph < kMsPhases; ++ph) {
             tab.off[ph][i] = tot[ph];

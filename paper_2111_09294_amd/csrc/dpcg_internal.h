@@ -38,6 +38,19 @@ constexpr int kRestrictRound = 4096;  // list entries per round of the restricti
 
 // tile (I, J), I >= J, of the lower triangle of a matrix of nt x nt tiles: index I (I + 1) / 2 + J
 __host__ __device__ inline int64_t coarse_tile_count(int32_t nt) { return (int64_t)nt * (nt + 1) / 2; }
+// The coarse product reads the dense E^-1 row by row in one launch while a lane's share of a
+// row is one round of loads, and the packed lower triangle (half the bytes, a second launch
+// to add the tiles' partials) above: 2.9 against 3.4 + 2.5 us at k = 156, 3.9-4.6 against
+// 4.6 + 3.8 us at k = 992; at k = 2200 the row form is faster itself but its 39 MB push K out
+// of the last-level cache (a 61^3 mixed solve 48.9 against 48.1 ms).
+constexpr int kCoarseRowsMax = 1024;
+constexpr int kCoarseRowWaves = 4;  // rows (waves) per workgroup of the row form
+__host__ __device__ inline bool coarse_by_rows(int32_t k) { return k <= kCoarseRowsMax; }
+// entries of the h^T delta partials the coarse product leaves for the prolongation
+__host__ __device__ inline int32_t coarse_parts(int32_t k, int32_t nt) {
+    if (k == 0) return 1;
+    return coarse_by_rows(k) ? (k + kCoarseRowWaves - 1) / kCoarseRowWaves : nt;
+}
 constexpr int kBatchCols = 32;    // columns of the multi-RHS workspace (right-hand sides per batch)
 constexpr int kBatchSegEntries = 2048;  // entries per multi-RHS restriction segment
 constexpr int kBatchTileWindow = 47;                         // block starts per multi-RHS tile

@@ -820,6 +820,59 @@ __device__ __forceinline__ void k_coarse_sum_body(int vb, int32_t k, int32_t nt,
     }
 }
 
+// The coarse product of a small system in one launch: a wave per row of the dense E^-1,
+// eight 16-byte loads per lane in flight (a row of up to 1,024 entries in one round).  With
+// h given, hdp[vb] = sum of h_j delta_j over the workgroup's kCoarseRowWaves rows.
+__device__ __forceinline__ void k_coarse_rows_body(int vb, int32_t k, int64_t ld, const double *__restrict__ einv,
+                                                   const double *__restrict__ g, double *__restrict__ delta,
+                                                   const double *__restrict__ h, double *__restrict__ hdp,
+                                                   const State *st) {
+    __shared__ double hs[kCoarseRowWaves];
+    constexpr int U = 8;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int row = vb * kCoarseRowWaves + wave;
+    const bool run = !st || st->flag == kRunning;
+    double acc = 0.0, hv = 0.0;
+    if (row < k) {
+        const double *__restrict__ A = einv + row * ld;
+        if (h && lane == 0) hv = h[row];
+        for (int j0 = 2 * lane; j0 < k; j0 += 128 * U) {
+            double2 a[U];
+            double x0[U], x1[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = j0 + 128 * u;
+                a[u] = make_double2(0.0, 0.0);
+                x0[u] = x1[u] = 0.0;
+                if (j < k) {  // ld is even: the pair stays in the row; entry k is not used
+                    a[u] = *reinterpret_cast<const double2 *>(A + j);
+                    x0[u] = g[j];
+                    if (j + 1 < k) x1[u] = g[j + 1];
+                    else a[u].y = 0.0;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = fma(a[u].y, x1[u], fma(a[u].x, x0[u], acc));
+        }
+    }
+    acc = wave_sum(acc);
+    if (lane == 0 && row < k && run) delta[row] = acc;
+    if (h) {
+        if (lane == 0) hs[wave] = hv * acc;
+        __syncthreads();
+        if (threadIdx.x == 0 && run) hdp[vb] = (hs[0] + hs[1]) + (hs[2] + hs[3]);
+    }
+}
+
+__global__ __launch_bounds__(64 * kCoarseRowWaves) void k_coarse_rows(int32_t k, int64_t ld,
+                                                                      const double *__restrict__ einv,
+                                                                      const double *__restrict__ g,
+                                                                      double *__restrict__ delta,
+                                                                      const double *__restrict__ h,
+                                                                      double *__restrict__ hdp, const State *st) {
+    k_coarse_rows_body(blockIdx.x, k, ld, einv, g, delta, h, hdp, st);
+}
+
 __global__ __launch_bounds__(256) void k_coarse_tiles(int32_t k, int32_t nt, const double *__restrict__ tiles,
                                                       const double *__restrict__ g, double *__restrict__ cpart,
                                                       const State *st) {
@@ -1105,13 +1158,18 @@ __global__ __launch_bounds__(kRestrictThreads) void k_ms_restrict(const MsTable 
     }
 }
 
-// the coarse product's two stages (as launch_coarse); with_state 0: the start (no
+// the coarse product (as launch_coarse: one stage by rows, or tiles and their sum); with_state 0: the start (no
 // state), 1: with the state, 2: also the tile-row sums of h_j delta_j for the prolongation
 __global__ __launch_bounds__(kThreads) void k_ms_coarse(const MsTable *__restrict__ tab, const MsSys *__restrict__ sys,
                                                         int with_state) {
     const int s = ms_find(tab, kMsCoarse, blockIdx.x);
     const MsSys &S = sys[s];
     if (!with_state && S.st->flag != kRunning) return;
+    if (coarse_by_rows(S.k)) {
+        k_coarse_rows_body(blockIdx.x - tab->off[kMsCoarse][s], S.k, S.einv_ld, S.einv, S.g, S.delta,
+                           with_state == 2 ? S.h : nullptr, S.hdp, with_state ? S.st : nullptr);
+        return;
+    }
     k_coarse_tiles_body(blockIdx.x - tab->off[kMsCoarse][s], S.k, S.coarse_nt, S.einv_tiles, S.g, S.cpart,
                         with_state ? S.st : nullptr);
 }
@@ -1144,8 +1202,8 @@ __global__ __launch_bounds__(kThreads) void k_ms_prolong(const MsTable *__restri
         k_prolong_body(vb, S.n, S.vec_nwg, S.z_ptr, S.z_col, S.z_val, S.delta, S.y, S.z, S.r, S.part_c, S.st,
                        advance);
     } else {
-        k_prolong_p_body(vb, S.n, S.vec_nwg, S.z_ptr, S.z_col, S.z_val, S.delta, S.y, S.hdp, max(1, S.coarse_nt),
-                         S.p0, S.p1, S.st);
+        k_prolong_p_body(vb, S.n, S.vec_nwg, S.z_ptr, S.z_col, S.z_val, S.delta, S.y, S.hdp,
+                         coarse_parts(S.k, S.coarse_nt), S.p0, S.p1, S.st);
     }
 }
 
@@ -1266,6 +1324,12 @@ hipError_t launch_restrict(const dpcg_ctx *c, const double *a, const double *b, 
 hipError_t launch_coarse(const dpcg_ctx *c, const double *g, double *delta, const State *st, double *cpart,
                          const double *h, double *hdp) {
     if (c->k == 0) return hipSuccess;
+    if (coarse_by_rows(c->k)) {
+        hipLaunchKernelGGL(k_coarse_rows, dim3((c->k + kCoarseRowWaves - 1) / kCoarseRowWaves),
+                           dim3(64 * kCoarseRowWaves), 0, c->stream, c->k, c->einv_ld, (const double *)c->einv, g,
+                           delta, h, hdp, st);
+        return hipGetLastError();
+    }
     const int nt = c->coarse_nt;
     hipLaunchKernelGGL(k_coarse_tiles, dim3((unsigned)coarse_tile_count(nt)), dim3(256), 0, c->stream, c->k, nt,
                        (const double *)c->einv_tiles, g, cpart, st);
@@ -1286,8 +1350,8 @@ hipError_t launch_prolong(const dpcg_ctx *c, const double *base, const double *d
 
 hipError_t launch_prolong_p(const dpcg_ctx *c, Workspace &w) {
     hipLaunchKernelGGL(k_prolong_p, dim3(c->prolong_nwg), dim3(kThreads), 0, c->stream, c->n, c->prolong_nwg,
-                       c->z_ptr, c->z_col, c->z_val, w.delta, w.y, (const double *)w.hdp, std::max(1, c->coarse_nt),
-                       w.p[0], w.p[1], w.st);
+                       c->z_ptr, c->z_col, c->z_val, w.delta, w.y, (const double *)w.hdp,
+                       coarse_parts(c->k, c->coarse_nt), w.p[0], w.p[1], w.st);
     return hipGetLastError();
 }
 

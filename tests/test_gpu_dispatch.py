@@ -1,0 +1,65 @@
+"""The kernels' dispatch rules at their edges, on small systems with a known answer.
+
+Systems: block-tridiagonal SPD matrices of 3x3 blocks with a dominant diagonal (condition
+number below 4), so that a solve to 1e-13 leaves an error below 4e-13 plus the rounding of
+the products, and 1e-11 is asked.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2111_09294_amd as D  # noqa: E402
+
+DEV = "cuda:0"
+
+
+def chain(nb, seed=0):
+    """K (scipy CSR) of nb block rows: 3x3 blocks on three block diagonals."""
+    import scipy.sparse as sp
+    rng = np.random.default_rng(seed)
+    off = rng.uniform(-0.1, 0.1, (max(nb - 1, 0), 3, 3))
+    diag = rng.uniform(-0.05, 0.05, (nb, 3, 3))
+    diag = 0.5 * (diag + diag.transpose(0, 2, 1)) + 1.5 * np.eye(3)
+    rows = np.arange(nb)
+    blocks = np.concatenate([diag, off, off.transpose(0, 2, 1)])
+    I = np.concatenate([rows, rows[:-1], rows[1:]])
+    J = np.concatenate([rows, rows[1:], rows[:-1]])
+    r = (3 * I[:, None, None] + np.arange(3)[None, :, None]) + np.zeros((1, 1, 3), int)
+    c = (3 * J[:, None, None] + np.arange(3)[None, None, :]) + np.zeros((1, 3, 1), int)
+    K = sp.csr_matrix((blocks.reshape(-1), (r.reshape(-1), c.reshape(-1))), shape=(3 * nb, 3 * nb))
+    K.sort_indices()
+    return K
+
+
+def solver(K, sel, block=3):
+    """Solver with nodal blocks of `block` unknowns and Z = unit vectors of the unknowns sel."""
+    n, k = K.shape[0], len(sel)
+    zp = np.zeros(n + 1, np.int64)
+    zp[np.asarray(sel, int) + 1] = 1
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    bp = np.unique(np.concatenate([np.arange(0, n, block), [n]]))
+    return D.Solver(n, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), k,
+                    t(np.cumsum(zp), torch.int64), t(np.arange(k), torch.int32),
+                    t(np.ones(k), torch.float64), t(bp, torch.int32))
+
+
+@pytest.mark.parametrize("k", [1, 2, 63, 64, 65, 127, 1023, 1024, 1025])
+def test_coarse_product_forms(k):
+    """E^-1 g by rows (k <= 1024) and by tiles; E = K at every third-or-so unknown."""
+    K = chain(700)
+    sel = np.sort(np.random.default_rng(k).permutation(2100)[:k])
+    g = np.random.default_rng(1).standard_normal(k)
+    with solver(K, sel) as s:
+        d = s.coarse_apply(torch.as_tensor(g, device=DEV)).cpu().numpy()
+        # the whole iteration on the same form
+        x = np.random.default_rng(2).standard_normal(2100)
+        u, info = s.solve(torch.as_tensor(K @ x, device=DEV), tol=1e-13)
+    ref = np.linalg.solve(K[sel][:, sel].toarray(), g)
+    assert np.linalg.norm(d - ref) <= 1e-13 * k ** 0.5 * np.linalg.norm(ref) + 1e-14
+    assert info["status"] == 0
+    assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
