@@ -142,6 +142,8 @@ int alloc_workspace(dpcg_ctx *c, Workspace &w) {
     return DPCG_OK;
 }
 
+int round8(int v) { return v >= 8 ? (v + 7) & ~7 : v; }
+
 int round_grid(int want) {
     if (want >= 8) want &= ~7;
     return std::max(1, want);
@@ -173,7 +175,8 @@ void choose_shapes(dpcg_ctx *c) {
     c->vec_nwg = round_grid((int)std::min<int64_t>((c->n + kThreads - 1) / kThreads, 1024));
     // two rows per thread: half the workgroups, each forming rho once (four measured slower)
     c->prolong_nwg = round_grid((int)std::min<int64_t>((c->n + 2 * kThreads - 1) / (2 * kThreads), 16384));
-    c->bj_nwg = round_grid(std::min(c->bj_ntiles, 65536));  // one tile each (partials reduced by one workgroup)
+    // one tile each, rounded up to a multiple of 8 (partials reduced by one workgroup)
+    c->bj_nwg = c->bj_ntiles <= 65536 ? round8(std::max(1, c->bj_ntiles)) : 65536;
 }
 
 int setup_impl(dpcg_ctx *c, int64_t n, const int64_t *k_rowptr, const int32_t *k_col, const double *k_val,
@@ -557,8 +560,6 @@ int autotune_spmv(dpcg_ctx *c, int reps) {
     c->tuned = true;
     return c->spmv.group;
 }
-
-int round8(int v) { return v >= 8 ? (v + 7) & ~7 : v; }
 
 int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, double *const *U, double tol,
                     const dpcg_options *opt_in, dpcg_info *infos) {

@@ -34,6 +34,12 @@ constexpr int kDenseRows = 32;    // rows of a dense block per workgroup of its 
 constexpr int kMaxElemDofs = 256; // largest element (DoFs) of dpcg_element_gradient
 constexpr int kCoarseTile = 64;   // E^-1 kept as the lower-triangle tiles of this size
 constexpr int kAlphaParts = 64;   // workgroups of the first stage of p^T q
+// Up to this many p^T q partials the update's workgroups add them all themselves (eight
+// loads per thread, in flight with the tile's own: the update takes the same 4.9 us at 23^3
+// and the first stage's 2.7 us and launch go); above, where every workgroup would read more
+// than 16 KB for the sum, the first stage makes kAlphaParts.
+constexpr int kFoldParts = 2048;
+__host__ __device__ inline bool fold_alpha(int32_t parts) { return parts <= kFoldParts; }
 constexpr int kRestrictRound = 4096;  // list entries per round of the restriction's loads (threads x depth)
 
 // tile (I, J), I >= J, of the lower triangle of a matrix of nt x nt tiles: index I (I + 1) / 2 + J

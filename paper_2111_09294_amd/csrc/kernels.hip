@@ -77,6 +77,23 @@ __device__ __forceinline__ double strided_share(const double *__restrict__ parts
     return a[0];
 }
 
+// As strided_share for a list of at least one entry that mostly fits one round: the
+// round's loads are clamped to the list instead of left to a serial tail.
+template <int NT, int U>
+__device__ __forceinline__ double masked_share(const double *__restrict__ parts, int n) {
+    double a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = parts[min((int)threadIdx.x + u * NT, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = (int)threadIdx.x + u * NT < n ? a[u] : 0.0;
+    for (int i = threadIdx.x + U * NT; i < n; i += NT) a[0] += parts[i];
+#pragma unroll
+    for (int w = 1; w < U; w <<= 1)
+#pragma unroll
+        for (int u = 0; u + w < U; u += 2 * w) a[u] += a[u + w];
+    return a[0];
+}
+
 template <int NW>
 __device__ __forceinline__ double reduce_parts_n(const double *parts, int n, double *lds) {
     return block_sum_n<NW>(strided_share<NW * 64, 16>(parts, n), lds);
@@ -393,28 +410,47 @@ __global__ __launch_bounds__(kThreads) void k_beta_p(const double *__restrict__ 
 
 
 // y_d = sum_j Minv_B[d - s_B, j] r_{s_B + j} for the DoFs of this tile (whole blocks),
-// given row d's inverse row m and its packed size and position in the block.
+// given row d's inverse row m and its packed size and position in the block.  The first
+// six entries (a plain node's whole row) are loaded by bj_first, ahead of the barrier that
+// makes the tile's r complete; longer rows load six more at a time, added in order.
+constexpr int kBjDepth = 6;
+
 template <class M>
-__device__ __forceinline__ double bj_row_at(int t, const double *tile, const M *__restrict__ m, int meta) {
+__device__ __forceinline__ void bj_first(const M *__restrict__ m, int meta, double (&v)[kBjDepth]) {
+    const int last = max((meta >> 8) - 1, 0);  // clamped, so that no load waits for a branch
+#pragma unroll
+    for (int u = 0; u < 3; ++u) v[u] = (double)m[min(u, last)];
+#pragma unroll
+    for (int u = 3; u < kBjDepth; ++u) v[u] = 0.0;
+    if (__any(last >= 3)) {
+#pragma unroll
+        for (int u = 3; u < kBjDepth; ++u) v[u] = (double)m[min(u, last)];
+    }
+}
+
+template <class M>
+__device__ __forceinline__ double bj_row_at(int t, const double *tile, const M *__restrict__ m, int meta,
+                                            double (&v)[kBjDepth]) {
     const int size = meta >> 8, loc = meta & 255;
     const double *rt = tile + (t - loc);
     double s = 0.0;
-    for (int j0 = 0; j0 < size; j0 += 6) {  // six entries' loads issued together, added in order
-        double v[6];
+    for (int j0 = 0; j0 < size; j0 += kBjDepth) {
+        if (j0 > 0) {
 #pragma unroll
-        for (int u = 0; u < 6; ++u) v[u] = j0 + u < size ? (double)m[j0 + u] : 0.0;
+            for (int u = 0; u < kBjDepth; ++u) v[u] = j0 + u < size ? (double)m[j0 + u] : 0.0;
+        }
 #pragma unroll
-        for (int u = 0; u < 6; ++u)
+        for (int u = 0; u < kBjDepth; ++u)
             if (j0 + u < size) s = fma(v[u], rt[j0 + u], s);
     }
     return s;
 }
 
-// sum_e z_val[e] delta[z_col[e]] over e in [e0, e1) in index order, four entries per step
+// c + sum_e z_val[e] delta[z_col[e]] over e in [e0, e1) in index order, four entries per step
 // with their column, value and delta loads issued together (clamped as above).
 __device__ __forceinline__ double z_row_dot(int e0, int e1, const int32_t *__restrict__ z_col,
-                                            const double *__restrict__ z_val, const double *__restrict__ delta) {
-    double c = 0.0;
+                                            const double *__restrict__ z_val, const double *__restrict__ delta,
+                                            double c = 0.0) {
     for (int e = e0; e < e1; e += 4) {
         const int i1 = min(e + 1, e1 - 1), i2 = min(e + 2, e1 - 1), i3 = min(e + 3, e1 - 1);
         const int32_t c0 = z_col[e], c1 = z_col[i1], c2 = z_col[i2], c3 = z_col[i3];
@@ -428,79 +464,100 @@ __device__ __forceinline__ double z_row_dot(int e0, int e1, const int32_t *__res
     return c;
 }
 
-template <class M>
-__device__ __forceinline__ double bj_row(int t, int64_t d, const double *tile, const M *__restrict__ minv,
-                                         const int32_t *__restrict__ bj_rowoff,
-                                         const int32_t *__restrict__ bj_meta) {
-    return bj_row_at(t, tile, minv + bj_rowoff[d], bj_meta[d]);
+// Tiles [t0, t1) of workgroup w: one each when the grid has a workgroup per tile (those past
+// the last get none), else an even split.
+__device__ __forceinline__ void tile_range(int w, int32_t ntiles, int32_t nwg, int &t0, int &t1) {
+    if (nwg >= ntiles) {
+        t0 = min(w, ntiles);
+        t1 = min(w + 1, ntiles);
+    } else {
+        t0 = (int)(((int64_t)w * ntiles) / nwg);
+        t1 = (int)(((int64_t)(w + 1) * ntiles) / nwg);
+    }
 }
 
 // Step length, solution and residual updates of Algorithm 1 with the residual norm
 // partials, then the block-Jacobi apply y = M^{-1} r that opens Algorithm 3.
+// alpha_i = rho_i / p_i^T q_i: every workgroup adds the n_pq partial sums in the same order,
+// so all hold the same bits and see a breakdown alike.  In a small system the kernel's time
+// is its chain of dependent loads, so everything that needs neither alpha nor the state is
+// asked for first: tile bounds with the partials and the state, then the tile's vectors and
+// row offsets, then the inverse rows, three round trips in all (7.0 -> 4.9 us at 10^3, 7.5 ->
+// 4.9 us at 23^3; at 80^3, where bytes bound it, 31.2 -> 30.5 us).
 template <class M>
 __device__ __forceinline__ void k_update_bj_body(int vb, 
     int32_t ntiles, int32_t nwg, const int32_t *__restrict__ tile_start, double *__restrict__ u,
     double *__restrict__ r, double *__restrict__ y, const double *__restrict__ q, const double *p0,
     const double *p1, const M *__restrict__ minv, const int32_t *__restrict__ bj_rowoff,
     const int32_t *__restrict__ bj_meta, double *__restrict__ part_rr, double *__restrict__ part_ry,
-    const double *__restrict__ part_pq2, State *st) {
+    const double *__restrict__ part_pq, int32_t n_pq, State *st) {
     __shared__ double lds[2 * (kThreads / 64)];
     __shared__ double tile[kThreads];
     const int t = threadIdx.x;
     const int w = xcd_remap(vb, nwg);
     int t0, t1;
-    if ((uint64_t)ntiles * (uint64_t)nwg < (1ull << 32)) {  // 32-bit quotients when they fit
-        t0 = (int)(((uint32_t)w * (uint32_t)ntiles) / (uint32_t)nwg);
-        t1 = (int)(((uint32_t)(w + 1) * (uint32_t)ntiles) / (uint32_t)nwg);
-    } else {
-        t0 = (int)(((int64_t)w * ntiles) / nwg);
-        t1 = (int)(((int64_t)(w + 1) * ntiles) / nwg);
-    }
-    // the first tile's bounds are loaded before the state, so the two round trips overlap
-    int64_t b0 = 0, b1 = 0;
+    tile_range(w, ntiles, nwg, t0, t1);
+    int d = 0, d1 = 0;
     if (t0 < t1) {
-        b0 = tile_start[t0];
-        b1 = tile_start[t0 + 1];
+        d = tile_start[t0] + t;
+        d1 = tile_start[t0 + 1];
     }
-    if (st->flag != kRunning) return;
-    // alpha_i = rho_i / p_i^T q_i: every wave adds the kAlphaParts first-stage sums with the
-    // same butterfly, so all workgroups hold the same bits; a breakdown is seen by all
-    const double pq = wave_sum((threadIdx.x & 63) < kAlphaParts ? part_pq2[threadIdx.x & 63] : 0.0);
-    const double alpha = st->rho[st->iter & 1] / pq;
+    // up to kAlphaParts sums (the first stage's), one per lane of every wave, or the SpMV's
+    // own partials over the workgroup's threads
+    const bool folded = n_pq > kAlphaParts;
+    double pq = folded ? masked_share<kThreads, kFoldParts / kThreads>(part_pq, n_pq)
+                       : ((t & 63) < n_pq ? part_pq[t & 63] : 0.0);
+    const int32_t flag = st->flag, it = st->iter;
+    const double rho0 = st->rho[0], rho1 = st->rho[1];
+    const double *p = (it & 1) ? p1 : p0;
+    int meta = 0;
+    const M *m = minv;
+    double ud = 0.0, pd = 0.0, qd = 0.0, rd = 0.0, mv[kBjDepth];
+    auto load = [&]() {  // lanes past the tile read its last DoF
+        const int dc = min(d, max(d1 - 1, 0));
+        meta = bj_meta[dc];
+        const int off = bj_rowoff[dc];
+        ud = u[dc];
+        pd = p[dc];
+        qd = q[dc];
+        rd = r[dc];
+        if (d >= d1) meta = 0;
+        m = minv + (meta ? off : 0);
+        bj_first(m, meta, mv);
+    };
+    load();
+    if (flag != kRunning) return;
+    pq = folded ? block_sum(pq, lds) : wave_sum(pq);
+    const double alpha = ((it & 1) ? rho1 : rho0) / pq;
     if (!(pq > 0.0) || !isfinite(pq) || !isfinite(alpha)) {
         if (vb == 0 && threadIdx.x == 0) {
             st->flag = kBreakdown;
-            st->bad = st->iter;
-            st->iters_done = st->iter;
+            st->bad = it;
+            st->iters_done = it;
         }
         return;
     }
-    const double *p = (st->iter & 1) ? p1 : p0;
     double acc = 0.0, accy = 0.0;
-    for (int tt = t0; tt < t1; ++tt) {
-        if (tt > t0) {
-            b0 = tile_start[tt];
-            b1 = tile_start[tt + 1];
-        }
-        const int64_t d0 = b0, d1 = b1;
-        const int64_t d = d0 + t;
+    for (int tt = t0; tt < t1;) {
         double rn = 0.0;
-        int meta = 0, roff = 0;  // loaded with the vectors, ahead of the barrier
-        __syncthreads();
         if (d < d1) {
-            meta = bj_meta[d];
-            roff = bj_rowoff[d];
-            u[d] = fma(alpha, p[d], u[d]);
-            rn = fma(-alpha, q[d], r[d]);
+            u[d] = fma(alpha, pd, ud);
+            rn = fma(-alpha, qd, rd);
             r[d] = rn;
             tile[t] = rn;
             acc = fma(rn, rn, acc);
         }
         __syncthreads();
         if (d < d1) {
-            const double yd = bj_row_at(t, tile, minv + roff, meta);
+            const double yd = bj_row_at(t, tile, m, meta, mv);
             y[d] = yd;
             accy = fma(rn, yd, accy);
+        }
+        if (++tt < t1) {
+            d = tile_start[tt] + t;
+            d1 = tile_start[tt + 1];
+            load();
+            __syncthreads();
         }
     }
     if (part_ry) {  // r^T y partials: rho = r^T z is formed from them in the prolongation
@@ -521,9 +578,9 @@ __global__ __launch_bounds__(kThreads) void k_update_bj(
     double *__restrict__ r, double *__restrict__ y, const double *__restrict__ q, const double *p0,
     const double *p1, const M *__restrict__ minv, const int32_t *__restrict__ bj_rowoff,
     const int32_t *__restrict__ bj_meta, double *__restrict__ part_rr, double *__restrict__ part_ry,
-    const double *__restrict__ part_pq2, State *st) {
+    const double *__restrict__ part_pq, int32_t n_pq, State *st) {
     k_update_bj_body<M>(blockIdx.x, ntiles, nwg, tile_start, u, r, y, q, p0, p1, minv, bj_rowoff, bj_meta, part_rr,
-                        part_ry, part_pq2, st);
+                        part_ry, part_pq, n_pq, st);
 }
 
 
@@ -538,14 +595,23 @@ __device__ __forceinline__ void k_bj_body(int vb, int32_t ntiles, int32_t nwg, c
     if (st && st->flag != kRunning) return;
     const int t = threadIdx.x;
     const int w = xcd_remap(vb, nwg);
-    const int t0 = (int)(((int64_t)w * ntiles) / nwg), t1 = (int)(((int64_t)(w + 1) * ntiles) / nwg);
+    int t0, t1;
+    tile_range(w, ntiles, nwg, t0, t1);
     for (int tt = t0; tt < t1; ++tt) {
         const int64_t d0 = tile_start[tt], d1 = tile_start[tt + 1];
         const int64_t d = d0 + t;
+        const int64_t dc = min(d, d1 - 1);
+        double mv[kBjDepth];
+        int meta = bj_meta[dc];
+        const int off = bj_rowoff[dc];
+        const double rd = r[dc];
+        if (d >= d1) meta = 0;
+        const M *m = minv + (meta ? off : 0);
+        bj_first(m, meta, mv);
         __syncthreads();
-        if (d < d1) tile[t] = r[d];
+        if (d < d1) tile[t] = rd;
         __syncthreads();
-        if (d < d1) y[d] = bj_row(t, d, tile, minv, bj_rowoff, bj_meta);
+        if (d < d1) y[d] = bj_row_at(t, tile, m, meta, mv);
     }
 }
 
@@ -932,37 +998,69 @@ __global__ __launch_bounds__(kThreads) void k_prolong(int64_t n, int32_t nwg, co
 // and of beta_{i-1} = rho_i / rho_{i-1} and writes p_i = y + Z delta + beta_{i-1} p_{i-1}
 // into buffer i & 1 directly (z itself is never stored).  The restriction has already
 // advanced the iteration.  Workgroup 0 stores rho_i in slot i & 1 and tests it.
+// Everything that does not need rho is loaded before the one barrier (two rows per thread,
+// their first four Z entries together), so the chain is row pointers, columns, delta (6.4 ->
+// 5.6 us at 10^3, 8.0 -> 6.5 us at 23^3, 29.2 -> 27.7 us at 80^3).
 __device__ __forceinline__ void k_prolong_p_body(int vb, int64_t n, int32_t nwg, const int32_t *__restrict__ z_ptr,
                                                  const int32_t *__restrict__ z_col, const double *__restrict__ z_val,
                                                  const double *__restrict__ delta, const double *__restrict__ y,
                                                  const double *__restrict__ hparts, int32_t nhp, double *p0,
                                                  double *p1, State *st) {
-    __shared__ double lds[4];
-    if (wg_flag(st) != kRunning) return;
+    __shared__ double lds[kThreads / 64];
+    __shared__ int32_t sflag;
+    // the flag as the whole workgroup sees it (workgroup 0 may set it below)
+    const int32_t flag = __hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     const int it = st->iter;
+    const double ry = st->ry, rho_old = st->rho[(it + 1) & 1];
     double *__restrict__ pc = (it & 1) ? p1 : p0;
     const double *__restrict__ pp = (it & 1) ? p0 : p1;
     const int w = xcd_remap(vb, nwg);
-    const int64_t per = (n + nwg - 1) / nwg;
+    const uint32_t per = ((uint32_t)n + (uint32_t)nwg - 1) / (uint32_t)nwg;  // n < 2^30
     const int64_t d1 = min(n, (int64_t)(w + 1) * per);
-    // the thread's first two rows (the grid gives each thread two or more), y + Z delta and the
-    // old p, before beta is known: these loads overlap the reduction below
     int64_t d = (int64_t)w * per + threadIdx.x;
-    const int64_t d2 = d + kThreads;
-    double v = 0.0, pold = 0.0, v2 = 0.0, pold2 = 0.0;
-    if (d < d1) {
-        const double c = z_row_dot(z_ptr[d], z_ptr[d + 1], z_col, z_val, delta);
-        v = y[d] + c;
-        pold = pp[d];
+    constexpr int R = 2;  // rows per thread (the grid gives most threads two)
+    int e0[R], e1[R];
+    double v[R], pold[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {  // lanes past the range read row n - 1, with no entries
+        const int64_t di = d + i * kThreads, dc = min(di, n - 1);
+        e0[i] = z_ptr[dc];
+        e1[i] = di < d1 ? z_ptr[dc + 1] : 0;
+        v[i] = y[dc];
+        pold[i] = pp[dc];
     }
-    if (d2 < d1) {
-        const double c = z_row_dot(z_ptr[d2], z_ptr[d2 + 1], z_col, z_val, delta);
-        v2 = y[d2] + c;
-        pold2 = pp[d2];
+    double hs = masked_share<kThreads, kCoarseRowsMax / kCoarseRowWaves / kThreads>(hparts, nhp);
+    if (z_col) {
+        int32_t zc[R][4];
+        double zv[R][4];
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {  // clamped to the row (and to the array for an empty one)
+                const int e = max(min(e0[i] + u, e1[i] - 1), 0);
+                zc[i][u] = z_col[e];
+                zv[i][u] = z_val[e];
+            }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = delta[zc[i][u]];
+            double c = 0.0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c = e0[i] + u < e1[i] ? fma(zv[i][u], x[u], c) : c;
+            if (e0[i] + 4 < e1[i]) c = z_row_dot(e0[i] + 4, e1[i], z_col, z_val, delta, c);
+            v[i] += c;
+        }
     }
-    const double rho = st->ry + block_sum(strided_share<kThreads, 8>(hparts, nhp), lds);
+    hs = wave_sum(hs);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = hs;
+    if (threadIdx.x == 0) sflag = flag;
+    __syncthreads();
+    if (sflag != kRunning) return;
+    const double rho = ry + ((lds[0] + lds[1]) + (lds[2] + lds[3]));
     const bool bad = !isfinite(rho);
-    const double beta = rho / st->rho[(it + 1) & 1];
+    const double beta = rho / rho_old;
     if (vb == 0 && threadIdx.x == 0) {
         if (bad) {
             st->flag = kBreakdown;
@@ -974,9 +1072,10 @@ __device__ __forceinline__ void k_prolong_p_body(int vb, int64_t n, int32_t nwg,
         }
     }
     if (bad) return;
-    if (d < d1) pc[d] = fma(beta, pold, v);
-    if (d2 < d1) pc[d2] = fma(beta, pold2, v2);
-    for (d += 2 * kThreads; d < d1; d += kThreads) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (d + i * kThreads < d1) pc[d + i * kThreads] = fma(beta, pold[i], v[i]);
+    for (d += R * kThreads; d < d1; d += kThreads) {
         const double c = z_row_dot(z_ptr[d], z_ptr[d + 1], z_col, z_val, delta);
         pc[d] = fma(beta, pp[d], y[d] + c);
     }
@@ -1118,6 +1217,7 @@ __global__ __launch_bounds__(kSpmvThreads) void k_ms_spmv(const MsTable *__restr
 // first stage of p^T q for system blockIdx.x / kAlphaParts (as k_alpha)
 __global__ __launch_bounds__(1024) void k_ms_alpha(const MsSys *__restrict__ sys) {
     const MsSys &S = sys[blockIdx.x / kAlphaParts];
+    if (fold_alpha(S.spmv_nwg)) return;  // its update adds the partials itself
     k_alpha_body(blockIdx.x % kAlphaParts, S.part_a, S.spmv_nwg, S.part_d, S.st);
 }
 
@@ -1126,7 +1226,9 @@ __global__ __launch_bounds__(kThreads) void k_ms_update_bj(const MsTable *__rest
     const int s = ms_find(tab, kMsBj, blockIdx.x);
     const MsSys &S = sys[s];
     k_update_bj_body<double>(blockIdx.x - tab->off[kMsBj][s], S.bj_ntiles, S.bj_nwg, S.bj_wg_start, S.u, S.r, S.y,
-                             S.q, S.p0, S.p1, S.minv, S.bj_rowoff, S.bj_meta, S.part_b, S.part_c, S.part_d, S.st);
+                             S.q, S.p0, S.p1, S.minv, S.bj_rowoff, S.bj_meta, S.part_b, S.part_c,
+                             fold_alpha(S.spmv_nwg) ? S.part_a : S.part_d,
+                             fold_alpha(S.spmv_nwg) ? S.spmv_nwg : kAlphaParts, S.st);
 }
 
 __global__ __launch_bounds__(kThreads) void k_ms_bj(const MsTable *__restrict__ tab, const MsSys *__restrict__ sys) {
@@ -1258,21 +1360,26 @@ hipError_t launch_spmv_residual(const dpcg_ctx *c, const double *x, const double
 }
 
 hipError_t launch_update_bj(const dpcg_ctx *c, double *u, Workspace &w, bool fused) {
-    hipLaunchKernelGGL(k_alpha, dim3(kAlphaParts), dim3(1024), 0, c->stream, (const double *)w.part_a, c->spmv.nwg,
-                       w.part_d, (const State *)w.st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const bool fold = fold_alpha(c->spmv.nwg);
+    if (!fold) {
+        hipLaunchKernelGGL(k_alpha, dim3(kAlphaParts), dim3(1024), 0, c->stream, (const double *)w.part_a,
+                           c->spmv.nwg, w.part_d, (const State *)w.st);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const double *parts = fold ? w.part_a : w.part_d;
+    const int32_t n_pq = fold ? c->spmv.nwg : kAlphaParts;
     if (c->inner32)
         hipLaunchKernelGGL(k_update_bj<float>, dim3(c->bj_nwg), dim3(kThreads), 0, c->stream, c->bj_ntiles,
                            c->bj_nwg, c->bj_wg_start, u, w.r, w.y, (const double *)w.q, (const double *)w.p[0],
                            (const double *)w.p[1], (const float *)c->minv32, c->bj_rowoff, c->bj_meta, w.part_b,
-                           fused ? w.part_c : nullptr, (const double *)w.part_d, w.st);
+                           fused ? w.part_c : nullptr, parts, n_pq, w.st);
     else
         hipLaunchKernelGGL(k_update_bj<double>, dim3(c->bj_nwg), dim3(kThreads), 0, c->stream, c->bj_ntiles,
                            c->bj_nwg, c->bj_wg_start, u, w.r, w.y, (const double *)w.q, (const double *)w.p[0],
                            (const double *)w.p[1], (const double *)c->minv, c->bj_rowoff, c->bj_meta, w.part_b,
-                           fused ? w.part_c : nullptr, (const double *)w.part_d, w.st);
-    e = hipGetLastError();
+                           fused ? w.part_c : nullptr, parts, n_pq, w.st);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_bj_dense(c, w.r, w.y, w.st);
 }

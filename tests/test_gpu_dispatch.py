@@ -63,3 +63,16 @@ def test_coarse_product_forms(k):
     assert np.linalg.norm(d - ref) <= 1e-13 * k ** 0.5 * np.linalg.norm(ref) + 1e-14
     assert info["status"] == 0
     assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
+
+
+@pytest.mark.parametrize("nb", [1, 85, 86, 4096, 4097, 131072, 131073])
+def test_step_length_partials(nb):
+    """p^T q from up to 64 partials, from the SpMV's own up to 2048 (64 block rows each), and
+    through a first stage above; 85 block rows fill one tile of the update, 86 start another.
+    Blocks of 6 unknowns, the last one of 3 where nb is odd."""
+    K = chain(nb)
+    x = np.random.default_rng(3).standard_normal(3 * nb)
+    with solver(K, [0] if nb > 1 else [], block=6) as s:
+        u, info = s.solve(torch.as_tensor(K @ x, device=DEV), tol=1e-13)
+    assert info["status"] == 0
+    assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
