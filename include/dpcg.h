@@ -52,7 +52,7 @@ enum {
 
 typedef struct {
     int32_t max_iter;          /* iteration cap (K p products); default 20000            */
-    int32_t check_every;       /* iterations enqueued between host polls; default 16     */
+    int32_t check_every;       /* most iterations enqueued ahead of the last known state; default 16 */
     int32_t use_initial_guess; /* 1: u (or lambda) holds u_{-1} of Algorithm 2 on entry */
     int32_t record_history;    /* 1: keep ||r_i||/||f|| for i = 0..iterations            */
     int32_t precision;         /* DPCG_PREC_FP64 (default) or DPCG_PREC_MIXED            */

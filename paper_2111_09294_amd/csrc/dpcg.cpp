@@ -63,27 +63,35 @@ namespace {
 // Pinned state mirrors and timing events are kept in process-wide free lists: creating
 // and releasing them costs milliseconds, and handles come and go once per system.
 std::mutex g_pool_mutex;
-std::vector<State *> g_pinned_states;
+struct HostMirror {
+    State st;
+    alignas(64) uint64_t progress;
+};
+std::vector<HostMirror *> g_mirrors;
 std::vector<hipEvent_t> g_events;
 
-State *take_pinned_state() {
+// The pinned mirror of a workspace: the state's copy and the progress word.
+bool take_mirror(Workspace &w) {
+    HostMirror *m = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        if (!g_pinned_states.empty()) {
-            State *s = g_pinned_states.back();
-            g_pinned_states.pop_back();
-            return s;
+        if (!g_mirrors.empty()) {
+            m = g_mirrors.back();
+            g_mirrors.pop_back();
         }
     }
-    State *s = nullptr;
-    if (hipHostMalloc((void **)&s, sizeof(State), hipHostMallocDefault) != hipSuccess) return nullptr;
-    return s;
+    if (!m && hipHostMalloc((void **)&m, sizeof(HostMirror), hipHostMallocDefault) != hipSuccess) return false;
+    w.snap = &m->st;
+    w.progress = &m->progress;
+    return true;
 }
 
-void give_pinned_state(State *s) {
-    if (!s) return;
+void give_mirror(Workspace &w) {
+    if (!w.snap) return;
     std::lock_guard<std::mutex> lk(g_pool_mutex);
-    g_pinned_states.push_back(s);
+    g_mirrors.push_back(reinterpret_cast<HostMirror *>(w.snap));
+    w.snap = nullptr;
+    w.progress = nullptr;
 }
 
 hipError_t take_event(hipEvent_t *e) {
@@ -137,8 +145,7 @@ int alloc_workspace(dpcg_ctx *c, Workspace &w) {
     char *base = nullptr;
     TRY(alloc(c, &base, workspace_bytes(c)));
     carve_workspace(c, w, base);
-    w.snap = take_pinned_state();
-    if (!w.snap) return DPCG_EHIP;
+    if (!take_mirror(w)) return DPCG_EHIP;
     return DPCG_OK;
 }
 
@@ -204,7 +211,7 @@ void release(dpcg_ctx *c) {
     release_batch(c);
     for (void *p : c->allocations) dev_release(p);
     for (auto &w : c->ws) {
-        give_pinned_state(w.snap);
+        give_mirror(w);
         if (w.hist) (void)hipFree(w.hist);
     }
     delete c;
@@ -317,6 +324,47 @@ int enqueue_iteration(dpcg_ctx *c, Workspace &w, double *u, int max_iter, int re
     return DPCG_OK;
 }
 
+// Keeps iterations enqueued on the stream (enqueue(i) for i = 0, 1, ...) until every
+// workspace's flag leaves kRunning or max_iter have been enqueued and finished.  The
+// SpMV posts the state it finds to pinned memory; the host stays at most
+// min(check_every, kAhead) iterations ahead of it, so a solve neither stops for a read-back
+// nor runs more than kAhead - 1 idle iterations past its end (with a read-back every 16
+// iterations a 10^3 solve took 2.85 ms, now 2.59; 23^3 7.3 -> 6.9 ms; three iterations cover
+// the host's 15 us per iteration of launches).  Returns the iterations enqueued, or a
+// negative status.
+constexpr int kAhead = 3;
+
+template <class Enqueue>
+int32_t follow(hipStream_t s, Workspace *const *ws, int count, int max_iter, int check_every, const Enqueue &enqueue) {
+    const int ahead = std::min(check_every, kAhead);
+    int32_t enq = 0;
+    uint32_t spins = 0;
+    while (true) {
+        bool running = false;
+        int32_t done = enq;
+        for (int i = 0; i < count; ++i) {
+            const uint64_t v = __atomic_load_n(ws[i]->progress, __ATOMIC_RELAXED);
+            if ((int32_t)(v >> 32) != kRunning) continue;
+            running = true;
+            done = std::min(done, (int32_t)(uint32_t)v);
+        }
+        if (!running || (enq >= max_iter && done >= enq)) return enq;
+        if (enq < max_iter && enq - done < ahead) {
+            const int e = enqueue(enq);
+            if (e != DPCG_OK) return e;
+            ++enq;
+            spins = 0;
+        } else if ((++spins & 4095) == 0) {
+            // nothing left on the stream (the state tells why), or an error
+            const hipError_t q = hipStreamQuery(s);
+            if (q == hipSuccess) return enq;
+            if (q != hipErrorNotReady) return DPCG_EHIP;
+        } else {
+            __builtin_ia32_pause();
+        }
+    }
+}
+
 // Algorithm 1 from the start of Algorithm 2 on workspace w until the device flag leaves
 // kRunning (thr: absolute threshold on ||r_i||).  st receives the final state, with
 // iters_done set also when the loop ended by the host-side cap (max_iter == 0).
@@ -327,17 +375,14 @@ int run_cg(dpcg_ctx *c, Workspace &w, const double *f, double *u, double thr, bo
     init.thr = thr;
     *w.snap = init;
     HIP_TRY(hipMemcpyAsync(w.st, w.snap, sizeof(State), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
     c->events_used = 0;
+    __atomic_store_n(w.progress, 0, __ATOMIC_SEQ_CST);
     TRY(enqueue_start(c, w, f, u, guess, max_iter, record));
+    Workspace *one = &w;
+    const int32_t enq = follow(c->stream, &one, 1, max_iter, check_every,
+                               [&](int32_t i) { return enqueue_iteration(c, w, u, max_iter, record, i); });
+    if (enq < 0) return enq;
     TRY(read_state(c, w, st));
-    int32_t enq = 0;
-    while (st.flag == kRunning && enq < max_iter) {
-        const int m = std::min(check_every, max_iter - enq);
-        for (int i = 0; i < m; ++i) TRY(enqueue_iteration(c, w, u, max_iter, record, enq + i));
-        enq += m;
-        TRY(read_state(c, w, st));
-    }
     if (st.flag == kRunning) st.iters_done = enq;
     if (c->timing > 0) TRY(collect_events(c, (st.iters_done + c->timing - 1) / c->timing));
     return DPCG_OK;
@@ -622,6 +667,8 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
     HIP_TRY(hipStreamSynchronize(S));
     // descriptors and phase offsets
     std::vector<MsSys> sys(count);
+    std::vector<Workspace *> ws(count);
+    bool fold = true;  // every system's update adds its own p^T q
     MsTable tab{};
     tab.nsys = count;
     int tot[kMsPhases] = {};
@@ -680,12 +727,16 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         d.cpart = w.cpart;
         d.hdp = w.hdp;
         d.st = w.st;
+        d.progress = w.progress;
+        __atomic_store_n(w.progress, fnorm[i] > 0.0 ? 0 : (uint64_t)kConverged << 32, __ATOMIC_SEQ_CST);
+        ws[i] = &w;
         const int n_ph[kMsPhases] = {round8(c->spmv.nwg), 1, round8(c->bj_nwg), std::max(1, c->k),
                                      c->k == 0                ? 0
                                      : coarse_by_rows(c->k) ? coarse_parts(c->k, c->coarse_nt)
                                                             : (int)coarse_tile_count(c->coarse_nt),
                                      coarse_by_rows(c->k) ? 0 : c->coarse_nt,
                                      round8(c->vec_nwg)};
+        fold = fold && fold_alpha(c->spmv.nwg);
         for (int ph = 0; ph < kMsPhases; ++ph) {
             tab.off[ph][i] = tot[ph];
             tot[ph] += n_ph[ph];
@@ -731,27 +782,18 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         for (int i = 0; i < count; ++i) st[i] = *hs[i]->ws[0].snap;
         return DPCG_OK;
     };
+    const int32_t enq = follow(S, ws.data(), count, max_iter, opt.check_every, [&](int32_t) -> int {
+        LAUNCH(launch_ms_spmv_p(S, T, Y, tot[kMsSpmv]));
+        if (!fold) LAUNCH(launch_ms_alpha(S, Y, count));
+        LAUNCH(launch_ms_update_bj(S, T, Y, tot[kMsBj]));
+        LAUNCH(launch_ms_restrict(S, T, Y, tot[kMsRestrict], 1, 1, 1, max_iter));
+        LAUNCH(launch_ms_coarse(S, T, Y, tot[kMsCoarse], 2));
+        LAUNCH(launch_ms_coarse_sum(S, T, Y, tot[kMsCoarseSum], 2));
+        LAUNCH(launch_ms_prolong(S, T, Y, tot[kMsVec], 2, 0));
+        return DPCG_OK;
+    });
+    if (enq < 0) return enq;
     TRY(read_all());
-    int32_t enq = 0;
-    auto any_running = [&]() {
-        for (int i = 0; i < count; ++i)
-            if (st[i].flag == kRunning) return true;
-        return false;
-    };
-    while (any_running() && enq < max_iter) {
-        const int m = std::min(opt.check_every, max_iter - enq);
-        for (int it = 0; it < m; ++it) {
-            LAUNCH(launch_ms_spmv_p(S, T, Y, tot[kMsSpmv]));
-            LAUNCH(launch_ms_alpha(S, Y, count));
-            LAUNCH(launch_ms_update_bj(S, T, Y, tot[kMsBj]));
-            LAUNCH(launch_ms_restrict(S, T, Y, tot[kMsRestrict], 1, 1, 1, max_iter));
-            LAUNCH(launch_ms_coarse(S, T, Y, tot[kMsCoarse], 2));
-            LAUNCH(launch_ms_coarse_sum(S, T, Y, tot[kMsCoarseSum], 2));
-            LAUNCH(launch_ms_prolong(S, T, Y, tot[kMsVec], 2, 0));
-        }
-        enq += m;
-        TRY(read_all());
-    }
     int worst = DPCG_OK;
     const double ms = now_ms() - t0;
     for (int i = 0; i < count; ++i) {

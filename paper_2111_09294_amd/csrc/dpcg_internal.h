@@ -149,6 +149,7 @@ struct Workspace {
     double *dcor = nullptr;     // mixed precision: correction of one inner solve
     State *st = nullptr;        // device
     State *snap = nullptr;      // pinned host mirror
+    uint64_t *progress = nullptr;  // pinned: (flag << 32 | iterations done), posted by the SpMV
     double *hist = nullptr;     // device, ||r_i|| per iteration
     int64_t hist_cap = 0;
     std::vector<double> host_hist;
@@ -239,6 +240,7 @@ struct MsSys {
     int32_t coarse_nt, pad2;
     double *cpart, *hdp;
     State *st;
+    uint64_t *progress;
 };
 
 struct MsTable {

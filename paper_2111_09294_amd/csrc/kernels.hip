@@ -293,6 +293,15 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv(SpmvShape sh, const int32
 }
 
 
+// Tells the host (pinned memory) the flag and the iterations done, so that it can keep a
+// few iterations enqueued without waiting for the stream.  The SpMV's first workgroup does
+// it as the kernel starts: a kernel ends only once the host's bus has taken the store (about
+// 1 us), which the rest of the product hides and the short kernels do not.
+__device__ __forceinline__ void post_progress(uint64_t *progress, int32_t flag, int32_t done) {
+    __hip_atomic_store(progress, (uint64_t)(uint32_t)flag << 32 | (uint32_t)done, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Matrix product of Algorithm 1 for iteration i = st->iter: q = K p_i (p_i in buffer
 // i & 1, formed by the prolongation or the beta kernel) and partials of p_i^T q.  Only
 // single-workgroup kernels and workgroup 0 of later kernels change the flag, so it is
@@ -304,7 +313,7 @@ __device__ __forceinline__ void k_spmv_p_body(int vb, SpmvShape sh, const int32_
                                                          const V *__restrict__ bval, int64_t nnzb,
                                                          const double *p0, const double *p1,
                                                          double *__restrict__ q, double *__restrict__ part_pq,
-                                                         const State *st) {
+                                                         const State *st, uint64_t *progress) {
     __shared__ double lds[kSpmvWaves];
     const int w = xcd_remap(vb, sh.nwg);
     int s0, s1;
@@ -316,8 +325,10 @@ __device__ __forceinline__ void k_spmv_p_body(int vb, SpmvShape sh, const int32_
         beg = brow_ptr[row];
         end = brow_ptr[row + 1];
     }
-    if (st->flag != kRunning) return;
-    const double *__restrict__ p = (st->iter & 1) ? p1 : p0;
+    const int32_t flag = st->flag, it = st->iter;
+    if (vb == 0 && threadIdx.x == 0) post_progress(progress, flag, it);
+    if (flag != kRunning) return;
+    const double *__restrict__ p = (it & 1) ? p1 : p0;
     XPlain xl{p};
     double acc = 0.0;
     for (int s = s0; s < s1; ++s) {
@@ -346,8 +357,8 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv_p(SpmvShape sh, const int
                                                          const V *__restrict__ bval, int64_t nnzb,
                                                          const double *p0, const double *p1,
                                                          double *__restrict__ q, double *__restrict__ part_pq,
-                                                         const State *st) {
-    k_spmv_p_body<G, V, CI>(blockIdx.x, sh, brow_ptr, bcol, bval, nnzb, p0, p1, q, part_pq, st);
+                                                         const State *st, uint64_t *progress) {
+    k_spmv_p_body<G, V, CI>(blockIdx.x, sh, brow_ptr, bcol, bval, nnzb, p0, p1, q, part_pq, st, progress);
 }
 
 
@@ -1134,20 +1145,20 @@ hipError_t spmv_p_g(const dpcg_ctx *c, Workspace &w, hipEvent_t ev0, hipEvent_t 
     if (c->inner32 && b16)
         hipExtLaunchKernelGGL((k_spmv_p<G, float, int16_t>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream, ev0,
                               ev1, 0, sh, c->brow_ptr, b16, (const float *)c->bval32, c->nnzb,
-                              (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a, (const State *)w.st);
+                              (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a, (const State *)w.st, w.progress);
     else if (c->inner32)
         hipExtLaunchKernelGGL((k_spmv_p<G, float, int32_t>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream, ev0,
                               ev1, 0, sh, c->brow_ptr, (const int32_t *)c->bcol, (const float *)c->bval32, c->nnzb,
-                              (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a, (const State *)w.st);
+                              (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a, (const State *)w.st, w.progress);
     else if (b16)
         hipExtLaunchKernelGGL((k_spmv_p<G, double, int16_t>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream,
                               ev0, ev1, 0, sh, c->brow_ptr, b16, (const double *)c->bval, c->nnzb,
-                              (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a, (const State *)w.st);
+                              (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a, (const State *)w.st, w.progress);
     else
         hipExtLaunchKernelGGL((k_spmv_p<G, double, int32_t>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream,
                               ev0, ev1, 0, sh, c->brow_ptr, (const int32_t *)c->bcol, (const double *)c->bval,
                               c->nnzb, (const double *)w.p[0], (const double *)w.p[1], w.q, w.part_a,
-                              (const State *)w.st);
+                              (const State *)w.st, w.progress);
     return hipGetLastError();
 }
 
@@ -1198,10 +1209,10 @@ __global__ __launch_bounds__(kSpmvThreads) void k_ms_spmv(const MsTable *__restr
     const SpmvShape sh{S.nb, S.steps, S.spmv_nwg};
     if (MODE == 0) {
         switch (S.group) {
-            case 4: k_spmv_p_body<4, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st); break;
-            case 8: k_spmv_p_body<8, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st); break;
-            case 16: k_spmv_p_body<16, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st); break;
-            default: k_spmv_p_body<32, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st); break;
+            case 4: k_spmv_p_body<4, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+            case 8: k_spmv_p_body<8, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+            case 16: k_spmv_p_body<16, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+            default: k_spmv_p_body<32, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
         }
     } else {
         if (S.st->flag != kRunning) return;

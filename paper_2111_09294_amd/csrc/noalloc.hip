@@ -78,6 +78,7 @@ int dpcg_solve_noalloc(dpcg_handle h, const double *f, double *u, double tol, co
     dpcg::carve_workspace(h, w, base);
     dpcg::State snap{};
     w.snap = &snap;  // pageable host mirror of the state: nothing to allocate
+    w.progress = h->ws[0].progress;
     // kernel timing draws events from a pool that may create some: off for this call
     const int32_t timing = h->timing;
     h->timing = 0;
