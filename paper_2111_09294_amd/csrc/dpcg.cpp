@@ -325,9 +325,9 @@ int enqueue_iteration(dpcg_ctx *c, Workspace &w, double *u, int max_iter, int re
 }
 
 // Keeps iterations enqueued on the stream (enqueue(i) for i = 0, 1, ...) until every
-// workspace's flag leaves kRunning or max_iter have been enqueued and finished.  The
+// workspace's flag leaves kRunning or max_iter have been enqueued.  The
 // SpMV posts the state it finds to pinned memory; the host stays at most
-// min(check_every, kAhead) iterations ahead of it, so a solve neither stops for a read-back
+// min(check_every, kAhead) iterations ahead of the last one started, so a solve neither stops for a read-back
 // nor runs more than kAhead - 1 idle iterations past its end (with a read-back every 16
 // iterations a 10^3 solve took 2.85 ms, now 2.59; 23^3 7.3 -> 6.9 ms; three iterations cover
 // the host's 15 us per iteration of launches).  Returns the iterations enqueued, or a
@@ -341,15 +341,15 @@ int32_t follow(hipStream_t s, Workspace *const *ws, int count, int max_iter, int
     uint32_t spins = 0;
     while (true) {
         bool running = false;
-        int32_t done = enq;
+        int32_t started = enq;
         for (int i = 0; i < count; ++i) {
             const uint64_t v = __atomic_load_n(ws[i]->progress, __ATOMIC_RELAXED);
             if ((int32_t)(v >> 32) != kRunning) continue;
             running = true;
-            done = std::min(done, (int32_t)(uint32_t)v);
+            started = std::min(started, (int32_t)(uint32_t)v);
         }
-        if (!running || (enq >= max_iter && done >= enq)) return enq;
-        if (enq < max_iter && enq - done < ahead) {
+        if (!running || enq >= max_iter) return enq;
+        if (enq - started < ahead) {
             const int e = enqueue(enq);
             if (e != DPCG_OK) return e;
             ++enq;

@@ -149,7 +149,7 @@ struct Workspace {
     double *dcor = nullptr;     // mixed precision: correction of one inner solve
     State *st = nullptr;        // device
     State *snap = nullptr;      // pinned host mirror
-    uint64_t *progress = nullptr;  // pinned: (flag << 32 | iterations done), posted by the SpMV
+    uint64_t *progress = nullptr;  // pinned: (flag << 32 | iterations started), posted by the SpMV
     double *hist = nullptr;     // device, ||r_i|| per iteration
     int64_t hist_cap = 0;
     std::vector<double> host_hist;

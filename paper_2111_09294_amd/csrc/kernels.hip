@@ -293,12 +293,12 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv(SpmvShape sh, const int32
 }
 
 
-// Tells the host (pinned memory) the flag and the iterations done, so that it can keep a
+// Tells the host (pinned memory) the flag and the iterations started, so that it can keep a
 // few iterations enqueued without waiting for the stream.  The SpMV's first workgroup does
 // it as the kernel starts: a kernel ends only once the host's bus has taken the store (about
 // 1 us), which the rest of the product hides and the short kernels do not.
-__device__ __forceinline__ void post_progress(uint64_t *progress, int32_t flag, int32_t done) {
-    __hip_atomic_store(progress, (uint64_t)(uint32_t)flag << 32 | (uint32_t)done, __ATOMIC_RELAXED,
+__device__ __forceinline__ void post_progress(uint64_t *progress, int32_t flag, int32_t started) {
+    __hip_atomic_store(progress, (uint64_t)(uint32_t)flag << 32 | (uint32_t)started, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -326,7 +326,7 @@ __device__ __forceinline__ void k_spmv_p_body(int vb, SpmvShape sh, const int32_
         end = brow_ptr[row + 1];
     }
     const int32_t flag = st->flag, it = st->iter;
-    if (vb == 0 && threadIdx.x == 0) post_progress(progress, flag, it);
+    if (vb == 0 && threadIdx.x == 0) post_progress(progress, flag, it + 1);
     if (flag != kRunning) return;
     const double *__restrict__ p = (it & 1) ? p1 : p0;
     XPlain xl{p};
