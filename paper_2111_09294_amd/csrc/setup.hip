@@ -1357,73 +1357,134 @@ __device__ __forceinline__ void gj_sweep_tile(int p, int nt, int I, int J, const
 constexpr int kCb = 64;
 constexpr int kCbLd = kCb + 1;  // LDS row stride: a column's 16 rows in distinct banks
 
-// P = S^-1 (symmetrised, in place) for the 64 x 64 SPD pivot block S in LDS (row stride
-// kCbLd) by Gauss-Jordan elimination without pivoting, as pivot_inverse, in its
-// symmetric form: during the in-place elimination of a symmetric matrix, entry (k, c)
-// equals sigma_c times entry (c, k), sigma_c = -1 for the columns already pivoted and +1
-// for the others, so step k reads only column k and takes row k from it.  Thread
-// (ty, tx) = (t / 64, t % 64) keeps rows 16 ty + q, q < 16, of column tx in registers;
-// the lane that owns column k + 1 writes it to W (2 kCb doubles, ping-pong by step
-// parity), one barrier per step.  Pivot j is tested against kdim * DBL_EPSILON times the
-// original diagonal entry gcol0 + j; returns whether one failed (in every thread).
-__device__ __forceinline__ bool pivot_inverse64(double *S, double *W, const double *__restrict__ diag0, int64_t gcol0,
-                                                int32_t kdim) {
-    __shared__ int bad_s;
-    const int tx = threadIdx.x & 63, r0 = (threadIdx.x >> 6) * 16;
-    const int64_t gmine = gcol0 + threadIdx.x;
-    const double myfl = ((int)threadIdx.x < kCb && gmine < kdim) ? (double)kdim * DBL_EPSILON * fabs(diag0[gmine]) : 0.0;
-    if (threadIdx.x == 0) bad_s = 0;
-    double a[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) a[q] = S[(r0 + q) * kCbLd + tx];
-    if ((int)threadIdx.x < kCb) W[threadIdx.x] = S[threadIdx.x * kCbLd];  // column 0
-    bool bad = false;
-    __syncthreads();
-#pragma unroll 1
-    for (int k = 0; k < kCb; ++k) {
-        const double *col = W + (k & 1) * kCb;
-        double *nxt = W + ((k & 1) ^ 1) * kCb;
-        // all LDS reads of the step first (one wait)
-        const double p = col[k];
-        const double ck = col[tx];
-        double rk[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) rk[q] = col[r0 + q];
-        const double kc = tx < k ? -ck : ck;  // entry (k, tx)
-        if ((int)threadIdx.x == k && (!(p > myfl) || !isfinite(p))) bad = true;
+// v from lane K of each row of 16 lanes, in every lane of the row (one DPP move per half)
+template <int K>
+__device__ __forceinline__ double row_bcast(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + K, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + K, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+// v from row G of 16 lanes, lane by lane, in every row: the row swaps of gfx950 with both
+// operands the same register (odd rows of one against even rows of the other, then the
+// halves)
+template <int G>
+__device__ __forceinline__ int rows_bcast_b32(int v) {
+    const auto h = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const unsigned x = h[G & 1];
+    const auto w = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return (int)w[G >> 1];
+}
+template <int G>
+__device__ __forceinline__ double rows_bcast(double v) {
+    return __hiloint2double(rows_bcast_b32<G>(__double2hiint(v)), rows_bcast_b32<G>(__double2loint(v)));
+}
+
+// Steps K .. 15 of the in-place Gauss-Jordan elimination (as pivot_inverse) of a 16 x 16
+// block held by one wave: lane l keeps elements (l / 16 + 4 v, l % 16), v < 4, the layout of
+// the matrix instruction's result.  Row K and column K travel by lane moves within the vector
+// unit (through the LDS crossbar a step took 0.2 us), no barrier.  Pivot K is kept in the
+// lanes of column K.
+template <int K>
+__device__ __forceinline__ void gj16_steps(double (&a)[4], double &pivots) {
+    if constexpr (K < 16) {
+        const int l = threadIdx.x & 63, c = l & 15, g = l >> 4;
+        const double rowk = rows_bcast<K % 4>(a[K / 4]);
+        const double p = row_bcast<K>(rowk);
+        pivots = c == K ? p : pivots;
         // 1/p: hardware reciprocal refined by two Newton steps
         double ip = __builtin_amdgcn_rcp(p);
         ip = fma(ip, fma(-p, ip, 1.0), ip);
         ip = fma(ip, fma(-p, ip, 1.0), ip);
-        const double kcip = kc * ip;
+        const double rip = rowk * ip;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const double m = -rk[q] * ip;
-            const double v = fma(m, kc, a[q]);
-            a[q] = (tx == k) ? m : v;
+        for (int v = 0; v < 4; ++v) {
+            const double m = -row_bcast<K>(a[v]) * ip;
+            double x = fma(m, rowk, a[v]);
+            x = c == K ? m : x;
+            if (v == K / 4) x = g == K % 4 ? (c == K ? ip : rip) : x;
+            a[v] = x;
         }
-        if (k >= r0 && k < r0 + 16) {  // row k lies in this wave: a uniform branch
+        gj16_steps<K + 1>(a, pivots);
+    }
+}
+
+// P = S^-1 (symmetrised, in place) for the 64 x 64 SPD pivot block S in LDS (row stride
+// kCbLd) by Gauss-Jordan elimination without pivoting, in four stages of 16 pivots.  Stage q
+// of the 256 threads: every wave inverts the 16 x 16 block S_qq in its own registers; wave w
+// forms the new row block T_w = P S_qw and the new column block -S_wq P; then S_wJ -= S_wq T_J
+// on the matrix cores.  P is symmetric, so its registers serve as either operand.  Two
+// barriers a stage: what bounds the routine is one wave's chain of 64 pivot steps.  A barrier
+// per pivot step over the whole block took 38 us in all, this 15; a sweep of the coarse
+// inversion, which ends with the next pivot's inverse, went from 44 to 21 us up to k = 1000
+// and from 57 to 46.5 us at k = 4528.  Pivot j is tested against kdim * DBL_EPSILON times the
+// original diagonal entry gcol0 + j; returns whether one failed (in every thread).
+__device__ __forceinline__ bool pivot_inverse64(double *S, const double *__restrict__ diag0, int64_t gcol0,
+                                                int32_t kdim) {
+    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, c = l & 15, g = l >> 4;
+    double floors[4];  // of pivots 16 q + c
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (r0 + q == k) a[q] = (tx == k) ? ip : kcip;
+    for (int q = 0; q < 4; ++q) {
+        const int64_t gmine = gcol0 + 16 * q + c;
+        floors[q] = gmine < kdim ? (double)kdim * DBL_EPSILON * fabs(diag0[gmine]) : 0.0;
+    }
+    bool bad = false;
+    // one stage's code for all four: unrolled, the fetch of 64 steps of code costs as much as
+    // running them
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        const double fl = q < 2 ? (q == 0 ? floors[0] : floors[1]) : (q == 2 ? floors[2] : floors[3]);
+        double inv[4], col[4], pivots = 1.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            inv[v] = S[(16 * q + g + 4 * v) * kCbLd + 16 * q + c];
+            col[v] = S[(16 * wv + c) * kCbLd + 16 * q + g + 4 * v];  // operand rows of S_wq
         }
-        if (tx == k + 1) {
+        gj16_steps<0>(inv, pivots);
+        bad = bad || !(pivots > fl) || !isfinite(pivots);
+        dbl4 e = {0.0, 0.0, 0.0, 0.0};
+        if (wv != q) {
+            dbl4 t = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int q = 0; q < 16; ++q) nxt[r0 + q] = a[q];
+            for (int v = 0; v < 4; ++v) {
+                t = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[v], S[(16 * q + g + 4 * v) * kCbLd + 16 * wv + c], t, 0, 0, 0);
+                e = __builtin_amdgcn_mfma_f64_16x16x4f64(-col[v], inv[v], e, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[(16 * q + g + 4 * v) * kCbLd + 16 * wv + c] = t[v];
+        }
+        __syncthreads();
+        if (wv != q) {
+#pragma unroll
+            for (int j = 1; j < 4; ++j) {  // the column blocks other than q
+                const int J = (q + j) & 3;
+                dbl4 x;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[v] = S[(16 * wv + g + 4 * v) * kCbLd + 16 * J + c];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    x = __builtin_amdgcn_mfma_f64_16x16x4f64(-col[v], S[(16 * q + g + 4 * v) * kCbLd + 16 * J + c], x,
+                                                             0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) S[(16 * wv + g + 4 * v) * kCbLd + 16 * J + c] = x[v];
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[(16 * wv + g + 4 * v) * kCbLd + 16 * q + c] = e[v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[(16 * q + g + 4 * v) * kCbLd + 16 * q + c] = inv[v];
         }
         __syncthreads();
     }
-    if (bad) atomicOr(&bad_s, 1);
+    const int r0 = wv * 16;
+    double a[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) S[(r0 + q) * kCbLd + tx] = a[q];
+    for (int q = 0; q < 16; ++q) a[q] = 0.5 * (S[(r0 + q) * kCbLd + l] + S[l * kCbLd + r0 + q]);
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 16; ++q) a[q] = 0.5 * (S[(r0 + q) * kCbLd + tx] + S[tx * kCbLd + r0 + q]);
+    for (int q = 0; q < 16; ++q) S[(r0 + q) * kCbLd + l] = a[q];
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 16; ++q) S[(r0 + q) * kCbLd + tx] = a[q];
-    __syncthreads();
-    return bad_s != 0;
+    return __any(bad);
 }
 
 // X Y for 64 x 64 tiles X, Y in LDS (row stride kCbLd) on the matrix cores: wave w of the
@@ -1461,7 +1522,7 @@ __device__ __forceinline__ double diag_tile_at(const double *__restrict__ A, int
 __global__ __launch_bounds__(256) void k_cgj_first_pivot(const double *__restrict__ A, int64_t ld, int32_t kdim,
                                                          const double *__restrict__ diag0, double *__restrict__ P,
                                                          int *fail) {
-    __shared__ double S[kCb * kCbLd], W[4 * kCb];
+    __shared__ double S[kCb * kCbLd];
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     double sv[16];
 #pragma unroll
@@ -1478,7 +1539,7 @@ __global__ __launch_bounds__(256) void k_cgj_first_pivot(const double *__restric
 #pragma unroll
     for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = sv[q];
     __syncthreads();
-    const bool bad = pivot_inverse64(S, W, diag0, 0, kdim);
+    const bool bad = pivot_inverse64(S, diag0, 0, kdim);
 #pragma unroll
     for (int q = 0; q < 16; ++q) P[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
     if (bad && threadIdx.x == 0) atomicOr(fail, 1);
@@ -1538,7 +1599,7 @@ __global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__rest
                                                    const double *__restrict__ P, double *__restrict__ Pnext,
                                                    const double *__restrict__ cbuf, const double *__restrict__ tbuf,
                                                    const double *__restrict__ diag0, int *fail) {
-    __shared__ double X[kCb * kCbLd], Y[kCb * kCbLd], W[4 * kCb];
+    __shared__ double X[kCb * kCbLd], Y[kCb * kCbLd];
     const int64_t ntl = (int64_t)nt * (nt + 1) / 2;
     const int64_t first = p + 1 < nt ? (int64_t)(p + 1) * (p + 2) / 2 + (p + 1) : 0;
     const int64_t tid = (blockIdx.x + first) % ntl;
@@ -1609,7 +1670,7 @@ __global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__rest
             Y[a * kCbLd + tb] = a >= tb ? X[a * kCbLd + tb] : X[tb * kCbLd + a];
         }
         __syncthreads();
-        const bool bad = pivot_inverse64(Y, W, diag0, r0, kdim);
+        const bool bad = pivot_inverse64(Y, diag0, r0, kdim);
 #pragma unroll
         for (int q = 0; q < 16; ++q) Pnext[(ta + 4 * q) * kCb + tb] = Y[(ta + 4 * q) * kCbLd + tb];
         if (bad && threadIdx.x == 0) atomicOr(fail, 1);
