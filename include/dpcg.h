@@ -90,7 +90,8 @@ typedef struct {
     int64_t bj_values;         /* sum of squared sizes of the blocks of <= 18 unknowns  */
     int64_t device_bytes;      /* device memory held by the handle                      */
     int64_t dense_blocks;      /* blocks of more than 18 unknowns                       */
-    int64_t dense_values;      /* entries of their stored inverses (sum of ld^2)        */
+    int64_t dense_values;      /* entries of their stored inverses (lower triangles of
+                                  32 x 32 tiles)                                        */
     int64_t spmv_col_bytes;    /* bytes per block column the iteration SpMV reads: 2 when
                                   every column fits as a 16-bit offset from its block
                                   row, else 4                                           */
@@ -121,8 +122,8 @@ void dpcg_default_options(dpcg_options *opt);
  *       1..8192 unknowns.  Blocks of up to 18 unknowns (one node's standard plus
  *       enriched DoFs, eq. block_jacobi_enr) share the fused small-block kernels.
  *       Larger blocks (the subdomain-sized blocks of Sec. 3.4: all unknowns of
- *       one subdomain, numbered consecutively) keep an explicit FP64 inverse of
- *       ld x ld entries, ld = 32 * ceil(size / 32), made by Gauss-Jordan sweeps
+ *       one subdomain, numbered consecutively) keep an explicit FP64 inverse (the
+ *       lower triangle of 32 x 32 tiles), made by Gauss-Jordan sweeps
  *       at setup and applied by a dense matrix-vector kernel each iteration;
  *       dpcg_solve_batch and dpcg_solve_many refuse handles with such blocks
  *       (DPCG_EINVAL).

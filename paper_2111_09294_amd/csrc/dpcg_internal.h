@@ -12,8 +12,9 @@
 //       bj_meta[d] = size<<8 | (d - block start), 0 for the DoFs of larger blocks.
 //       Tile w of the update kernel, [bj_wg_start[w], bj_wg_start[w+1]), holds whole
 //       small blocks (a tile may cut a large block).  Blocks of kMaxBlock+1 ..
-//       kMaxDense DoFs ("dense blocks", subdomain-sized) keep their inverse in dinv:
-//       ld x ld row-major, ld = 32 * ceil(size / 32), zero beyond size.
+//       kMaxDense DoFs ("dense blocks", subdomain-sized) keep their symmetric inverse in
+//       dinv as the lower triangle of kDenseTile^2 row-major tiles, tile (I, J) at
+//       I (I + 1) / 2 + J, diagonal tiles whole, zero beyond size.
 //   Z   CSR by rows (prolongation), Z^T and (KZ)^T as CSR with k rows
 //       (restriction), E^-1 dense row-major with leading dimension einv_ld.
 #pragma once
@@ -30,7 +31,8 @@ namespace dpcg {
 constexpr int kThreads = 256;     // threads per workgroup everywhere
 constexpr int kMaxBlock = 18;     // largest block-Jacobi block of the fused (nodal) path
 constexpr int kMaxDense = 8192;   // largest block-Jacobi block (dense path above kMaxBlock)
-constexpr int kDenseRows = 32;    // rows of a dense block per workgroup of its apply
+constexpr int kDenseTile = 32;    // a dense block's inverse is kept as the lower tiles of this size
+constexpr int kDenseStrip = 8;    // tiles of one tile row per wave of its apply
 constexpr int kMaxElemDofs = 256; // largest element (DoFs) of dpcg_element_gradient
 constexpr int kCoarseTile = 64;   // E^-1 kept as the lower-triangle tiles of this size
 constexpr int kAlphaParts = 64;   // workgroups of the first stage of p^T q
@@ -203,13 +205,18 @@ struct BatchWorkspace {
     bool grouped = false;
 };
 
-// A block-Jacobi block of more than kMaxBlock DoFs and a workgroup of its apply.
+// A block-Jacobi block of more than kMaxBlock DoFs; a wave of its apply (tiles (row, j0) ..
+// of the lower triangle, kDenseStrip at most); a tile row of the apply's sums with its strips.
 struct DenseBlk {
     int64_t off;                    // first entry of its inverse in dinv
-    int32_t start, size, ld, block; // first DoF, DoFs, leading dimension, block index
+    int64_t tile0;                  // first of its lower tiles among all blocks'
+    int32_t start, size, block, pad;  // first DoF, DoFs, block index
 };
-struct DenseChunk {
-    int32_t dense, row0;            // index in the dense table, first row
+struct DenseStrip {
+    int32_t dense, row, j0, pad;
+};
+struct DenseRow {
+    int32_t dense, row, strip0, strip1;
 };
 
 // Several systems per launch: one descriptor per system (its operator, its forward
@@ -278,10 +285,13 @@ struct dpcg_ctx {
     int64_t *bj_moff = nullptr;     // offset of each block's inverse in minv (nblocks + 1)
     int32_t bjb_ntiles = 0;
     // dense (subdomain-sized) blocks, in increasing block order
-    int32_t ndense = 0, ndchunks = 0, dense_maxld = 0;
+    int32_t ndense = 0, ndstrips = 0, ndrows = 0;
+    int64_t dense_tiles = 0;
     std::vector<dpcg::DenseBlk> dense_h;
     dpcg::DenseBlk *dense = nullptr;
-    dpcg::DenseChunk *dchunk = nullptr;
+    dpcg::DenseStrip *dstrip = nullptr;
+    dpcg::DenseRow *drow = nullptr;
+    double *dpart = nullptr;  // their apply's partial sums: one row per lower tile, then per strip
     double *dinv = nullptr;
     float *dinv32 = nullptr;
     int64_t dinv_len = 0;

@@ -636,60 +636,88 @@ __global__ __launch_bounds__(kThreads) void k_bj(int32_t ntiles, int32_t nwg, co
 }
 
 
-// y_B = M_B^-1 r_B for the blocks of more than kMaxBlock DoFs (Algorithm 3's block
-// solve with the explicit inverse of a subdomain-sized block).  A workgroup owns
-// kDenseRows consecutive rows of one block: r_B is staged in LDS (zero from the
-// block's size up to ld), each wave takes 8 rows and every lane reads 16-byte pieces of
-// all 8 rows per step, so a wave keeps 8 row streams in flight.  The row sums are
-// reduced across the wave in a fixed order.
-template <class M> struct DensePiece;
-template <> struct DensePiece<double> { static constexpr int W = 2; using T = double2; };
-template <> struct DensePiece<float> { static constexpr int W = 4; using T = float4; };
-
-__device__ __forceinline__ double piece_dot(const double2 &a, const double *x) {
-    return fma(a.y, x[1], a.x * x[0]);
-}
-__device__ __forceinline__ double piece_dot(const float4 &a, const double *x) {
-    return fma((double)a.w, x[3], fma((double)a.z, x[2], fma((double)a.y, x[1], (double)a.x * x[0])));
-}
-
+// y_B = M_B^-1 r_B for the blocks of more than kMaxBlock DoFs (Algorithm 3's block solve with
+// the explicit inverse of a subdomain-sized block), from the lower triangle of the symmetric
+// inverse: every stored value is read once and used for its own row and its mirror's.  What
+// bounds it is those bytes, 4 m^2 per block instead of 8 m^2.  Stage 1, a wave per strip of up
+// to kDenseStrip tiles of one tile row I: lane (h, b) holds rows 16 h .. 16 h + 15 of column b
+// of a tile (the sixteen loads of a tile in flight together), adds its products with r_J into
+// the strip's row sums in registers and leaves the tile's column sums with r_I, the
+// contribution to y_J, as one partial row per tile.  Stage 2 adds a tile row's strips and
+// column partials in a fixed order.
+// 8 blocks of 4,400 DoFs: 117 + 8 us against 208 us for the full rows of the inverse.
 template <class M>
 __global__ __launch_bounds__(kThreads) void k_bj_dense(const DenseBlk *__restrict__ blk,
-                                                       const DenseChunk *__restrict__ chunk,
-                                                       const double *__restrict__ r, double *__restrict__ y,
-                                                       const M *__restrict__ dinv, const State *st) {
-    constexpr int W = DensePiece<M>::W;
-    constexpr int R = kDenseRows / 4;  // rows per wave
-    using T = typename DensePiece<M>::T;
-    extern __shared__ double rb[];  // ld of the largest dense block
+                                                       const DenseStrip *__restrict__ strips, int32_t nstrips,
+                                                       int64_t ntiles, const double *__restrict__ r,
+                                                       const M *__restrict__ dinv, double *__restrict__ part,
+                                                       const State *st) {
+    constexpr int T = kDenseTile, H = T / 2;
     if (st && st->flag != kRunning) return;
-    const DenseChunk ch = chunk[xcd_remap(blockIdx.x, gridDim.x)];
-    const DenseBlk B = blk[ch.dense];
-    for (int j = threadIdx.x; j < B.ld; j += kThreads) rb[j] = j < B.size ? r[B.start + j] : 0.0;
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int i0 = ch.row0 + wave * R;
-    const int nr = min(R, B.size - i0);
-    if (nr <= 0) return;
-    const M *base = dinv + B.off + (int64_t)i0 * B.ld;
-    double acc[R];
+    const int lane = threadIdx.x & 63, b = lane & (T - 1), h = lane >> 5;
+    const int sid = xcd_remap(blockIdx.x, gridDim.x) * (kThreads / 64) + (threadIdx.x >> 6);
+    if (sid >= nstrips) return;
+    const DenseStrip S = strips[sid];
+    const DenseBlk B = blk[S.dense];
+    const double *rb = r + B.start;
+    const int64_t t0 = (int64_t)S.row * (S.row + 1) / 2;
+    const M *A = dinv + B.off + (t0 + S.j0) * (T * T) + h * H * T + b;
+    double ri[H], acc[H];
 #pragma unroll
-    for (int q = 0; q < R; ++q) acc[q] = 0.0;
-    for (int j = W * lane; j < B.ld; j += 64 * W) {
-        T v[R];
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (q < nr) v[q] = *reinterpret_cast<const T *>(base + (int64_t)q * B.ld + j);
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (q < nr) acc[q] += piece_dot(v[q], rb + j);
+    for (int a = 0; a < H; ++a) {
+        ri[a] = rb[min(S.row * T + h * H + a, B.size - 1)];  // the tile is zero beyond the block
+        acc[a] = 0.0;
     }
+    const int j1 = min(S.j0 + kDenseStrip, S.row + 1);
+    for (int j = S.j0; j < j1; ++j, A += T * T) {
+        M v[H];
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        double a = acc[q];
+        for (int a = 0; a < H; ++a) v[a] = A[a * T];
+        const double rj = rb[min(j * T + b, B.size - 1)];
+        double cs = 0.0;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        if (lane == 0 && q < nr) y[B.start + i0 + q] = a;
+        for (int a = 0; a < H; ++a) {
+            acc[a] = fma((double)v[a], rj, acc[a]);
+            cs = fma((double)v[a], ri[a], cs);
+        }
+        cs += lane_xor<32>(cs);
+        if (j < S.row && h == 0) part[(B.tile0 + t0 + j) * T + b] = cs;
+    }
+    // row sums over the 32 columns, scattered: each exchange halves the rows a lane carries
+#pragma unroll
+    for (int a = 0; a < 8; ++a) acc[a] = ((b & 16) ? acc[a + 8] : acc[a]) + lane_xor<16>((b & 16) ? acc[a] : acc[a + 8]);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) acc[a] = ((b & 8) ? acc[a + 4] : acc[a]) + lane_xor<8>((b & 8) ? acc[a] : acc[a + 4]);
+#pragma unroll
+    for (int a = 0; a < 2; ++a) acc[a] = ((b & 4) ? acc[a + 2] : acc[a]) + lane_xor<4>((b & 4) ? acc[a] : acc[a + 2]);
+    double s = ((b & 2) ? acc[1] : acc[0]) + lane_xor<2>((b & 2) ? acc[0] : acc[1]);
+    s += lane_xor<1>(s);
+    if ((b & 1) == 0) part[(ntiles + sid) * T + h * H + (b >> 1)] = s;
+}
+
+// row b >> 1 above: bits 16, 8, 4, 2 of the lane are bits 8, 4, 2, 1 of the row
+__global__ __launch_bounds__(kThreads) void k_bj_dense_sum(const DenseBlk *__restrict__ blk,
+                                                           const DenseRow *__restrict__ rows, int64_t ntiles,
+                                                           const double *__restrict__ part, double *__restrict__ y,
+                                                           const State *st) {
+    constexpr int T = kDenseTile, G = kThreads / T;
+    __shared__ double lds[G][T];
+    if (st && st->flag != kRunning) return;
+    const DenseRow R = rows[blockIdx.x];
+    const DenseBlk B = blk[R.dense];
+    const int b = threadIdx.x % T, g = threadIdx.x / T;
+    const int nt = (B.size + T - 1) / T;
+    double s = 0.0;
+    for (int i = R.strip0 + g; i < R.strip1; i += G) s += part[(ntiles + i) * T + b];
+#pragma unroll 4
+    for (int I = R.row + 1 + g; I < nt; I += G) s += part[(B.tile0 + (int64_t)I * (I + 1) / 2 + R.row) * T + b];
+    lds[g][b] = s;
+    __syncthreads();
+    if (g == 0 && R.row * T + b < B.size) {
+        double t = lds[0][b];
+#pragma unroll
+        for (int i = 1; i < G; ++i) t += lds[i][b];
+        y[B.start + R.row * T + b] = t;
     }
 }
 
@@ -1417,13 +1445,17 @@ hipError_t launch_bj(const dpcg_ctx *c, const double *r, double *y, Workspace *w
 // the dense blocks' part of y = M^-1 r, after the small blocks' kernel on the same stream
 hipError_t launch_bj_dense(const dpcg_ctx *c, const double *r, double *y, const State *st) {
     if (c->ndense == 0) return hipSuccess;
-    const size_t lds = sizeof(double) * (size_t)c->dense_maxld;
+    const dim3 grid((unsigned)((c->ndstrips + kThreads / 64 - 1) / (kThreads / 64)));
     if (c->inner32)
-        hipLaunchKernelGGL(k_bj_dense<float>, dim3(c->ndchunks), dim3(kThreads), lds, c->stream, c->dense, c->dchunk,
-                           r, y, (const float *)c->dinv32, st);
+        hipLaunchKernelGGL(k_bj_dense<float>, grid, dim3(kThreads), 0, c->stream, c->dense, c->dstrip, c->ndstrips,
+                           c->dense_tiles, r, (const float *)c->dinv32, c->dpart, st);
     else
-        hipLaunchKernelGGL(k_bj_dense<double>, dim3(c->ndchunks), dim3(kThreads), lds, c->stream, c->dense, c->dchunk,
-                           r, y, (const double *)c->dinv, st);
+        hipLaunchKernelGGL(k_bj_dense<double>, grid, dim3(kThreads), 0, c->stream, c->dense, c->dstrip, c->ndstrips,
+                           c->dense_tiles, r, (const double *)c->dinv, c->dpart, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bj_dense_sum, dim3(c->ndrows), dim3(kThreads), 0, c->stream, c->dense, c->drow,
+                       c->dense_tiles, (const double *)c->dpart, y, st);
     return hipGetLastError();
 }
 

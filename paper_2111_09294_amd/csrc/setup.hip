@@ -19,7 +19,6 @@ namespace dpcg {
 namespace {
 
 constexpr int kTileDofs = 239;   // block-Jacobi tile window: tiles hold <= 239 + 17 = 256 DoFs
-constexpr int kNb = 32;          // Gauss-Jordan pivot block
 
 // ---------------------------------------------------------------- small helpers
 __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t *lds, int64_t &total) {
@@ -1177,168 +1176,15 @@ __global__ void k_symmetrise(int32_t k, int64_t ld, const double *__restrict__ e
     }
 }
 
-// ---------------------------------------------------------------- block Gauss-Jordan
-// P = S^-1 for the symmetric positive definite 32 x 32 pivot block S (LDS) by in-place
-// Gauss-Jordan elimination without pivoting (on an SPD matrix its pivots are the Schur
-// complement pivots of the Cholesky factorisation).  Step k, pivot p = a_kk:
-//   a_rc -= a_rk a_kc / p (r, c != k),  a_kc /= p,  a_rk = -a_rk / p,  a_kk = 1 / p.
-// Thread (ty, tx) of the 256 keeps a[ty + 8q][tx], q < 4, in registers; only row k and
-// column k travel through LDS (W, ping-pong by step parity), one barrier per step.
-// Every pivot is tested against kdim * DBL_EPSILON times the original diagonal entry;
-// a failure sets *fail to 1 (failval < 0) or lowers it to failval.
-__device__ void pivot_inverse(const double *S, int lds, double *W, const double *diag0, int64_t gcol0, int32_t kdim,
-                              double *P, int *fail, int failval) {
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    double *rowk = W, *colk = W + 2 * kNb;  // [parity][32] each
-    // thread j tests pivot j; its floor is loaded before the first barrier
-    const int64_t gmine = gcol0 + threadIdx.x;
-    const double myfl = ((int)threadIdx.x < kNb && gmine < kdim) ? (double)kdim * DBL_EPSILON * fabs(diag0[gmine]) : 0.0;
-    double a[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = ty + 8 * q;
-        a[q] = S[r * lds + tx];
-        if (r == 0) rowk[tx] = a[q];
-        if (tx == 0) colk[r] = a[q];
-    }
-    bool bad = false;
-    __syncthreads();
-    // unrolled by 8 only: fully unrolled it needs ~150 VGPRs, which would cap the occupancy
-    // of every sweep workgroup at 3 waves per SIMD (this routine is inlined into the sweeps)
-#pragma unroll 8
-    for (int k = 0; k < kNb; ++k) {
-        // all LDS reads of the step first (one wait), then selects instead of branches
-        const int cb = k & 1, nb = cb ^ 1;
-        const double p = rowk[cb * kNb + k];
-        const double kc = rowk[cb * kNb + tx];
-        double rk[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) rk[q] = colk[cb * kNb + ty + 8 * q];
-        if ((int)threadIdx.x == k && (!(p > myfl) || !isfinite(p))) bad = true;
-        // 1/p: hardware reciprocal refined by two Newton steps
-        double ip = __builtin_amdgcn_rcp(p);
-        ip = fma(ip, fma(-p, ip, 1.0), ip);
-        ip = fma(ip, fma(-p, ip, 1.0), ip);
-        const double kcip = kc * ip;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int r = ty + 8 * q;
-            const double m = -rk[q] * ip;
-            double v = fma(m, kc, a[q]);
-            v = (tx == k) ? m : v;
-            v = (r == k) ? ((tx == k) ? ip : kcip) : v;
-            a[q] = v;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int r = ty + 8 * q;
-            if (r == k + 1) rowk[nb * kNb + tx] = a[q];
-            if (tx == k + 1) colk[nb * kNb + r] = a[q];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) P[(ty + 8 * q) * kNb + tx] = a[q];
-    if (bad) {
-        if (failval < 0) atomicOr(fail, 1);
-        else atomicMin(fail, failval);
-    }
-}
-
-// The 32 x 32 tile products of the sweeps on the matrix cores: wave w of the 256 threads
-// computes the 16 x 16 quarter (w / 2, w % 2) of X Y (X, Y in LDS, row stride kLd) as
-// eight v_mfma_f64_16x16x4f64 steps.  Operand lanes: a = X[row l % 16][k-step col l / 16],
-// b = Y[k-step row l / 16][col l % 16]; result item v of lane l is element
-// (l / 16 + 4 v, l % 16) of the quarter.  The stride 33 spreads a column's 16 rows over
-// distinct LDS banks.
-constexpr int kLd = kNb + 1;
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ dbl4 tile_mfma(const double *X, const double *Y) {
-    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int r = (wv >> 1) * 16 + (l & 15), c = (wv & 1) * 16 + (l & 15), kq = l >> 4;
-    dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s4 = 0; s4 < kNb; s4 += 4)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r * kLd + s4 + kq], Y[(s4 + kq) * kLd + c], acc, 0, 0, 0);
-    return acc;
-}
-
-// row and column (within the 32 x 32 tile) of result item v of this thread
-__device__ __forceinline__ int tile_row(int v) {
-    return ((threadIdx.x >> 6) >> 1) * 16 + ((threadIdx.x & 63) >> 4) + 4 * v;
-}
-__device__ __forceinline__ int tile_col() { return ((threadIdx.x >> 6) & 1) * 16 + (threadIdx.x & 15); }
-
-// One sweep with pivot block p of the dense block-Jacobi blocks' inversion: B = sweep(A).
-// Tile (I, J) of 32 x 32:
-//   I = J = p: P;  I = p: P A_pJ;  J = p: -A_Ip P;  else A_IJ - A_Ip (P A_pJ).
-// Every tile is computed from its own formula (the coarse matrix, Jacobi-scaled, uses
-// the symmetric 64-wide sweeps below instead).  All global loads of a tile are issued
-// before the first LDS store, and P A_pJ reuses the LDS of A_pJ.  The workgroup of tile
-// (p+1, p+1) also inverts the next pivot block.
-__device__ __forceinline__ void gj_sweep_tile(int p, int nt, int I, int J, const double *__restrict__ A,
-                                              double *__restrict__ B, int64_t ld, int32_t kdim,
-                                              const double *__restrict__ Pcur, double *__restrict__ Pnext,
-                                              const double *__restrict__ diag0, int *fail, int failval) {
-    __shared__ double Ps[kNb * kLd], X[kNb * kLd], Y[kNb * kLd];
-    const int64_t r0 = (int64_t)I * kNb, c0 = (int64_t)J * kNb, q0 = (int64_t)p * kNb;
-    const bool piv = I == p && J == p, rowp = !piv && I == p, colp = !piv && J == p;
-    const bool gen = !piv && !rowp && !colp;
-    const bool use_x = colp || gen, use_y = rowp || gen;  // X = A_Ip, Y = A_pJ
-    const int cc = tile_col();
-    double pr[4], xr[4], yr[4], sr[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int t = threadIdx.x + 256 * q, a = t / kNb, b = t % kNb;
-        pr[q] = Pcur[t];
-        xr[q] = use_x ? A[(r0 + a) * ld + q0 + b] : 0.0;
-        yr[q] = use_y ? A[(q0 + a) * ld + c0 + b] : 0.0;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sr[v] = gen ? A[(r0 + tile_row(v)) * ld + c0 + cc] : 0.0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int t = threadIdx.x + 256 * q, a = t / kNb, b = t % kNb;
-        Ps[a * kLd + b] = pr[q];
-        if (use_x) X[a * kLd + b] = xr[q];
-        if (use_y) Y[a * kLd + b] = yr[q];
-    }
-    __syncthreads();
-    dbl4 d;
-    if (piv) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) d[v] = Ps[tile_row(v) * kLd + cc];
-    } else if (rowp) {
-        d = tile_mfma(Ps, Y);
-    } else if (colp) {
-        const dbl4 x4 = tile_mfma(X, Ps);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) d[v] = -x4[v];
-    } else {
-        const dbl4 t4 = tile_mfma(Ps, Y);  // P A_pJ, into Y once every wave has read Y
-        __syncthreads();
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Y[tile_row(v) * kLd + cc] = t4[v];
-        __syncthreads();
-        const dbl4 x4 = tile_mfma(X, Y);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) d[v] = sr[v] - x4[v];
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) B[(r0 + tile_row(v)) * ld + c0 + cc] = d[v];
-    if (I == p + 1 && J == p + 1) {
-        __syncthreads();  // every wave is done with Y
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Y[tile_row(v) * kLd + cc] = d[v];
-        __syncthreads();
-        pivot_inverse(Y, kLd, X, diag0, (int64_t)(p + 1) * kNb, kdim, Pnext, fail, failval);
-    }
-}
-
-// ---------------------------------------------------------------- E^-1: symmetric sweeps
-// The coarse matrix is symmetric positive definite, so its block Gauss-Jordan inverse is
-// run as the symmetric sweep operator on the lower triangle of 64 x 64 tiles only.  After
+// ---------------------------------------------------------------- symmetric sweeps
+// The coarse matrix and the dense block-Jacobi blocks are symmetric positive definite, so
+// their block Gauss-Jordan inverses are run as the symmetric sweep operator on the lower
+// triangle of 64 x 64 tiles only, Jacobi-scaled.  Gauss-Jordan elimination without pivoting:
+// its pivots are the Schur complement pivots of the Cholesky factorisation.  Step k, pivot
+// p = a_kk:  a_rc -= a_rk a_kc / p (r, c != k),  a_kc /= p,  a_rk = -a_rk / p,  a_kk = 1 / p.
+// After
 // the sweeps over pivot blocks 0 .. p-1 the working matrix is symmetric up to signs: its
 // entry (i, j) equals sigma_i sigma_j times entry (j, i), sigma = -1 on the rows of the
 // pivot blocks already swept and +1 on the others, so every tile above the diagonal is a
@@ -1380,8 +1226,7 @@ __device__ __forceinline__ double rows_bcast(double v) {
     return __hiloint2double(rows_bcast_b32<G>(__double2hiint(v)), rows_bcast_b32<G>(__double2loint(v)));
 }
 
-// Steps K .. 15 of the in-place Gauss-Jordan elimination (as pivot_inverse) of a 16 x 16
-// block held by one wave: lane l keeps elements (l / 16 + 4 v, l % 16), v < 4, the layout of
+// Steps K .. 15 of the in-place Gauss-Jordan elimination of a 16 x 16 block held by one wave: lane l keeps elements (l / 16 + 4 v, l % 16), v < 4, the layout of
 // the matrix instruction's result.  Row K and column K travel by lane moves within the vector
 // unit (through the LDS crossbar a step took 0.2 us), no barrier.  Pivot K is kept in the
 // lanes of column K.
@@ -1431,8 +1276,9 @@ __device__ __forceinline__ bool pivot_inverse64(double *S, const double *__restr
     bool bad = false;
     // one stage's code for all four: unrolled, the fetch of 64 steps of code costs as much as
     // running them
+    const int stages = (int)min((int64_t)4, (kdim - gcol0 + 15) / 16);  // the identity tail inverts to itself
 #pragma unroll 1
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < stages; ++q) {
         const double fl = q < 2 ? (q == 0 ? floors[0] : floors[1]) : (q == 2 ? floors[2] : floors[3]);
         double inv[4], col[4], pivots = 1.0;
 #pragma unroll
@@ -1512,17 +1358,43 @@ __device__ __forceinline__ void cb_mfma(const double *X, const double *Y, dbl4 (
     }
 }
 
-// entry (a, b) of diagonal tile (I, I) (first row r0) of the row-major ld x ld array A,
-// from its lower half
-__device__ __forceinline__ double diag_tile_at(const double *__restrict__ A, int64_t ld, int64_t r0, int a, int b) {
-    return a >= b ? A[(r0 + a) * ld + r0 + b] : A[(r0 + b) * ld + r0 + a];
+// The lower tiles (I, J), I >= J, of a matrix under inversion: row-major ld x ld (the coarse
+// matrix) or packed tile after tile (a dense block).
+struct RowTiles {
+    double *A;
+    int64_t ld;
+    __device__ __forceinline__ double *tile(int I, int J) const { return A + (int64_t)I * kCb * ld + J * kCb; }
+    __device__ __forceinline__ int64_t stride() const { return ld; }
+};
+struct PackedTiles {
+    double *A;
+    __device__ __forceinline__ double *tile(int I, int J) const {
+        return A + ((int64_t)I * (I + 1) / 2 + J) * (kCb * kCb);
+    }
+    __device__ __forceinline__ int64_t stride() const { return kCb; }
+};
+
+// a failed pivot sets *fail to 1 (failval < 0) or lowers it to failval
+__device__ __forceinline__ void pivot_failed(int *fail, int failval) {
+    if (failval < 0) atomicOr(fail, 1);
+    else atomicMin(fail, failval);
+}
+
+// (I, J) of lower tile number tid = I (I + 1) / 2 + J
+__device__ __forceinline__ void lower_tile(int64_t tid, int &I, int &J) {
+    I = (int)((sqrt(8.0 * (double)tid + 1.0) - 1.0) * 0.5);
+    while ((int64_t)(I + 1) * (I + 2) / 2 <= tid) ++I;
+    while ((int64_t)I * (I + 1) / 2 > tid) --I;
+    J = (int)(tid - (int64_t)I * (I + 1) / 2);
 }
 
 // P_0 = A_00^-1 (symmetrised) from the first diagonal tile's lower half.
-__global__ __launch_bounds__(256) void k_cgj_first_pivot(const double *__restrict__ A, int64_t ld, int32_t kdim,
-                                                         const double *__restrict__ diag0, double *__restrict__ P,
-                                                         int *fail) {
+template <class M>
+__device__ __forceinline__ void first_pivot_body(const M &mat, int32_t kdim, const double *__restrict__ diag0,
+                                                 double *__restrict__ P, int *fail, int failval) {
     __shared__ double S[kCb * kCbLd];
+    const double *A = mat.tile(0, 0);
+    const int64_t ld = mat.stride();
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     double sv[16];
 #pragma unroll
@@ -1542,30 +1414,35 @@ __global__ __launch_bounds__(256) void k_cgj_first_pivot(const double *__restric
     const bool bad = pivot_inverse64(S, diag0, 0, kdim);
 #pragma unroll
     for (int q = 0; q < 16; ++q) P[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
-    if (bad && threadIdx.x == 0) atomicOr(fail, 1);
+    if (bad && threadIdx.x == 0) pivot_failed(fail, failval);
+}
+
+__global__ __launch_bounds__(256) void k_cgj_first_pivot(double *A, int64_t ld, int32_t kdim,
+                                                         const double *__restrict__ diag0, double *__restrict__ P,
+                                                         int *fail) {
+    first_pivot_body(RowTiles{A, ld}, kdim, diag0, P, fail, -1);
 }
 
 // Panel of sweep p, workgroup J != p: the tile A_pJ (stored below the diagonal for J < p;
 // for J > p the transpose of the stored (J, p), sign +1), T_J = P A_pJ into tbuf[J], and
 // the column tile A_Jp = s A_pJ^T into cbuf[J] (s = +1 for J > p, -1 for J < p: block row
 // J is swept, block row p not yet).  Both buffers hold nt tiles of 64 x 64, row-major.
-__global__ __launch_bounds__(256) void k_cgj_panel(int p, const double *__restrict__ A, int64_t ld,
-                                                   const double *__restrict__ P, double *__restrict__ cbuf,
-                                                   double *__restrict__ tbuf) {
+template <class M>
+__device__ __forceinline__ void panel_body(int p, int J, const M &mat, const double *__restrict__ P,
+                                           double *__restrict__ cbuf, double *__restrict__ tbuf) {
     __shared__ double S[kCb * kCbLd], Y[kCb * kCbLd];
-    const int J = blockIdx.x;
     if (J == p) return;
-    const int64_t rp = (int64_t)p * kCb, cj = (int64_t)J * kCb;
     // all loads (coalesced, row-major) before the first LDS store: P, and the stored
     // tile (p, J) for J < p or (J, p) for J > p, which is A_pJ transposed
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
-    const int64_t yo = J < p ? rp * ld + cj : cj * ld + rp;
+    const double *A = J < p ? mat.tile(p, J) : mat.tile(J, p);
+    const int64_t ld = mat.stride();
     double pv[16], yv[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int a = ta + 4 * q;
         pv[q] = P[a * kCb + tb];
-        yv[q] = A[yo + (int64_t)a * ld + tb];
+        yv[q] = A[a * ld + tb];
     }
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
@@ -1591,23 +1468,21 @@ __global__ __launch_bounds__(256) void k_cgj_panel(int p, const double *__restri
         for (int v = 0; v < 4; ++v) tj[cb_row(b, v) * kCb + cb_col(b)] = acc[b][v];
 }
 
-// Sweep p over the lower tiles (I, J), I >= J, in place (tiles numbered row by row,
-// I (I + 1) / 2 + J).  The tiles are rotated so that the next pivot tile (p + 1, p + 1)
-// is dispatched first: its workgroup also inverts it into Pnext (the critical path of
-// the sweep, overlapped with the other tiles).  P and Pnext are distinct buffers.
-__global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__restrict__ A, int64_t ld, int32_t kdim,
-                                                   const double *__restrict__ P, double *__restrict__ Pnext,
-                                                   const double *__restrict__ cbuf, const double *__restrict__ tbuf,
-                                                   const double *__restrict__ diag0, int *fail) {
+__global__ __launch_bounds__(256) void k_cgj_panel(int p, double *A, int64_t ld, const double *__restrict__ P,
+                                                   double *__restrict__ cbuf, double *__restrict__ tbuf) {
+    panel_body(p, blockIdx.x, RowTiles{A, ld}, P, cbuf, tbuf);
+}
+
+// Sweep p of lower tile (I, J), in place.  The workgroup of the next pivot tile (p + 1, p + 1)
+// also inverts it into Pnext (P and Pnext are distinct buffers).
+template <class M>
+__device__ __forceinline__ void sweep_body(int p, int I, int J, const M &mat, int32_t kdim,
+                                           const double *__restrict__ P, double *__restrict__ Pnext,
+                                           const double *__restrict__ cbuf, const double *__restrict__ tbuf,
+                                           const double *__restrict__ diag0, int *fail, int failval) {
     __shared__ double X[kCb * kCbLd], Y[kCb * kCbLd];
-    const int64_t ntl = (int64_t)nt * (nt + 1) / 2;
-    const int64_t first = p + 1 < nt ? (int64_t)(p + 1) * (p + 2) / 2 + (p + 1) : 0;
-    const int64_t tid = (blockIdx.x + first) % ntl;
-    int I = (int)((sqrt(8.0 * (double)tid + 1.0) - 1.0) * 0.5);
-    while ((int64_t)(I + 1) * (I + 2) / 2 <= tid) ++I;
-    while ((int64_t)I * (I + 1) / 2 > tid) --I;
-    const int J = (int)(tid - (int64_t)I * (I + 1) / 2);
-    const int64_t r0 = (int64_t)I * kCb, c0 = (int64_t)J * kCb;
+    double *A = mat.tile(I, J);
+    const int64_t ld = mat.stride();
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     if (I == p || J == p) {
         // pivot tile P; row p: T_J; column p: -T_I^T (transposed through LDS)
@@ -1623,7 +1498,7 @@ __global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__rest
             for (int q = 0; q < 16; ++q) v[q] = -X[tb * kCbLd + ta + 4 * q];
         }
 #pragma unroll
-        for (int q = 0; q < 16; ++q) A[(r0 + ta + 4 * q) * ld + c0 + tb] = v[q];
+        for (int q = 0; q < 16; ++q) A[(ta + 4 * q) * ld + tb] = v[q];
         return;
     }
     // all loads before the first LDS store
@@ -1639,7 +1514,7 @@ __global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__rest
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int a = cb_row(b, v), c = cb_col(b);
-            sr[4 * b + v] = I == J ? diag_tile_at(A, ld, r0, a, c) : A[(r0 + a) * ld + c0 + c];
+            sr[4 * b + v] = I == J && a < c ? A[c * ld + a] : A[a * ld + c];  // a diagonal tile's lower half
         }
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
@@ -1654,7 +1529,7 @@ __global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__rest
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             sr[4 * b + v] -= acc[b][v];
-            A[(r0 + cb_row(b, v)) * ld + c0 + cb_col(b)] = sr[4 * b + v];
+            A[cb_row(b, v) * ld + cb_col(b)] = sr[4 * b + v];
         }
     if (I == p + 1 && J == p + 1) {
         __syncthreads();  // every wave is done with X
@@ -1670,11 +1545,24 @@ __global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *__rest
             Y[a * kCbLd + tb] = a >= tb ? X[a * kCbLd + tb] : X[tb * kCbLd + a];
         }
         __syncthreads();
-        const bool bad = pivot_inverse64(Y, diag0, r0, kdim);
+        const bool bad = pivot_inverse64(Y, diag0, (int64_t)I * kCb, kdim);
 #pragma unroll
         for (int q = 0; q < 16; ++q) Pnext[(ta + 4 * q) * kCb + tb] = Y[(ta + 4 * q) * kCbLd + tb];
-        if (bad && threadIdx.x == 0) atomicOr(fail, 1);
+        if (bad && threadIdx.x == 0) pivot_failed(fail, failval);
     }
+}
+
+// The tiles, numbered row by row, are rotated so that the next pivot tile is dispatched first:
+// its inverse is the critical path of the sweep, overlapped with the other tiles.
+__global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *A, int64_t ld, int32_t kdim,
+                                                   const double *__restrict__ P, double *__restrict__ Pnext,
+                                                   const double *__restrict__ cbuf, const double *__restrict__ tbuf,
+                                                   const double *__restrict__ diag0, int *fail) {
+    const int64_t ntl = (int64_t)nt * (nt + 1) / 2;
+    const int64_t first = p + 1 < nt ? (int64_t)(p + 1) * (p + 2) / 2 + (p + 1) : 0;
+    int I, J;
+    lower_tile((blockIdx.x + first) % ntl, I, J);
+    sweep_body(p, I, J, RowTiles{A, ld}, kdim, P, Pnext, cbuf, tbuf, diag0, fail, -1);
 }
 
 // The final E^-1 from the lower tiles of the inverse X of the scaled matrix: F = S X S,
@@ -1688,10 +1576,8 @@ __global__ __launch_bounds__(256) void k_einv_from_lower(int32_t k, int64_t ld, 
     constexpr int T = kCoarseTile;
     __shared__ double F[T][T + 1];
     const int64_t tid = blockIdx.x;
-    int I = (int)((sqrt(8.0 * (double)tid + 1.0) - 1.0) * 0.5);
-    while ((int64_t)(I + 1) * (I + 2) / 2 <= tid) ++I;
-    while ((int64_t)I * (I + 1) / 2 > tid) --I;
-    const int J = (int)(tid - (int64_t)I * (I + 1) / 2);
+    int I, J;
+    lower_tile(tid, I, J);
     double *out = tiles + tid * T * T;
     for (int e = threadIdx.x; e < T * T; e += 256) {
         const int a = e / T, b = e % T;
@@ -1716,45 +1602,72 @@ __global__ __launch_bounds__(256) void k_einv_from_lower(int32_t k, int64_t ld, 
 }
 
 // ---------------------------------------------------------------- dense blocks
-// Block-Jacobi blocks of more than kMaxBlock DoFs (subdomain-sized blocks).  K_BB is
-// gathered from the block's lower triangle (mirrored), padded to ld = 32 * ceil(m / 32)
-// with the identity, and inverted by the Gauss-Jordan sweeps above, batched over the
-// blocks: the table is sorted by ld, largest first, so the blocks that still have a
-// pivot tile p form a prefix, and sweep p runs the tiles of that prefix in one launch.
-// A failed pivot lowers the flag to the block's index.
+// Block-Jacobi blocks of more than kMaxBlock DoFs (subdomain-sized blocks).  The lower
+// triangle of K_BB, Jacobi-scaled, is gathered into packed 64 x 64 tiles (the identity beyond
+// the block's size) and inverted by the symmetric sweeps above, batched over the blocks: the
+// table is sorted by tiles, most first, so the blocks that still have a pivot tile p form a
+// prefix, and sweep p runs the tiles of that prefix in one launch.  A failed pivot lowers the
+// flag to the block's index.
+// Bound by the traffic of the tiles (64 KB each per sweep): 69 sweeps of 300 us and panels of
+// 18 us for 8 blocks of 4,400 DoFs, 4.1 TB/s and 34 TFLOP/s; sweeps of 32 pivots over every
+// tile of both triangles took 138 launches of 570 us.
 struct GjMat {
-    int64_t off;    // first entry of its ld x ld matrix in the work buffers (= in dinv)
-    int64_t tile0;  // first workgroup of its tiles in a sweep (prefix of nt^2)
-    int64_t dg;     // first entry of its original diagonal in diag0 (prefix of ld)
-    int32_t ld, size, start, block;
+    int64_t tile0;  // first lower tile (prefix of nt (nt + 1) / 2), also its place in the work buffer
+    int64_t row0;   // first tile row (prefix of nt): its panels, its diagonal and scale (64 each)
+    int64_t out;    // first entry of its inverse in dinv
+    int32_t nt, size, start, block;
 };
 
+// last matrix whose first tile (row) is <= wg
+template <int64_t GjMat::*FIRST>
 __device__ __forceinline__ int gj_find(const GjMat *__restrict__ m, int count, int64_t wg) {
-    int lo = 0, hi = count - 1;  // last matrix with tile0 <= wg
+    int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (m[mid].tile0 <= wg) lo = mid;
+        if (m[mid].*FIRST <= wg) lo = mid;
         else hi = mid - 1;
     }
     return lo;
 }
 
-// rows of matrix blockIdx.y (grid-stride): the lower-triangle entries of K_BB to both
-// (i, c) and (c, i), the original diagonal to diag0, the identity beyond the block's
-// size.  A and diag0 are zero on entry.
+// scale_i = 1 / sqrt(K_ii) of the matrices' rows (1 where K_ii <= 0 or is absent, whose pivot
+// then fails the SPD test, and beyond the block's size), one wave per row
+__global__ __launch_bounds__(256) void k_dense_scale(const GjMat *__restrict__ mats, int count,
+                                                     const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
+                                                     const double *__restrict__ val, double *__restrict__ scale) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int mi = blockIdx.y; mi < count; mi += gridDim.y) {
+        const GjMat G = mats[mi];
+        for (int i = blockIdx.x * 4 + wave; i < G.nt * kCb; i += gridDim.x * 4) {
+            double d = 0.0;
+            if (i < G.size) {
+                const int64_t g = (int64_t)G.start + i;
+                for (int64_t e = ptr[g] + lane; e < ptr[g + 1]; e += 64)
+                    if (idx[e] == g) d = val[e];
+            }
+            d = wave_sum(d);  // at most one lane holds it
+            if (lane == 0) scale[G.row0 * kCb + i] = d > 0.0 ? 1.0 / sqrt(d) : 1.0;
+        }
+    }
+}
+
+// rows of matrix blockIdx.y (grid-stride): the scaled lower-triangle entries of K_BB, their
+// diagonal to diag0, the identity beyond the block's size.  W and diag0 are zero on entry.
 __global__ __launch_bounds__(256) void k_dense_gather(const GjMat *__restrict__ mats, int count,
                                                       const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
-                                                      const double *__restrict__ val, double *__restrict__ A,
+                                                      const double *__restrict__ val,
+                                                      const double *__restrict__ scale, double *__restrict__ W,
                                                       double *__restrict__ diag0) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int mi = blockIdx.y; mi < count; mi += gridDim.y) {
         const GjMat G = mats[mi];
-        double *a = A + G.off;
-        for (int i = blockIdx.x * 4 + wave; i < G.ld; i += gridDim.x * 4) {
+        const PackedTiles T{W + G.tile0 * (kCb * kCb)};
+        const double *sc = scale + G.row0 * kCb;
+        for (int i = blockIdx.x * 4 + wave; i < G.nt * kCb; i += gridDim.x * 4) {
             if (i >= G.size) {
                 if (lane == 0) {
-                    a[(int64_t)i * G.ld + i] = 1.0;
-                    diag0[G.dg + i] = 1.0;
+                    T.tile(i / kCb, i / kCb)[(i % kCb) * (kCb + 1)] = 1.0;
+                    diag0[G.row0 * kCb + i] = 1.0;
                 }
                 continue;
             }
@@ -1762,64 +1675,81 @@ __global__ __launch_bounds__(256) void k_dense_gather(const GjMat *__restrict__ 
             for (int64_t e = ptr[g] + lane; e < ptr[g + 1]; e += 64) {
                 const int64_t c = (int64_t)idx[e] - G.start;
                 if (c < 0 || c > i) continue;
-                const double v = val[e];
-                a[(int64_t)i * G.ld + c] = v;
-                a[c * G.ld + i] = v;
-                if (c == i) diag0[G.dg + i] = v;
+                const double v = (val[e] * sc[i]) * sc[c];
+                T.tile(i / kCb, (int)c / kCb)[(i % kCb) * kCb + c % kCb] = v;
+                if (c == i) diag0[G.row0 * kCb + i] = v;
             }
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict__ mats, int count,
-                                                         const double *__restrict__ A,
+__global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict__ mats, int count, double *W,
                                                          const double *__restrict__ diag0, double *__restrict__ P,
                                                          int *fail) {
-    __shared__ double S[kNb * kNb], W[kNb * kNb];
     for (int mi = blockIdx.x; mi < count; mi += gridDim.x) {
         const GjMat G = mats[mi];
         __syncthreads();
-        for (int t = threadIdx.x; t < kNb * kNb; t += 256) S[t] = A[G.off + (t / kNb) * (int64_t)G.ld + (t % kNb)];
-        __syncthreads();
-        pivot_inverse(S, kNb, W, diag0 + G.dg, 0, G.size, P + (int64_t)mi * 2 * kNb * kNb, fail, G.block);
+        first_pivot_body(PackedTiles{W + G.tile0 * (kCb * kCb)}, G.size, diag0 + G.row0 * kCb,
+                         P + (int64_t)mi * 2 * kCb * kCb, fail, G.block);
     }
 }
 
-// sweep p over the first count matrices (those with more than p pivot tiles)
-__global__ __launch_bounds__(256) void k_gjb_sweep(int p, const GjMat *__restrict__ mats, int count,
-                                                   const double *__restrict__ A, double *__restrict__ B,
-                                                   double *__restrict__ P, const double *__restrict__ diag0,
-                                                   int *fail) {
-    const int mi = gj_find(mats, count, blockIdx.x);
+// panels and sweep p over the first count matrices (those with more than p pivot tiles)
+__global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restrict__ mats, int count, double *W,
+                                                   const double *__restrict__ P, double *__restrict__ cbuf,
+                                                   double *__restrict__ tbuf) {
+    const int mi = gj_find<&GjMat::row0>(mats, count, blockIdx.x);
     const GjMat G = mats[mi];
-    const int nt = G.ld / kNb;
-    const int64_t t = blockIdx.x - G.tile0;
-    double *pv = P + (int64_t)mi * 2 * kNb * kNb;
-    gj_sweep_tile(p, nt, (int)(t / nt), (int)(t % nt), A + G.off, B + G.off, G.ld, G.size, pv + (p & 1) * kNb * kNb,
-                  pv + ((p + 1) & 1) * kNb * kNb, diag0 + G.dg, fail, G.block);
+    panel_body(p, (int)(blockIdx.x - G.row0), PackedTiles{W + G.tile0 * (kCb * kCb)},
+               P + ((int64_t)mi * 2 + (p & 1)) * (kCb * kCb), cbuf + G.row0 * (kCb * kCb), tbuf + G.row0 * (kCb * kCb));
 }
 
-__global__ __launch_bounds__(256) void k_gjb_zero(const GjMat *__restrict__ mats, int count, double *__restrict__ A) {
-    for (int mi = blockIdx.y; mi < count; mi += gridDim.y) {
-        const GjMat G = mats[mi];
-        const int64_t len = (int64_t)G.ld * G.ld;
-        for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < len; t += (int64_t)gridDim.x * 256) A[G.off + t] = 0.0;
+// The first count workgroups take the matrices' next pivot tiles (the longest ones), the
+// others every other tile.
+__global__ __launch_bounds__(256) void k_gjb_sweep(int p, const GjMat *__restrict__ mats, int count, double *W,
+                                                   double *P, const double *__restrict__ cbuf,
+                                                   const double *__restrict__ tbuf, const double *__restrict__ diag0,
+                                                   int *fail) {
+    const bool pivots = (int)blockIdx.x < count;
+    const int64_t t = (int64_t)blockIdx.x - count;
+    const int mi = pivots ? (int)blockIdx.x : gj_find<&GjMat::tile0>(mats, count, t);
+    const GjMat G = mats[mi];
+    int I = p + 1, J = p + 1;
+    if (pivots) {
+        if (I >= G.nt) return;
+    } else {
+        lower_tile(t - G.tile0, I, J);
+        if (I == p + 1 && J == p + 1) return;
+    }
+    double *Pm = P + (int64_t)mi * 2 * (kCb * kCb);
+    sweep_body(p, I, J, PackedTiles{W + G.tile0 * (kCb * kCb)}, G.size, Pm + (p & 1) * (kCb * kCb),
+               Pm + ((p + 1) & 1) * (kCb * kCb), cbuf + G.row0 * (kCb * kCb), tbuf + G.row0 * (kCb * kCb),
+               diag0 + G.row0 * kCb, fail, G.block);
+}
+
+// The inverse S X S (S the scale) from X's lower triangle, as the apply reads it: lower tiles
+// of kDenseTile^2, diagonal ones whole, zero beyond the block.  One workgroup per 64 x 64 tile.
+__global__ __launch_bounds__(256) void k_gjb_finish(const GjMat *__restrict__ mats, int count,
+                                                    const double *__restrict__ W, const double *__restrict__ scale,
+                                                    double *__restrict__ dinv) {
+    constexpr int T = kDenseTile;
+    const int mi = gj_find<&GjMat::tile0>(mats, count, blockIdx.x);
+    const GjMat G = mats[mi];
+    int I, J;
+    lower_tile(blockIdx.x - G.tile0, I, J);
+    const double *X = W + (int64_t)blockIdx.x * (kCb * kCb), *sc = scale + G.row0 * kCb;
+    const int ntd = (G.size + T - 1) / T;
+    for (int e = threadIdx.x; e < kCb * kCb; e += 256) {
+        const int sub = e / (T * T), a = e / T % T, b = e % T;
+        const int It = 2 * I + (sub >> 1), Jt = 2 * J + (sub & 1);
+        if (It >= ntd || Jt > It) continue;
+        const int r = It * T + a, c = Jt * T + b, hi = max(r, c), lo = min(r, c);
+        double v = 0.0;
+        if (hi < G.size) v = (X[(hi - I * kCb) * kCb + lo - J * kCb] * sc[lo]) * sc[hi];
+        dinv[G.out + ((int64_t)It * (It + 1) / 2 + Jt) * (T * T) + a * T + b] = v;
     }
 }
 
-// matrices with an even number of pivot tiles end their sweeps in the work buffer
-__global__ __launch_bounds__(256) void k_gjb_copy_even(const GjMat *__restrict__ mats, int count,
-                                                       const double *__restrict__ src, double *__restrict__ dst) {
-    for (int mi = blockIdx.y; mi < count; mi += gridDim.y) {
-        const GjMat G = mats[mi];
-        if ((G.ld / kNb) % 2 != 0) continue;
-        const int64_t len = (int64_t)G.ld * G.ld;
-        for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < len; t += (int64_t)gridDim.x * 256)
-            dst[G.off + t] = src[G.off + t];
-    }
-}
-
-// ---------------------------------------------------------------- value updates
 __global__ void k_to_i64(const int32_t *__restrict__ a, int64_t n, int64_t *__restrict__ out) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         out[i] = a[i];
@@ -2129,10 +2059,10 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         double *cbuf = nullptr, *tbuf = nullptr;
         HT(pool.tmp(&cbuf, ld * kCb));
         HT(pool.tmp(&tbuf, ld * kCb));
-        hipLaunchKernelGGL(k_cgj_first_pivot, dim3(1), dim3(256), 0, s, (const double *)ga, ld, k, diag0, pv, cfail);
+        hipLaunchKernelGGL(k_cgj_first_pivot, dim3(1), dim3(256), 0, s, ga, ld, k, diag0, pv, cfail);
         for (int p = 0; p < nt; ++p) {
             const double *pc = pv + (p & 1) * kCb * kCb;
-            hipLaunchKernelGGL(k_cgj_panel, dim3(nt), dim3(256), 0, s, p, (const double *)ga, ld, pc, cbuf, tbuf);
+            hipLaunchKernelGGL(k_cgj_panel, dim3(nt), dim3(256), 0, s, p, ga, ld, pc, cbuf, tbuf);
             hipLaunchKernelGGL(k_cgj_sweep, dim3((unsigned)coarse_tile_count(nt)), dim3(256), 0, s, p, nt, ga, ld, k, pc,
                                pv + ((p + 1) & 1) * kCb * kCb, (const double *)cbuf, (const double *)tbuf, diag0,
                                cfail);
@@ -2167,71 +2097,82 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     std::vector<GjMat> m(count);
     for (int i = 0; i < count; ++i) {
         const DenseBlk &D = c->dense_h[which[i]];
-        m[i] = GjMat{D.off, 0, 0, D.ld, D.size, D.start, D.block};
+        m[i] = GjMat{0, 0, D.off, (D.size + kCb - 1) / kCb, D.size, D.start, D.block};
     }
-    std::stable_sort(m.begin(), m.end(), [](const GjMat &a, const GjMat &b) { return a.ld > b.ld; });
-    std::vector<int64_t> tiles(count + 1, 0);
-    int64_t dg = 0;
+    std::stable_sort(m.begin(), m.end(), [](const GjMat &a, const GjMat &b) { return a.nt > b.nt; });
+    std::vector<int64_t> tiles(count + 1, 0), rows(count + 1, 0);
     for (int i = 0; i < count; ++i) {
-        const int64_t nt = m[i].ld / kNb;
         m[i].tile0 = tiles[i];
-        tiles[i + 1] = tiles[i] + nt * nt;
-        m[i].dg = dg;
-        dg += m[i].ld;
+        m[i].row0 = rows[i];
+        tiles[i + 1] = tiles[i] + coarse_tile_count(m[i].nt);
+        rows[i + 1] = rows[i] + m[i].nt;
     }
+    constexpr int64_t kTile = kCb * kCb;
     GjMat *md = nullptr;
-    double *X0 = nullptr, *diag0 = nullptr, *pv = nullptr;
+    double *W = nullptr, *diag0 = nullptr, *scale = nullptr, *pv = nullptr, *cbuf = nullptr, *tbuf = nullptr;
     HT(pool.tmp(&md, count));
-    HT(pool.tmp(&X0, c->dinv_len));
-    HT(pool.tmp(&diag0, dg));
-    HT(pool.tmp(&pv, (int64_t)count * 2 * kNb * kNb));
+    HT(pool.tmp(&W, tiles[count] * kTile));
+    HT(pool.tmp(&diag0, rows[count] * kCb));
+    HT(pool.tmp(&scale, rows[count] * kCb));
+    HT(pool.tmp(&pv, (int64_t)count * 2 * kTile));
+    HT(pool.tmp(&cbuf, rows[count] * kTile));
+    HT(pool.tmp(&tbuf, rows[count] * kTile));
     HT(hipMemcpyAsync(md, m.data(), sizeof(GjMat) * count, hipMemcpyHostToDevice, s));
-    HT(hipMemsetAsync(diag0, 0, sizeof(double) * dg, s));
+    HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[count] * kCb, s));
+    HT(hipMemsetAsync(W, 0, sizeof(double) * tiles[count] * kTile, s));
     const int gy = std::min(count, 65535);
-    const int ldmax = m[0].ld;
-    hipLaunchKernelGGL(k_gjb_zero, dim3(64, gy), dim3(256), 0, s, md, count, X0);
-    hipLaunchKernelGGL(k_dense_gather, dim3(std::min(1024, (ldmax + 3) / 4), gy), dim3(256), 0, s, md, count, kp, kc,
-                       kv, X0, diag0);
-    hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, count, X0, diag0, pv, bad_flag);
+    const dim3 rgrid(std::min(1024, (m[0].nt * kCb + 3) / 4), gy);
+    hipLaunchKernelGGL(k_dense_scale, rgrid, dim3(256), 0, s, md, count, kp, kc, kv, scale);
+    hipLaunchKernelGGL(k_dense_gather, rgrid, dim3(256), 0, s, md, count, kp, kc, kv, scale, W, diag0);
+    hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, count, W, diag0, pv, bad_flag);
     int active = count;
-    for (int p = 0; p < ldmax / kNb; ++p) {
-        while (active > 0 && m[active - 1].ld / kNb <= p) --active;
-        const double *src = (p & 1) ? c->dinv : X0;
-        double *dst = (p & 1) ? X0 : c->dinv;
-        hipLaunchKernelGGL(k_gjb_sweep, dim3((unsigned)tiles[active]), dim3(256), 0, s, p, md, active, src, dst, pv,
-                           diag0, bad_flag);
+    for (int p = 0; p < m[0].nt; ++p) {
+        while (active > 0 && m[active - 1].nt <= p) --active;
+        hipLaunchKernelGGL(k_gjb_panel, dim3((unsigned)rows[active]), dim3(256), 0, s, p, md, active, W, pv, cbuf, tbuf);
+        hipLaunchKernelGGL(k_gjb_sweep, dim3((unsigned)(tiles[active] + active)), dim3(256), 0, s, p, md, active, W, pv,
+                           cbuf, tbuf, diag0, bad_flag);
     }
-    hipLaunchKernelGGL(k_gjb_copy_even, dim3(64, gy), dim3(256), 0, s, md, count, X0, c->dinv);
+    hipLaunchKernelGGL(k_gjb_finish, dim3((unsigned)tiles[count]), dim3(256), 0, s, md, count, W, scale, c->dinv);
     HT(hipGetLastError());
     return DPCG_OK;
 }
 
-// The dense-block tables from the host copy of the partition: extents, offsets in dinv,
-// and the apply's workgroups (kDenseRows rows of one block each).
+// The dense-block tables from the host copy of the partition: extents, offsets in dinv, and
+// the apply's strips and tile rows.
 int dense_tables(dpcg_ctx *c, const int32_t *bph, int32_t nblocks) {
     hipStream_t s = c->stream;
     c->dense_h.clear();
-    int64_t off = 0;
+    int64_t tiles = 0;
     for (int32_t b = 0; b < nblocks; ++b) {
         const int32_t m = bph[b + 1] - bph[b];
         if (m <= kMaxBlock) continue;
-        const int32_t ld = (m + kNb - 1) / kNb * kNb;
-        c->dense_h.push_back(DenseBlk{off, bph[b], m, ld, (int32_t)b});
-        c->dense_maxld = std::max(c->dense_maxld, ld);
-        off += (int64_t)ld * ld;
+        c->dense_h.push_back(DenseBlk{tiles * kDenseTile * kDenseTile, tiles, bph[b], m, (int32_t)b, 0});
+        tiles += coarse_tile_count((m + kDenseTile - 1) / kDenseTile);
     }
-    std::vector<DenseChunk> ch;
-    for (size_t i = 0; i < c->dense_h.size(); ++i)
-        for (int32_t r = 0; r < c->dense_h[i].size; r += kDenseRows) ch.push_back(DenseChunk{(int32_t)i, r});
+    std::vector<DenseStrip> st;
+    std::vector<DenseRow> rows;
+    for (size_t i = 0; i < c->dense_h.size(); ++i) {
+        const int32_t nt = (c->dense_h[i].size + kDenseTile - 1) / kDenseTile;
+        for (int32_t I = 0; I < nt; ++I) {
+            rows.push_back(DenseRow{(int32_t)i, I, (int32_t)st.size(), 0});
+            for (int32_t j = 0; j <= I; j += kDenseStrip) st.push_back(DenseStrip{(int32_t)i, I, j, 0});
+            rows.back().strip1 = (int32_t)st.size();
+        }
+    }
     c->ndense = (int32_t)c->dense_h.size();
-    c->ndchunks = (int32_t)ch.size();
-    c->dinv_len = off;
+    c->ndstrips = (int32_t)st.size();
+    c->ndrows = (int32_t)rows.size();
+    c->dense_tiles = tiles;
+    c->dinv_len = tiles * kDenseTile * kDenseTile;
     HT(keep(c, &c->dense, c->ndense));
-    HT(keep(c, &c->dchunk, c->ndchunks));
-    HT(keep(c, &c->dinv, off));
+    HT(keep(c, &c->dstrip, c->ndstrips));
+    HT(keep(c, &c->drow, c->ndrows));
+    HT(keep(c, &c->dinv, c->dinv_len));
+    HT(keep(c, &c->dpart, (tiles + c->ndstrips) * kDenseTile));
     HT(hipMemcpyAsync(c->dense, c->dense_h.data(), sizeof(DenseBlk) * c->ndense, hipMemcpyHostToDevice, s));
-    HT(hipMemcpyAsync(c->dchunk, ch.data(), sizeof(DenseChunk) * c->ndchunks, hipMemcpyHostToDevice, s));
-    HT(hipStreamSynchronize(s));  // ch is a host temporary
+    HT(hipMemcpyAsync(c->dstrip, st.data(), sizeof(DenseStrip) * c->ndstrips, hipMemcpyHostToDevice, s));
+    HT(hipMemcpyAsync(c->drow, rows.data(), sizeof(DenseRow) * c->ndrows, hipMemcpyHostToDevice, s));
+    HT(hipStreamSynchronize(s));  // st and rows are host temporaries
     return DPCG_OK;
 }
 

@@ -76,3 +76,27 @@ def test_step_length_partials(nb):
         u, info = s.solve(torch.as_tensor(K @ x, device=DEV), tol=1e-13)
     assert info["status"] == 0
     assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
+
+
+@pytest.mark.parametrize("sizes", [[19, 31, 32, 33, 5], [63, 64, 65, 12], [96, 97, 128, 129], [255, 256, 257, 3, 18],
+                                   [513, 24, 1000]])
+def test_dense_block_tiles(sizes):
+    """Subdomain-sized blocks at the edges of the inverse's tiles (32), of the sweeps' (64) and
+    of the apply's strips (8 tiles), beside nodal blocks, each against LAPACK."""
+    n = -(-sum(sizes) // 3) * 3
+    K = chain(n // 3, seed=7)
+    bp = np.cumsum([0] + sizes + ([n - sum(sizes)] if n > sum(sizes) else []))
+    r = np.random.default_rng(8).standard_normal(n)
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    with D.Solver(n, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), 0, None, None,
+                  None, t(bp, torch.int32)) as s:
+        y = s.bj_apply(t(r, torch.float64)).cpu().numpy()
+        y32 = s.bj_apply_fp32(t(r, torch.float64)).cpu().numpy()
+        u, info = s.solve(t(K @ r, torch.float64), tol=1e-13)
+    assert info["status"] == 0 and np.linalg.norm(u.cpu().numpy() - r) <= 1e-11 * np.linalg.norm(r)
+    for a, b in zip(bp[:-1], bp[1:]):
+        Minv = np.linalg.inv(K[a:b, a:b].toarray())
+        ref = Minv @ r[a:b]
+        assert np.linalg.norm(y[a:b] - ref) <= (b - a) * 4e-15 * np.linalg.norm(ref)
+        bound = 2.0 ** -24 * np.abs(Minv) @ np.abs(r[a:b])
+        assert np.all(np.abs(y32[a:b] - ref) <= 1.01 * bound + (b - a) * 4e-15 * np.abs(ref).max())
