@@ -100,3 +100,25 @@ def test_dense_block_tiles(sizes):
         assert np.linalg.norm(y[a:b] - ref) <= (b - a) * 4e-15 * np.linalg.norm(ref)
         bound = 2.0 ** -24 * np.abs(Minv) @ np.abs(r[a:b])
         assert np.all(np.abs(y32[a:b] - ref) <= 1.01 * bound + (b - a) * 4e-15 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("nrhs", [1, 7, 8, 9, 16, 17, 32])
+def test_batch_widths(problems, nrhs):
+    """The batch layout's widths (8, 16, 32 columns): K X of an enriched mesh entry by entry
+    (pairs, twin rows and long rows; two sums of at most m products differ by 2 m eps
+    (|K| |x|)), and a solve with known columns, unequal in length to finish apart."""
+    p = problems("edge10")
+    K = p.K_scipy().tocsr()
+    X = np.random.default_rng(nrhs).standard_normal((p.n, nrhs))
+    with D.Solver.from_problem(p, DEV) as s:
+        Y = s.spmv_batch(torch.as_tensor(X, device=DEV)).cpu().numpy()
+    m = int(np.diff(K.indptr).max())
+    assert np.all(np.abs(Y - K @ X) <= 2 * m * np.finfo(float).eps * (abs(K) @ np.abs(X)))
+    nb = 1001
+    C = chain(nb, seed=2)
+    X = np.random.default_rng(nrhs).standard_normal((3 * nb, nrhs)) * 10.0 ** np.arange(nrhs)[None, :]
+    X[: 3 * (nb // 2), -1] = 0.0
+    with solver(C, np.arange(0, 3 * nb, 50)) as s:
+        U, infos = s.solve_batch(torch.as_tensor(C @ X, device=DEV), tol=1e-13)
+    err = np.linalg.norm(U.cpu().numpy() - X, axis=0)
+    assert all(i["status"] == 0 for i in infos) and np.all(err <= 1e-11 * np.linalg.norm(X, axis=0))
