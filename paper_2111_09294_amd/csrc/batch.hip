@@ -34,18 +34,16 @@ __device__ __forceinline__ int32_t wg_any(const BatchState *st) {
 }
 
 // sum of x[i stride] over i in [i0, n) with step di, added in index order, eight loads
-// issued before their additions
+// (clamped to the list) issued before their additions
 __device__ __forceinline__ double seq_sum(const double *__restrict__ x, int64_t stride, int i0, int n, int di) {
     double s = 0.0;
-    int i = i0;
-    for (; i + 7 * di < n; i += 8 * di) {
+    for (int i = i0; i < n; i += 8 * di) {
         double v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = x[(int64_t)(i + u * di) * stride];
+        for (int u = 0; u < 8; ++u) v[u] = x[(int64_t)min(i + u * di, n - 1) * stride];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
+        for (int u = 0; u < 8; ++u) s += i + u * di < n ? v[u] : 0.0;
     }
-    for (; i < n; i += di) s += x[(int64_t)i * stride];
     return s;
 }
 
@@ -330,11 +328,14 @@ __global__ __launch_bounds__(64 * kSpmmWaves) __attribute__((amdgpu_waves_per_eu
                                                const int32_t *__restrict__ pair_col,
                                                const uint16_t *__restrict__ pair_ab, const double *__restrict__ x,
                                                const double *__restrict__ f, double *__restrict__ y,
-                                               double *__restrict__ part, const BatchState *st) {
+                                               double *__restrict__ part, const BatchState *st,
+                                               uint64_t *progress) {
     __shared__ double lds[kSpmmWaves][W];
     __shared__ double sv[kSpmmWaves][2][9][kSpmmChunk];
     __shared__ int32_t sc[kSpmmWaves][kPairCap];
     __shared__ uint16_t sab[kSpmmWaves][kPairCap];
+    if (progress && blockIdx.x == 0 && threadIdx.x == 0)
+        post_progress(progress, st->any ? kRunning : kConverged, st->iter + 1);
     if (st && !st->any) return;
     constexpr int Q = W / 4, NB = 64 / Q;  // lanes of a row's columns, block groups
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, bg = lane / Q, cq = lane % Q;
@@ -509,7 +510,9 @@ __device__ __forceinline__ double col_sum_cm(const double *__restrict__ part, in
 // workgroup j reduces column j of the SpMM partials.
 __global__ __launch_bounds__(1024) void k_balpha(const double *__restrict__ part, int nparts, BatchState *st) {
     __shared__ double lds[16];
-    if (!st->any) return;
+    const int32_t any = st->any;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->pend = any;
+    if (!any) return;
     const int j = blockIdx.x;
     double pq;
     {  // fixed-order sum of column j over 1024 threads
@@ -535,9 +538,9 @@ __global__ __launch_bounds__(1024) void k_balpha(const double *__restrict__ part
     }
 }
 
-// update = 1: u_j += alpha_j p_j and r_j -= alpha_j q_j for the running columns, with
-// partials of ||r_j||^2; then (both modes) y = M^{-1} r over the tile's whole blocks
-// from an LDS copy of r.  One workgroup per contiguous range of tiles.  A tile's block
+// update = 1: r_j -= alpha_j q_j for the running columns, with partials of ||r_j||^2 and of
+// r_j^T y_j (u_j += alpha_j p_j waits for k_bprolong_p, which reads p anyway); then (both
+// modes) y = M^{-1} r over the tile's whole blocks from an LDS copy of r.  One workgroup per contiguous range of tiles.  A tile's block
 // inverses are one contiguous range of minv (whole blocks), staged in LDS with coalesced
 // loads when it fits in kBjStage entries (3 x 3 blocks: 3 per DoF), so the product reads
 // broadcast LDS words instead of broadcast global loads; each DoF's row offset, block size
@@ -546,12 +549,11 @@ constexpr int kBjStage = 480;
 
 template <int W>
 __global__ __launch_bounds__(256) void k_bupdate_bj(int32_t ntiles, int32_t nwg, const int32_t *__restrict__ tile_start,
-                                                    double *__restrict__ u, double *__restrict__ r,
-                                                    double *__restrict__ y, const double *__restrict__ q,
-                                                    const double *__restrict__ p, const double *__restrict__ minv,
+                                                    double *__restrict__ r, double *__restrict__ y,
+                                                    const double *__restrict__ q, const double *__restrict__ minv,
                                                     const int32_t *__restrict__ bj_rowoff,
-                                                    const int32_t *__restrict__ bj_meta, double *__restrict__ part,
-                                                    const BatchState *st, int update) {
+                                                    const int32_t *__restrict__ bj_meta, double *__restrict__ part_rr,
+                                                    double *__restrict__ part_ry, const BatchState *st, int update) {
     __shared__ double tile[kBatchTileDofs][W];
     __shared__ double mv[kBjStage];  // also the 256 doubles of the final group sum
     __shared__ int32_t md[kBatchTileDofs];
@@ -563,7 +565,7 @@ __global__ __launch_bounds__(256) void k_bupdate_bj(int32_t ntiles, int32_t nwg,
     const double alpha = run ? st->alpha[j] : 0.0;
     const int w = xcd_remap(blockIdx.x, nwg);
     const int t0 = (int)(((int64_t)w * ntiles) / nwg), t1 = (int)(((int64_t)(w + 1) * ntiles) / nwg);
-    double acc = 0.0;
+    double acc = 0.0, accy = 0.0;
     for (int t = t0; t < t1; ++t) {
         const int64_t d0 = tile_start[t], d1 = tile_start[t + 1];
         if (d1 <= d0) continue;  // uniform: the last tile can be empty
@@ -578,18 +580,14 @@ __global__ __launch_bounds__(256) void k_bupdate_bj(int32_t ntiles, int32_t nwg,
         }
         // a group's DoFs of the tile at a time (a whole tile): all loads first, then the updates
         for (int64_t db = d0 + g; db < d1; db += kBatchTileDofs) {
-            double rv[R], pv[R], qv[R], uv[R];
+            double rv[R], qv[R];
 #pragma unroll
             for (int h = 0; h < R; ++h) {
                 const int64_t d = db + NG * h, o = d * W + j;
-                rv[h] = pv[h] = qv[h] = uv[h] = 0.0;
+                rv[h] = qv[h] = 0.0;
                 if (d < d1) {
                     rv[h] = r[o];
-                    if (run) {
-                        pv[h] = p[o];
-                        qv[h] = q[o];
-                        uv[h] = u[o];
-                    }
+                    if (run) qv[h] = q[o];
                 }
             }
 #pragma unroll
@@ -598,7 +596,6 @@ __global__ __launch_bounds__(256) void k_bupdate_bj(int32_t ntiles, int32_t nwg,
                 if (d >= d1) continue;
                 double rn = rv[h];
                 if (run) {
-                    u[o] = fma(alpha, pv[h], uv[h]);
                     rn = fma(-alpha, qv[h], rn);
                     r[o] = rn;
                 }
@@ -620,25 +617,38 @@ __global__ __launch_bounds__(256) void k_bupdate_bj(int32_t ntiles, int32_t nwg,
                 else
                     for (int kk = 0; kk < size; ++kk) s = fma(minv[m0 + ro + kk], tile[base + kk][j], s);
                 y[d * W + j] = s;
+                accy = fma(tile[d - d0][j], s, accy);
             }
         }
     }
     __syncthreads();  // the last tile's reads of mv precede its reuse
-    const double tot = group_sum<W, 256>(acc, mv);
-    if (update && threadIdx.x < W) part[(int64_t)blockIdx.x * W + threadIdx.x] = tot;
+    if (!update) return;
+    const double rr = group_sum<W, 256>(acc, mv);
+    __syncthreads();
+    const double ry = group_sum<W, 256>(accy, mv);
+    if (threadIdx.x < W) {
+        part_rr[(int64_t)blockIdx.x * W + threadIdx.x] = rr;
+        part_ry[(int64_t)blockIdx.x * W + threadIdx.x] = ry;
+    }
 }
 
 // Column checks by workgroup 0 of a restriction launch (NT threads): ||r_j|| from the
 // row-major partials against thr_j and the iteration cap, then any = some column still
-// running.
+// running.  In an iteration (iter_offset 1) also r_j^T y_j and the step to the next iteration.
 template <int W, int NT>
-__device__ void column_check(BatchState *st, const double *__restrict__ part_rr, int n_rr, int iter_offset,
-                             int max_iter, double *lds) {
+__device__ void column_check(BatchState *st, const double *__restrict__ part_rr, const double *__restrict__ part_ry,
+                             int n_rr, int iter_offset, int max_iter, double *lds) {
     const int j = threadIdx.x % W;
     const double rr = col_reduce<W, NT>(part_rr, n_rr, lds);
+    if (iter_offset) {
+        __syncthreads();
+        const double ry = col_reduce<W, NT>(part_ry, n_rr, lds);
+        if (threadIdx.x < W) st->ry[j] = ry;
+    }
     __shared__ int32_t run_s[W];
     if (threadIdx.x < W) {
         int32_t fl = st->flag[j];
+        st->ran[j] = fl == kRunning;
         if (fl == kRunning) {
             const int done = st->iter + iter_offset;
             st->rr[j] = rr;
@@ -662,11 +672,12 @@ __device__ void column_check(BatchState *st, const double *__restrict__ part_rr,
         int32_t any = 0;
         for (int h = 0; h < W; ++h) any |= run_s[h];
         st->any = any;
+        st->iter += iter_offset;
     }
-    __syncthreads();
 }
 
-// Workgroup 0 runs the column checks when n_rr > 0.  Then the merged right-hand side
+// Workgroup 0 runs the column checks when n_rr > 0 (alone: they are as long a chain as a
+// segment), the others the merged right-hand side
 // of Algorithm 3 in segments: segment s of deflation vector c
 // sums Z^T[c, e] a[e][j] over its entries (list 0) or -(KZ)^T[c, e] b[e][j] (list 1; 0
 // when b is null) into seg_part[s][j].  Group g of W lanes takes the chunks of W
@@ -680,15 +691,20 @@ __global__ __launch_bounds__(1024) void k_brestrict(const int32_t *__restrict__ 
                                                    const int32_t *__restrict__ kzt_idx,
                                                    const double *__restrict__ kzt_val, const double *__restrict__ a,
                                                    const double *__restrict__ b, double *__restrict__ seg_part,
-                                                   BatchState *st, const double *__restrict__ part_rr, int n_rr,
-                                                   int iter_offset, int max_iter) {
+                                                   BatchState *st, const double *__restrict__ part_rr,
+                                                   const double *__restrict__ part_ry, int n_rr, int iter_offset,
+                                                   int max_iter) {
     __shared__ double lds[1024];
     const int j = threadIdx.x % W, g = threadIdx.x / W;
+    const int check = n_rr > 0 ? 1 : 0;
     if (st) {
         if (wg_any(st) == 0) return;
-        if (blockIdx.x == 0 && n_rr > 0) column_check<W, 1024>(st, part_rr, n_rr, iter_offset, max_iter, lds);
+        if (check && blockIdx.x == 0) {
+            column_check<W, 1024>(st, part_rr, part_ry, n_rr, iter_offset, max_iter, lds);
+            return;
+        }
     }
-    const int sg = xcd_remap(blockIdx.x, gridDim.x);
+    const int sg = xcd_remap(blockIdx.x - check, gridDim.x - check);
     if (sg >= nseg) return;
     const int list = seg[4 * sg + 1], e0 = seg[4 * sg + 2], e1 = seg[4 * sg + 3];
     const int32_t *idx = list ? kzt_idx : zt_idx;
@@ -722,23 +738,56 @@ __global__ __launch_bounds__(1024) void k_brestrict(const int32_t *__restrict__ 
             }
         }
     }
-    __syncthreads();  // lds may still be read by the check above
     const double t = group_sum<W, 1024>(s, lds);
     if (threadIdx.x < W) seg_part[(int64_t)sg * W + threadIdx.x] = list ? -t : t;
 }
 
-// g[c][j] = sum of column c's segment partials, in segment order (256 / W columns per
-// workgroup).
+// Sums of a deflation vector's partials by eight lane groups: those of Z^T (positions [s0, sm)
+// of part, stride apart) into h when given, and all [s0, s1) into g; eight positions per group
+// in flight.  32 / W vectors per 256-thread workgroup.
+template <int W>
+__device__ __forceinline__ void vector_sums(int32_t c, int32_t k, int s0, int sm, int s1, int64_t stride,
+                                            const double *__restrict__ part, double *__restrict__ gout,
+                                            double *__restrict__ h) {
+    __shared__ double lz[256], lk[256];
+    const int j = threadIdx.x % W, g = threadIdx.x / W % 8, v = threadIdx.x / (8 * W);
+    double tz = 0.0, tk = 0.0;
+    for (int sg = s0 + g; sg < s1; sg += 64) {
+        double x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = part[(int64_t)min(sg + 8 * q, s1 - 1) * stride + j];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int p = sg + 8 * q;
+            tz += p < sm ? x[q] : 0.0;
+            tk += p >= sm && p < s1 ? x[q] : 0.0;
+        }
+    }
+    lz[threadIdx.x] = tz;
+    lk[threadIdx.x] = tk;
+    __syncthreads();
+    if (g == 0 && c < k) {
+        double a = 0.0, b = 0.0;
+        for (int i = 0; i < 8; ++i) {
+            a += lz[(v * 8 + i) * W + j];
+            b += lk[(v * 8 + i) * W + j];
+        }
+        if (h) h[(int64_t)c * W + j] = a;
+        gout[(int64_t)c * W + j] = a + b;
+    }
+}
+
+// per-entry restriction: column c's segments are seg_ptr[c] .. seg_ptr[c + 1] - 1, those of
+// Z^T first (seg[4 s + 1] = 0)
 template <int W>
 __global__ __launch_bounds__(256) void k_bsegsum(int32_t k, const int32_t *__restrict__ seg_ptr,
+                                                 const int32_t *__restrict__ seg_mid,
                                                  const double *__restrict__ seg_part, double *__restrict__ gout,
-                                                 const BatchState *st) {
+                                                 double *__restrict__ h, const BatchState *st) {
     if (st && !st->any) return;
-    const int c = blockIdx.x * (256 / W) + threadIdx.x / W, j = threadIdx.x % W;
-    if (c >= k) return;
-    double t = 0.0;
-    for (int sg = seg_ptr[c]; sg < seg_ptr[c + 1]; ++sg) t += seg_part[(int64_t)sg * W + j];
-    gout[(int64_t)c * W + j] = t;
+    const int c = blockIdx.x * (32 / W) + threadIdx.x / (8 * W);
+    const bool in = c < k;
+    vector_sums<W>(c, k, in ? seg_ptr[c] : 0, in ? seg_mid[c] : 0, in ? seg_ptr[c + 1] : 0, W, seg_part, gout, h);
 }
 
 // ---- grouped restriction on the matrix cores ----
@@ -754,6 +803,7 @@ __global__ __launch_bounds__(256) void k_bsegsum(int32_t k, const int32_t *__res
 typedef double bdbl4 __attribute__((ext_vector_type(4)));
 constexpr int kGroupCols = 16;    // vectors of a group (one MFMA row tile)
 constexpr int kGroupRows = 128;   // rows of a group's list per segment (one wave)
+constexpr int kGroupRowsFew = 32;  // the same when that gives too few waves
 constexpr int kGroupUnroll = 8;   // 4-row MFMA steps whose loads are issued together
 constexpr int kGroupSeg = 7;      // ints per segment record
 
@@ -784,24 +834,32 @@ __global__ __launch_bounds__(256) void k_same_rows(int32_t k, const int32_t *__r
 // 16-column halves).  The row indices and values of kGroupUnroll steps are loaded
 // before their row gathers.  Rows m < kg of the result go to seg_part[s][m][.],
 // negated for list 1 (0 when b is null).  Workgroup 0 runs the column checks.
-constexpr int kGroupWaves = 16;  // segments (waves) per workgroup of the grouped restriction
+// Segments (waves) per workgroup of the grouped restriction: 16, whose consecutive segments
+// share a CU's cache, when that still gives every CU one (62 us at 40^3 x 32 against 117 with
+// 4), else 4, so that no CU stands idle.
+constexpr int kGroupWaves = 16, kGroupWavesFew = 4;
 
-template <int W>
-__global__ __launch_bounds__(64 * kGroupWaves) void k_brestrict_mfma(const int32_t *__restrict__ gseg, int32_t ngseg,
+template <int W, int WV>
+__global__ __launch_bounds__(64 * WV) void k_brestrict_mfma(const int32_t *__restrict__ gseg, int32_t ngseg,
                                                         const int32_t *__restrict__ zr,
                                                         const double *__restrict__ zv,
                                                         const int32_t *__restrict__ kzt_idx,
                                                         const double *__restrict__ kzt_val,
                                                         const double *__restrict__ a, const double *__restrict__ b,
                                                         double *__restrict__ seg_part, BatchState *st,
-                                                        const double *__restrict__ part_rr, int n_rr, int iter_offset,
+                                                        const double *__restrict__ part_rr,
+                                                        const double *__restrict__ part_ry, int n_rr, int iter_offset,
                                                         int max_iter) {
-    __shared__ double lds[64 * kGroupWaves];
+    __shared__ double lds[64 * WV];
+    const int check = n_rr > 0 ? 1 : 0;
     if (st) {
         if (wg_any(st) == 0) return;
-        if (blockIdx.x == 0 && n_rr > 0) column_check<W, 64 * kGroupWaves>(st, part_rr, n_rr, iter_offset, max_iter, lds);
+        if (check && blockIdx.x == 0) {
+            column_check<W, 64 * WV>(st, part_rr, part_ry, n_rr, iter_offset, max_iter, lds);
+            return;
+        }
     }
-    const int sg = xcd_remap(blockIdx.x, gridDim.x) * kGroupWaves + (threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int sg = xcd_remap(blockIdx.x - check, gridDim.x - check) * WV + (threadIdx.x >> 6), l = threadIdx.x & 63;
     if (sg >= ngseg) return;
     const int32_t *G = gseg + kGroupSeg * sg;
     const int kg = G[1], list = G[2], ibeg = G[3], vbeg = G[4], nrows = G[5], L = G[6];
@@ -848,39 +906,32 @@ __global__ __launch_bounds__(64 * kGroupWaves) void k_brestrict_mfma(const int32
     }
 }
 
-// g[c][j] = sum over the segments gcol[3c] .. gcol[3c+1]-1 of c's group of their partial
-// row gcol[3c+2], in segment order (256 / W vectors per workgroup).
+// grouped restriction: vector c adds partial row gcol[4c+3] of its group's segments
+// gcol[4c] .. gcol[4c+2]-1, those of Z^T before gcol[4c+1]
 template <int W>
 __global__ __launch_bounds__(256) void k_bgroupsum(int32_t k, const int32_t *__restrict__ gcol,
                                                    const double *__restrict__ seg_part, double *__restrict__ gout,
-                                                   const BatchState *st) {
+                                                   double *__restrict__ h, const BatchState *st) {
     if (st && !st->any) return;
-    const int c = blockIdx.x * (256 / W) + threadIdx.x / W, j = threadIdx.x % W;
-    if (c >= k) return;
-    const int s0 = gcol[3 * c], s1 = gcol[3 * c + 1], mo = gcol[3 * c + 2];
-    double t = 0.0;
-    for (int sg = s0; sg < s1; sg += 8) {  // eight loads in flight, added in segment order
-        double x[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = sg + q < s1 ? seg_part[((int64_t)(sg + q) * kGroupCols + mo) * W + j] : 0.0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (sg + q < s1) t += x[q];
-    }
-    gout[(int64_t)c * W + j] = t;
+    const int c = blockIdx.x * (32 / W) + threadIdx.x / (8 * W);
+    const int4 gc = c < k ? reinterpret_cast<const int4 *>(gcol)[c] : make_int4(0, 0, 0, 0);
+    vector_sums<W>(c, k, gc.x, gc.y, gc.z, (int64_t)kGroupCols * W, seg_part + gc.w * W, gout, h);
 }
 
 // delta = E^{-1} g for all W columns on the matrix cores: workgroup = 16 rows of
 // E^{-1}; wave w of 8 takes the w-th eighth of the contraction index c in steps of 4
 // (v_mfma_f64_16x16x4f64: a = E^{-1}[row l % 16][c + l / 16], b = g[c + l / 16][col],
 // one or two 16-column halves), then the eight partial tiles are added in wave order in LDS.
-// Result item v of lane l is row l / 16 + 4 v, column l % 16 of a half.
+// Result item v of lane l is row l / 16 + 4 v, column l % 16 of a half.  With h = Z^T R given,
+// hd[workgroup] = the sums of h_j delta_j over its rows.
 constexpr int kCoarseWaves = 8;
 template <int W>
 __global__ __launch_bounds__(64 * kCoarseWaves) void k_bcoarse(int32_t k, int64_t ld,
                                                                const double *__restrict__ einv,
                                                                const double *__restrict__ gin,
-                                                               double *__restrict__ delta, const BatchState *st) {
+                                                               double *__restrict__ delta,
+                                                               const double *__restrict__ h, double *__restrict__ hd,
+                                                               const BatchState *st) {
     __shared__ double part[kCoarseWaves][16][W + 1];
     if (st && !st->any) return;
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -919,6 +970,15 @@ __global__ __launch_bounds__(64 * kCoarseWaves) void k_bcoarse(int32_t k, int64_
 #pragma unroll
         for (int w = 0; w < kCoarseWaves; ++w) sum += part[w][rr][j];
         if (r0 + rr < k) delta[(int64_t)(r0 + rr) * W + j] = sum;
+        if (h) part[0][rr][j] = r0 + rr < k ? h[(int64_t)(r0 + rr) * W + j] * sum : 0.0;
+    }
+    if (h) {
+        __syncthreads();
+        if (threadIdx.x < W) {
+            double t = 0.0;
+            for (int rr = 0; rr < 16; ++rr) t += part[0][rr][threadIdx.x];
+            hd[(int64_t)blockIdx.x * W + threadIdx.x] = t;
+        }
     }
 }
 
@@ -953,14 +1013,57 @@ __device__ __forceinline__ double zrow_dot_long(int e0, int cnt, int j, const in
     return c;
 }
 
-// out = base + Z delta (base may be null); optional partials of rdot_j^T out_j;
-// optionally advance the iteration.
+// (Z delta)[d][j] and (Z delta)[db][j] for two rows of a lane group (db only with hb), their
+// loads issued together; each row's entries are added in index order from zero
+template <int W>
+__device__ __forceinline__ void zrows_dot(int64_t d, int64_t db, bool hb, int j, const int32_t *__restrict__ z_ptr,
+                                          const int32_t *__restrict__ z_col, const double *__restrict__ z_val,
+                                          const double *__restrict__ delta, double &ca, double &cb) {
+    const int ea = z_ptr[d], na = z_ptr[d + 1] - ea;
+    const int eb = hb ? z_ptr[db] : 0, nb = hb ? z_ptr[db + 1] - eb : 0;
+    if (na <= W && nb <= W) {
+        // lane j loads entry j of each row; the entries are passed round by shuffles,
+        // four per row and step, and their delta rows gathered together
+        int cola = 0, colb = 0;
+        double va = 0.0, vb = 0.0;
+        if (j < na) {
+            cola = z_col[ea + j];
+            va = z_val[ea + j];
+        }
+        if (j < nb) {
+            colb = z_col[eb + j];
+            vb = z_val[eb + j];
+        }
+        const int m = max(na, nb);  // the same for the whole group
+        for (int q0 = 0; q0 < m; q0 += 4) {
+            double xa[4], xb[4], wa[4], wb[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int ka = __shfl(cola, q0 + q, W), kb = __shfl(colb, q0 + q, W);
+                wa[q] = __shfl(va, q0 + q, W);
+                wb[q] = __shfl(vb, q0 + q, W);
+                xa[q] = q0 + q < na ? delta[(int64_t)ka * W + j] : 0.0;
+                xb[q] = q0 + q < nb ? delta[(int64_t)kb * W + j] : 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q0 + q < na) ca = fma(wa[q], xa[q], ca);
+                if (q0 + q < nb) cb = fma(wb[q], xb[q], cb);
+            }
+        }
+    } else {
+        ca = zrow_dot_long<W>(ea, na, j, z_col, z_val, delta);
+        if (hb) cb = zrow_dot_long<W>(eb, nb, j, z_col, z_val, delta);
+    }
+}
+
+// out = base + Z delta (base may be null); optional partials of rdot_j^T out_j.
 template <int W>
 __global__ __launch_bounds__(256) void k_bprolong(int64_t n, int32_t nwg, const int32_t *__restrict__ z_ptr,
                                                   const int32_t *__restrict__ z_col, const double *__restrict__ z_val,
                                                   const double *__restrict__ delta, const double *base, double *out,
                                                   const double *__restrict__ rdot, double *__restrict__ part,
-                                                  BatchState *st, int advance) {
+                                                  const BatchState *st) {
     __shared__ double lds[256];
     constexpr int NG = 256 / W;
     if (st && !st->any) return;
@@ -978,42 +1081,7 @@ __global__ __launch_bounds__(256) void k_bprolong(int64_t n, int32_t nwg, const 
         double sa = base ? base[oa] : 0.0, sb = base && hb ? base[ob] : 0.0;
         double ca = 0.0, cb = 0.0;
         if (delta) {
-            const int ea = z_ptr[d], na = z_ptr[d + 1] - ea;
-            const int eb = hb ? z_ptr[db] : 0, nb = hb ? z_ptr[db + 1] - eb : 0;
-            if (na <= W && nb <= W) {
-                // lane j loads entry j of each row; the entries are passed round by shuffles,
-                // four per row and step, and their delta rows gathered together
-                int cola = 0, colb = 0;
-                double va = 0.0, vb = 0.0;
-                if (j < na) {
-                    cola = z_col[ea + j];
-                    va = z_val[ea + j];
-                }
-                if (j < nb) {
-                    colb = z_col[eb + j];
-                    vb = z_val[eb + j];
-                }
-                const int m = max(na, nb);  // the same for the whole group
-                for (int q0 = 0; q0 < m; q0 += 4) {
-                    double xa[4], xb[4], wa[4], wb[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int ka = __shfl(cola, q0 + q, W), kb = __shfl(colb, q0 + q, W);
-                        wa[q] = __shfl(va, q0 + q, W);
-                        wb[q] = __shfl(vb, q0 + q, W);
-                        xa[q] = q0 + q < na ? delta[(int64_t)ka * W + j] : 0.0;
-                        xb[q] = q0 + q < nb ? delta[(int64_t)kb * W + j] : 0.0;
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (q0 + q < na) ca = fma(wa[q], xa[q], ca);
-                        if (q0 + q < nb) cb = fma(wb[q], xb[q], cb);
-                    }
-                }
-            } else {
-                ca = zrow_dot_long<W>(ea, na, j, z_col, z_val, delta);
-                if (hb) cb = zrow_dot_long<W>(eb, nb, j, z_col, z_val, delta);
-            }
+            zrows_dot<W>(d, db, hb, j, z_ptr, z_col, z_val, delta, ca, cb);
         }
         sa += ca;
         out[oa] = sa;
@@ -1028,43 +1096,91 @@ __global__ __launch_bounds__(256) void k_bprolong(int64_t n, int32_t nwg, const 
         const double t = group_sum<W, 256>(acc, lds);
         if (threadIdx.x < W) part[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = t;  // column-major
     }
-    if (advance && blockIdx.x == 0 && threadIdx.x == 0) st->iter = st->iter + 1;
 }
 
-// rho_j = r_j^T z_j, beta_{i-1,j} = rho_{i,j} / rho_{i-1,j} for the running columns,
-// rho kept in two parity slots; workgroup j reduces column j of the prolongation
-// partials.
-__global__ __launch_bounds__(256) void k_bbeta(const double *__restrict__ part, int nparts, BatchState *st) {
-    __shared__ double lds[4];
-    if (!st->any) return;
-    const int j = blockIdx.x;
-    const double rho = col_sum_cm(part, nparts, j, lds);
-    if (threadIdx.x == 0 && st->flag[j] == kRunning) {
-        const int it = st->iter;
-        if (it > 0 && !isfinite(rho)) {
-            st->flag[j] = kBreakdown;
-            st->bad[j] = it - 1;
-            st->iters_done[j] = it;
-        } else {
-            st->beta[j] = it > 0 ? rho / st->rho[(it + 1) & 1][j] : 0.0;
-            st->rho[it & 1][j] = rho;
+// An iteration's end for every column: u_j += alpha_j p_j for the columns that ran in it, and
+// the prolongation fused with beta and the new search direction for those that go on, as in
+// the single solve: rho_j = r_j^T z_j = r_j^T y_j + (Z^T r_j)^T delta_j from the check's sum and
+// the coarse product's partials hd, so z is not stored: p_j = y_j + Z delta_j + beta_j p_j (0 for
+// the others).  Every workgroup forms the same rho and beta; workgroup 0 stores them.  It runs
+// once after the last column stops (pend), for u.  Bound by its passes over y, p and u: one read
+// each, one write of p and u, where the update, the prolongation, beta and the p update read p
+// twice more, r once more and wrote and read z.
+template <int W>
+__global__ __launch_bounds__(256) void k_bprolong_p(int64_t n, int32_t nwg, const int32_t *__restrict__ z_ptr,
+                                                    const int32_t *__restrict__ z_col,
+                                                    const double *__restrict__ z_val,
+                                                    const double *__restrict__ delta, const double *__restrict__ y,
+                                                    const double *__restrict__ hd, int32_t nhd,
+                                                    double *__restrict__ u, double *__restrict__ p, BatchState *st) {
+    __shared__ double lds[256], beta_s[W];
+    constexpr int NG = 256 / W;
+    if (!st->pend) return;
+    const int j = threadIdx.x % W, g = threadIdx.x / W;
+    const int it = st->iter;
+    const bool ran = st->ran[j] != 0;
+    const int32_t flag = st->flag[j];
+    const double alpha = ran ? st->alpha[j] : 0.0;
+    const double hs = group_sum<W, 256>(seq_sum(hd + j, W, g, nhd, NG), lds);
+    if (threadIdx.x < W) {
+        const double rho = st->ry[j] + hs, old = st->rho[(it + 1) & 1][j];
+        const bool bad = !isfinite(rho);
+        beta_s[j] = rho / old;
+        if (blockIdx.x == 0 && flag == kRunning) {
+            if (bad) {
+                st->flag[j] = kBreakdown;
+                st->bad[j] = it - 1;
+                st->iters_done[j] = it;
+            } else {
+                st->beta[j] = beta_s[j];
+                st->rho[it & 1][j] = rho;
+            }
+        }
+        lds[j] = flag == kRunning && !bad ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    const bool run = lds[j] != 0.0;
+    const double beta = beta_s[j];
+    const int w = xcd_remap(blockIdx.x, nwg);
+    const int64_t per = (n + nwg - 1) / nwg;
+    const int64_t d1 = std::min<int64_t>(n, (int64_t)(w + 1) * per);
+    for (int64_t d = (int64_t)w * per + g; d < d1; d += 2 * NG) {
+        const int64_t db = d + NG;
+        const bool hb = db < d1;
+        const int64_t oa = d * W + j, ob = (hb ? db : d) * W + j;
+        const double ya = y[oa], yb = y[ob], pa = p[oa], pb = p[ob], ua = u[oa], ub = u[ob];
+        double ca = 0.0, cb = 0.0;
+        if (delta) zrows_dot<W>(d, db, hb, j, z_ptr, z_col, z_val, delta, ca, cb);
+        if (ran) u[oa] = fma(alpha, pa, ua);
+        p[oa] = run ? fma(beta, pa, ya + ca) : 0.0;
+        if (hb) {
+            if (ran) u[ob] = fma(alpha, pb, ub);
+            p[ob] = run ? fma(beta, pb, yb + cb) : 0.0;
         }
     }
 }
 
-// p_j = z_j + beta_j p_j (p_0 = z_0) for the running columns; 0 for the others.
+// The start's rho_0,j = r_j^T z_j for the running columns; workgroup j reduces column j of the
+// prolongation partials.
+__global__ __launch_bounds__(256) void k_brho(const double *__restrict__ part, int nparts, BatchState *st) {
+    __shared__ double lds[4];
+    if (!st->any) return;
+    const int j = blockIdx.x;
+    const double rho = col_sum_cm(part, nparts, j, lds);
+    if (threadIdx.x == 0 && st->flag[j] == kRunning) st->rho[0][j] = rho;
+}
+
+// p_0,j = z_j for the running columns; 0 for the others.
 template <int W>
-__global__ __launch_bounds__(256) void k_bpupdate(int64_t n, const double *__restrict__ z, double *__restrict__ p,
-                                                  const BatchState *st) {
+__global__ __launch_bounds__(256) void k_bpstart(int64_t n, const double *__restrict__ z, double *__restrict__ p,
+                                                 const BatchState *st) {
     if (!st->any) return;
     constexpr int NG = 256 / W;
     const int j = threadIdx.x % W;
     const bool run = st->flag[j] == kRunning;
-    const bool first = st->iter == 0;
-    const double beta = st->beta[j];
     for (int64_t d = blockIdx.x * (int64_t)NG + threadIdx.x / W; d < n; d += (int64_t)gridDim.x * NG) {
         const int64_t o = d * W + j;
-        p[o] = run ? (first ? z[o] : fma(beta, p[o], z[o])) : 0.0;
+        p[o] = run ? z[o] : 0.0;
     }
 }
 
@@ -1190,6 +1306,9 @@ int ensure_ws(dpcg_ctx *c) {
     BTRY(balloc(c, &b->p, nw));
     BTRY(balloc(c, &b->g, kw));
     BTRY(balloc(c, &b->delta, kw));
+    BTRY(balloc(c, &b->h, kw));
+    BTRY(balloc(c, &b->hd, ((size_t)c->k + 15) / 16 * W + W));
+    BHIP(hipMemsetAsync(b->hd, 0, sizeof(double) * W, c->stream));  // k = 0: one partial of zero
     const int64_t nslots = (c->nb + 1) / 2;
     b->spmm_nwg = grid_rows(nslots, kSpmmWaves, 1 << 30);
     BTRY(balloc(c, &b->pair_len, (size_t)nslots));
@@ -1197,15 +1316,17 @@ int ensure_ws(dpcg_ctx *c) {
     BTRY(balloc(c, &b->pair_ab, (size_t)nslots * kPairCap));
     BLAUNCH(k_pair_merge, dim3((unsigned)((nslots + 3) / 4)), dim3(256), 0, c->stream, c->nb, c->brow_ptr, c->bcol,
             (int32_t)nslots, b->pair_len, b->pair_col, b->pair_ab);
-    b->upd_nwg = grid_rows(c->bjb_ntiles, 1, 4096);  // about one tile per workgroup at 40^3
-    b->vec_nwg = grid_rows(c->n, 32, 8192);  // prolongation 44.9 -> 42.4 us at 40^3 against 4,096
+    b->upd_nwg = grid_rows(c->bjb_ntiles, 1, 16384);  // a tile each (4,096 at 40^3: 63.5 us, 4,528: 55.6)
+    b->vec_nwg = grid_rows(c->n, 64, 8192);  // 72.8 us at 40^3; 32 or 128 rows each 75.5 and 76.7
     const size_t np = (size_t)std::max({b->spmm_nwg, b->upd_nwg, b->vec_nwg}) * W;
     BTRY(balloc(c, &b->part, np));
     BTRY(balloc(c, &b->part2, np));
+    BTRY(balloc(c, &b->part3, (size_t)b->upd_nwg * W));
     BTRY(balloc(c, &b->st, 1));
-    BHIP(hipHostMalloc((void **)&b->snap, sizeof(BatchState), hipHostMallocDefault));
+    BHIP(hipHostMalloc((void **)&b->snap, sizeof(BatchState) + sizeof(uint64_t), hipHostMallocDefault));
+    b->progress = reinterpret_cast<uint64_t *>(b->snap + 1);
     // restriction segments from the column pointers of Z^T and (KZ)^T
-    std::vector<int32_t> zp(c->k + 1, 0), kp(c->k + 1, 0), seg, sptr(c->k + 1, 0);
+    std::vector<int32_t> zp(c->k + 1, 0), kp(c->k + 1, 0), seg, sptr(2 * (size_t)c->k + 1, 0);
     if (c->k > 0) {
         BHIP(hipMemcpyAsync(zp.data(), c->zt_ptr, sizeof(int32_t) * (c->k + 1), hipMemcpyDeviceToHost, c->stream));
         BHIP(hipMemcpyAsync(kp.data(), c->kzt_ptr, sizeof(int32_t) * (c->k + 1), hipMemcpyDeviceToHost, c->stream));
@@ -1214,6 +1335,7 @@ int ensure_ws(dpcg_ctx *c) {
     for (int cc = 0; cc < c->k; ++cc) {
         sptr[cc] = (int32_t)(seg.size() / 4);
         for (int list = 0; list < 2; ++list) {
+            if (list) sptr[c->k + 1 + cc] = (int32_t)(seg.size() / 4);
             const int32_t e0 = list ? kp[cc] : zp[cc], e1 = list ? kp[cc + 1] : zp[cc + 1];
             for (int32_t e = e0; e == e0 || e < e1; e += kBatchSegEntries) {
                 seg.push_back(cc);
@@ -1226,12 +1348,16 @@ int ensure_ws(dpcg_ctx *c) {
     b->nseg = (int32_t)(seg.size() / 4);
     sptr[c->k] = b->nseg;
     BTRY(balloc(c, &b->seg, std::max<size_t>(4, seg.size())));
-    BTRY(balloc(c, &b->seg_ptr, (size_t)c->k + 1));
+    BTRY(balloc(c, &b->seg_ptr, sptr.size()));
     // groups of consecutive vectors whose Z columns cover the same triplets and whose
     // (KZ)^T rows coincide; the grouped kernel is used when they hold two vectors or more
     // on average
-    std::vector<int32_t> gseg, gcol(3 * (size_t)std::max(1, c->k), 0), zr;
+    std::vector<int32_t> gseg, gcol(4 * (size_t)std::max(1, c->k), 0), zr;
     std::vector<double> zv;
+    // segments of 128 rows fill the device from about 2,048 of them on; a small system takes 32
+    // rows (21^3 x 6: 20.4 -> 15.4 us; at 40^3 x 32 they are as fast but twice the partials)
+    const int64_t nrow = ((int64_t)zp[c->k] + kp[c->k]) / 6;  // about six vectors to a group
+    const int32_t seg_rows = nrow < (int64_t)2048 * kGroupRows ? kGroupRowsFew : kGroupRows;
     if (c->k > 0) {
         const int64_t nz = zp[c->k];
         std::vector<int32_t> zi(std::max<int64_t>(1, nz));
@@ -1279,20 +1405,22 @@ int ensure_ws(dpcg_ctx *c) {
                     zv[v_off + (size_t)m * L + 3 * ti + zi[q] % 3] = zval[q];
                 }
             }
-            for (int32_t r0 = 0; r0 < L; r0 += kGroupRows) {
-                const int32_t rec[kGroupSeg] = {j0, kg, 0, r_off + r0, v_off + r0, std::min(kGroupRows, L - r0), L};
+            for (int32_t r0 = 0; r0 < L; r0 += seg_rows) {
+                const int32_t rec[kGroupSeg] = {j0, kg, 0, r_off + r0, v_off + r0, std::min(seg_rows, L - r0), L};
                 gseg.insert(gseg.end(), rec, rec + kGroupSeg);
             }
+            const int sm = (int)(gseg.size() / kGroupSeg);
             const int32_t e0 = kp[j0], len = kp[j0 + 1] - e0;
-            for (int32_t r0 = 0; r0 < len; r0 += kGroupRows) {
-                const int32_t rec[kGroupSeg] = {j0, kg, 1, e0 + r0, e0 + r0, std::min(kGroupRows, len - r0), len};
+            for (int32_t r0 = 0; r0 < len; r0 += seg_rows) {
+                const int32_t rec[kGroupSeg] = {j0, kg, 1, e0 + r0, e0 + r0, std::min(seg_rows, len - r0), len};
                 gseg.insert(gseg.end(), rec, rec + kGroupSeg);
             }
             const int s1 = (int)(gseg.size() / kGroupSeg);
             for (int cc = j0; cc < j1; ++cc) {
-                gcol[3 * cc] = s0;
-                gcol[3 * cc + 1] = s1;
-                gcol[3 * cc + 2] = cc - j0;
+                gcol[4 * cc] = s0;
+                gcol[4 * cc + 1] = sm;
+                gcol[4 * cc + 2] = s1;
+                gcol[4 * cc + 3] = cc - j0;
             }
             ++ngroups;
             j0 = j1;
@@ -1329,43 +1457,52 @@ int read_bstate(dpcg_ctx *c, BatchState &out) {
     return DPCG_OK;
 }
 
+// h: also Z^T a on its own (an iteration's fused prolongation)
 template <int W>
-int enqueue_restrict(dpcg_ctx *c, const double *a, const double *bvec, BatchState *st, const double *part_rr, int n_rr,
-                     int iter_offset, int max_iter) {
+int enqueue_restrict(dpcg_ctx *c, const double *a, const double *bvec, BatchState *st, const double *part_rr,
+                     const double *part_ry, int n_rr, int iter_offset, int max_iter, double *h) {
     BatchWorkspace *b = c->bws;
+    const int check = n_rr > 0 ? 1 : 0;  // a workgroup for the checks, then a multiple of 8: XCD-aware mapping
+    const dim3 vgrid((c->k + 32 / W - 1) / (32 / W));
     if (b->grouped) {
-        const int grid = ((b->ngseg + kGroupWaves - 1) / kGroupWaves + 7) & ~7;  // a multiple of 8: XCD-aware mapping
-        BLAUNCH(k_brestrict_mfma<W>, dim3(grid), dim3(64 * kGroupWaves), 0, c->stream, (const int32_t *)b->gseg, b->ngseg,
-                (const int32_t *)b->zr, (const double *)b->zv, c->kzt_idx, (const double *)c->kzt_val, a, bvec,
-                b->seg_part, st, part_rr, n_rr, iter_offset, max_iter);
-        BLAUNCH(k_bgroupsum<W>, dim3((c->k + 256 / W - 1) / (256 / W)), dim3(256), 0, c->stream, c->k, (const int32_t *)b->gcol,
-                (const double *)b->seg_part, b->g, (const BatchState *)st);
+        const int wv = b->ngseg >= 256 * kGroupWaves ? kGroupWaves : kGroupWavesFew;
+        const dim3 grid((((b->ngseg + wv - 1) / wv + 7) & ~7) + check);
+        if (wv == kGroupWaves)
+            BLAUNCH((k_brestrict_mfma<W, kGroupWaves>), grid, dim3(64 * kGroupWaves), 0, c->stream,
+                    (const int32_t *)b->gseg, b->ngseg, (const int32_t *)b->zr, (const double *)b->zv, c->kzt_idx,
+                    (const double *)c->kzt_val, a, bvec, b->seg_part, st, part_rr, part_ry, n_rr, iter_offset, max_iter);
+        else
+            BLAUNCH((k_brestrict_mfma<W, kGroupWavesFew>), grid, dim3(64 * kGroupWavesFew), 0, c->stream,
+                    (const int32_t *)b->gseg, b->ngseg, (const int32_t *)b->zr, (const double *)b->zv, c->kzt_idx,
+                    (const double *)c->kzt_val, a, bvec, b->seg_part, st, part_rr, part_ry, n_rr, iter_offset, max_iter);
+        BLAUNCH(k_bgroupsum<W>, vgrid, dim3(256), 0, c->stream, c->k, (const int32_t *)b->gcol,
+                (const double *)b->seg_part, b->g, h, (const BatchState *)st);
         return DPCG_OK;
     }
-    const int grid = std::max(8, (b->nseg + 7) & ~7);
+    const int grid = std::max(8, (b->nseg + 7) & ~7) + check;
     BLAUNCH(k_brestrict<W>, dim3(grid), dim3(1024), 0, c->stream, (const int32_t *)b->seg, b->nseg, c->zt_idx,
-            (const double *)c->zt_val, c->kzt_idx, (const double *)c->kzt_val, a, bvec, b->seg_part, st, part_rr, n_rr,
-            iter_offset, max_iter);
+            (const double *)c->zt_val, c->kzt_idx, (const double *)c->kzt_val, a, bvec, b->seg_part, st, part_rr,
+            part_ry, n_rr, iter_offset, max_iter);
     if (c->k > 0)
-        BLAUNCH(k_bsegsum<W>, dim3((c->k + 256 / W - 1) / (256 / W)), dim3(256), 0, c->stream, c->k, (const int32_t *)b->seg_ptr,
-                (const double *)b->seg_part, b->g, (const BatchState *)st);
+        BLAUNCH(k_bsegsum<W>, vgrid, dim3(256), 0, c->stream, c->k, (const int32_t *)b->seg_ptr,
+                (const int32_t *)b->seg_ptr + c->k + 1, (const double *)b->seg_part, b->g, h, (const BatchState *)st);
     return DPCG_OK;
 }
 
 template <int W>
-int enqueue_coarse(dpcg_ctx *c, const BatchState *st) {
+int enqueue_coarse(dpcg_ctx *c, const BatchState *st, const double *h) {
     BatchWorkspace *b = c->bws;
     if (c->k == 0) return DPCG_OK;
     BLAUNCH(k_bcoarse<W>, dim3((c->k + 15) / 16), dim3(64 * kCoarseWaves), 0, c->stream, c->k, c->einv_ld, c->einv,
-            b->g, b->delta, st);
+            b->g, b->delta, h, b->hd, st);
     return DPCG_OK;
 }
 
 template <int W>
-int enqueue_prolong(dpcg_ctx *c, const double *base, double *out, const double *rdot, BatchState *st, int advance) {
+int enqueue_prolong(dpcg_ctx *c, const double *base, double *out, const double *rdot, const BatchState *st) {
     BatchWorkspace *b = c->bws;
     BLAUNCH(k_bprolong<W>, dim3(b->vec_nwg), dim3(256), 0, c->stream, c->n, b->vec_nwg, c->z_ptr, c->z_col, c->z_val,
-            c->k > 0 ? b->delta : nullptr, base, out, rdot, b->part, st, advance);
+            c->k > 0 ? b->delta : nullptr, base, out, rdot, b->part, st);
     return DPCG_OK;
 }
 
@@ -1375,21 +1512,21 @@ int enqueue_bstart(dpcg_ctx *c, bool guess, int max_iter) {
     BatchWorkspace *b = c->bws;
     BatchState *st = b->st;
     if (c->k > 0) {
-        BTRY(enqueue_restrict<W>(c, b->f, guess ? b->u : nullptr, nullptr, nullptr, 0, 0, 0));
-        BTRY(enqueue_coarse<W>(c, nullptr));
-        BTRY(enqueue_prolong<W>(c, guess ? b->u : nullptr, b->u, nullptr, nullptr, 0));
+        BTRY(enqueue_restrict<W>(c, b->f, guess ? b->u : nullptr, nullptr, nullptr, nullptr, 0, 0, 0, nullptr));
+        BTRY(enqueue_coarse<W>(c, nullptr, nullptr));
+        BTRY(enqueue_prolong<W>(c, guess ? b->u : nullptr, b->u, nullptr, nullptr));
     }
     BLAUNCH((k_bspmm<1, W>), dim3(b->spmm_nwg), dim3(64 * kSpmmWaves), 0, c->stream, c->nb, c->brow_ptr, c->bcol, c->bval,
             (const int32_t *)b->pair_len, (const int32_t *)b->pair_col, (const uint16_t *)b->pair_ab,
-            (const double *)b->u, (const double *)b->f, b->r, b->part2, (const BatchState *)st);
-    BLAUNCH(k_bupdate_bj<W>, dim3(b->upd_nwg), dim3(256), 0, c->stream, c->bjb_ntiles, b->upd_nwg, c->bjb_start, b->u,
-            b->r, b->y, (const double *)b->q, (const double *)b->p, (const double *)c->minv, c->bj_rowoff, c->bj_meta,
-            b->part, (const BatchState *)st, 0);
-    BTRY(enqueue_restrict<W>(c, b->r, b->y, st, b->part2, b->spmm_nwg, 0, max_iter));
-    BTRY(enqueue_coarse<W>(c, st));
-    BTRY(enqueue_prolong<W>(c, b->y, b->z, b->r, st, 0));
-    BLAUNCH(k_bbeta, dim3(W), dim3(256), 0, c->stream, (const double *)b->part, b->vec_nwg, st);
-    BLAUNCH(k_bpupdate<W>, dim3(std::min<int64_t>(8192, (c->n + 7) / 8)), dim3(256), 0, c->stream, c->n,
+            (const double *)b->u, (const double *)b->f, b->r, b->part2, (const BatchState *)st, nullptr);
+    BLAUNCH(k_bupdate_bj<W>, dim3(b->upd_nwg), dim3(256), 0, c->stream, c->bjb_ntiles, b->upd_nwg, c->bjb_start,
+            b->r, b->y, (const double *)b->q, (const double *)c->minv, c->bj_rowoff, c->bj_meta, b->part, b->part3,
+            (const BatchState *)st, 0);
+    BTRY(enqueue_restrict<W>(c, b->r, b->y, st, b->part2, nullptr, b->spmm_nwg, 0, max_iter, nullptr));
+    BTRY(enqueue_coarse<W>(c, st, nullptr));
+    BTRY(enqueue_prolong<W>(c, b->y, b->z, b->r, st));
+    BLAUNCH(k_brho, dim3(W), dim3(256), 0, c->stream, (const double *)b->part, b->vec_nwg, st);
+    BLAUNCH(k_bpstart<W>, dim3(std::min<int64_t>(8192, (c->n + 7) / 8)), dim3(256), 0, c->stream, c->n,
             (const double *)b->z, b->p, (const BatchState *)st);
     return DPCG_OK;
 }
@@ -1413,18 +1550,17 @@ int enqueue_biteration(dpcg_ctx *c, int max_iter, std::vector<hipEvent_t> &ev, s
     hipExtLaunchKernelGGL((k_bspmm<0, W>), dim3(b->spmm_nwg), dim3(64 * kSpmmWaves), 0, c->stream, e0, e1, 0, c->nb, c->brow_ptr,
                           c->bcol, (const double *)c->bval, (const int32_t *)b->pair_len,
                           (const int32_t *)b->pair_col, (const uint16_t *)b->pair_ab, (const double *)b->p,
-                          (const double *)nullptr, b->q, b->part, (const BatchState *)st);
+                          (const double *)nullptr, b->q, b->part, (const BatchState *)st, b->progress);
     BHIP(hipGetLastError());
     BLAUNCH(k_balpha, dim3(W), dim3(1024), 0, c->stream, (const double *)b->part, b->spmm_nwg, st);
-    BLAUNCH(k_bupdate_bj<W>, dim3(b->upd_nwg), dim3(256), 0, c->stream, c->bjb_ntiles, b->upd_nwg, c->bjb_start, b->u,
-            b->r, b->y, (const double *)b->q, (const double *)b->p, (const double *)c->minv, c->bj_rowoff, c->bj_meta,
-            b->part2, (const BatchState *)st, 1);
-    BTRY(enqueue_restrict<W>(c, b->r, b->y, st, b->part2, b->upd_nwg, 1, max_iter));
-    BTRY(enqueue_coarse<W>(c, st));
-    BTRY(enqueue_prolong<W>(c, b->y, b->z, b->r, st, 1));
-    BLAUNCH(k_bbeta, dim3(W), dim3(256), 0, c->stream, (const double *)b->part, b->vec_nwg, st);
-    BLAUNCH(k_bpupdate<W>, dim3(std::min<int64_t>(8192, (c->n + 7) / 8)), dim3(256), 0, c->stream, c->n,
-            (const double *)b->z, b->p, (const BatchState *)st);
+    BLAUNCH(k_bupdate_bj<W>, dim3(b->upd_nwg), dim3(256), 0, c->stream, c->bjb_ntiles, b->upd_nwg, c->bjb_start,
+            b->r, b->y, (const double *)b->q, (const double *)c->minv, c->bj_rowoff, c->bj_meta, b->part2, b->part3,
+            (const BatchState *)st, 1);
+    BTRY(enqueue_restrict<W>(c, b->r, b->y, st, b->part2, b->part3, b->upd_nwg, 1, max_iter, b->h));
+    BTRY(enqueue_coarse<W>(c, st, b->h));
+    BLAUNCH(k_bprolong_p<W>, dim3(b->vec_nwg), dim3(256), 0, c->stream, c->n, b->vec_nwg, c->z_ptr, c->z_col, c->z_val,
+            c->k > 0 ? (const double *)b->delta : nullptr, (const double *)b->y, (const double *)b->hd,
+            std::max(1, (c->k + 15) / 16), b->u, b->p, st);
     return DPCG_OK;
 }
 
@@ -1446,7 +1582,7 @@ int spmv_batch_w(dpcg_ctx *c, int32_t nrhs, const double *X, double *Y) {
     BLAUNCH(k_bpack<W>, dim3(pgrid), dim3(256), 0, s, c->n, nrhs, X, b->p);
     BLAUNCH((k_bspmm<0, W>), dim3(b->spmm_nwg), dim3(64 * kSpmmWaves), 0, s, c->nb, c->brow_ptr, c->bcol, c->bval,
             (const int32_t *)b->pair_len, (const int32_t *)b->pair_col, (const uint16_t *)b->pair_ab,
-            (const double *)b->p, (const double *)nullptr, b->q, b->part, (const BatchState *)nullptr);
+            (const double *)b->p, (const double *)nullptr, b->q, b->part, (const BatchState *)nullptr, nullptr);
     BLAUNCH(k_bunpack<W>, dim3(pgrid), dim3(256), 0, s, c->n, nrhs, (const double *)b->q, Y, 0u);
     BHIP(hipStreamSynchronize(s));
     return DPCG_OK;
@@ -1483,16 +1619,13 @@ int solve_batch_w(dpcg_ctx *c, int32_t nrhs, const double *F, double *U, double 
     if (init.any) {
         *b->snap = init;
         BHIP(hipMemcpyAsync(b->st, b->snap, sizeof(BatchState), hipMemcpyHostToDevice, s));
-        BHIP(hipStreamSynchronize(s));
+        __atomic_store_n(b->progress, 0, __ATOMIC_SEQ_CST);
         BTRY(enqueue_bstart<W>(c, guess, opt.max_iter));
+        const int32_t enq = follow(s, &b->progress, 1, opt.max_iter, opt.check_every, [&](int32_t i) {
+            return enqueue_biteration<W>(c, opt.max_iter, ev, ev_used, i);
+        });
+        if (enq < 0) return enq;
         BTRY(read_bstate(c, st));
-        int32_t enq = 0;
-        while (st.any && enq < opt.max_iter) {
-            const int m = std::min(opt.check_every, opt.max_iter - enq);
-            for (int i = 0; i < m; ++i) BTRY(enqueue_biteration<W>(c, opt.max_iter, ev, ev_used, enq + i));
-            enq += m;
-            BTRY(read_bstate(c, st));
-        }
         for (int j = 0; j < W; ++j)
             if (st.flag[j] == kRunning) {  // the host-side cap ended the loop (max_iter == 0)
                 st.flag[j] = kMaxIter;
@@ -1514,7 +1647,7 @@ int solve_batch_w(dpcg_ctx *c, int32_t nrhs, const double *F, double *U, double 
     // true residuals f_j - K u_j
     BLAUNCH((k_bspmm<1, W>), dim3(b->spmm_nwg), dim3(64 * kSpmmWaves), 0, s, c->nb, c->brow_ptr, c->bcol, c->bval,
             (const int32_t *)b->pair_len, (const int32_t *)b->pair_col, (const uint16_t *)b->pair_ab,
-            (const double *)b->u, (const double *)b->f, b->q, b->part2, (const BatchState *)nullptr);
+            (const double *)b->u, (const double *)b->f, b->q, b->part2, (const BatchState *)nullptr, nullptr);
     BLAUNCH(k_baux<W>, dim3(1), dim3(1024), 0, s, (const double *)b->part2, (const double *)nullptr, b->spmm_nwg, b->st);
     BatchState fin;
     BTRY(read_bstate(c, fin));

@@ -324,47 +324,6 @@ int enqueue_iteration(dpcg_ctx *c, Workspace &w, double *u, int max_iter, int re
     return DPCG_OK;
 }
 
-// Keeps iterations enqueued on the stream (enqueue(i) for i = 0, 1, ...) until every
-// workspace's flag leaves kRunning or max_iter have been enqueued.  The
-// SpMV posts the state it finds to pinned memory; the host stays at most
-// min(check_every, kAhead) iterations ahead of the last one started, so a solve neither stops for a read-back
-// nor runs more than kAhead - 1 idle iterations past its end (with a read-back every 16
-// iterations a 10^3 solve took 2.85 ms, now 2.59; 23^3 7.3 -> 6.9 ms; three iterations cover
-// the host's 15 us per iteration of launches).  Returns the iterations enqueued, or a
-// negative status.
-constexpr int kAhead = 3;
-
-template <class Enqueue>
-int32_t follow(hipStream_t s, Workspace *const *ws, int count, int max_iter, int check_every, const Enqueue &enqueue) {
-    const int ahead = std::min(check_every, kAhead);
-    int32_t enq = 0;
-    uint32_t spins = 0;
-    while (true) {
-        bool running = false;
-        int32_t started = enq;
-        for (int i = 0; i < count; ++i) {
-            const uint64_t v = __atomic_load_n(ws[i]->progress, __ATOMIC_RELAXED);
-            if ((int32_t)(v >> 32) != kRunning) continue;
-            running = true;
-            started = std::min(started, (int32_t)(uint32_t)v);
-        }
-        if (!running || enq >= max_iter) return enq;
-        if (enq - started < ahead) {
-            const int e = enqueue(enq);
-            if (e != DPCG_OK) return e;
-            ++enq;
-            spins = 0;
-        } else if ((++spins & 4095) == 0) {
-            // nothing left on the stream (the state tells why), or an error
-            const hipError_t q = hipStreamQuery(s);
-            if (q == hipSuccess) return enq;
-            if (q != hipErrorNotReady) return DPCG_EHIP;
-        } else {
-            __builtin_ia32_pause();
-        }
-    }
-}
-
 // Algorithm 1 from the start of Algorithm 2 on workspace w until the device flag leaves
 // kRunning (thr: absolute threshold on ||r_i||).  st receives the final state, with
 // iters_done set also when the loop ended by the host-side cap (max_iter == 0).
@@ -378,8 +337,7 @@ int run_cg(dpcg_ctx *c, Workspace &w, const double *f, double *u, double thr, bo
     c->events_used = 0;
     __atomic_store_n(w.progress, 0, __ATOMIC_SEQ_CST);
     TRY(enqueue_start(c, w, f, u, guess, max_iter, record));
-    Workspace *one = &w;
-    const int32_t enq = follow(c->stream, &one, 1, max_iter, check_every,
+    const int32_t enq = follow(c->stream, &w.progress, 1, max_iter, check_every,
                                [&](int32_t i) { return enqueue_iteration(c, w, u, max_iter, record, i); });
     if (enq < 0) return enq;
     TRY(read_state(c, w, st));
@@ -667,7 +625,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
     HIP_TRY(hipStreamSynchronize(S));
     // descriptors and phase offsets
     std::vector<MsSys> sys(count);
-    std::vector<Workspace *> ws(count);
+    std::vector<uint64_t *> progress(count);
     bool fold = true;  // every system's update adds its own p^T q
     MsTable tab{};
     tab.nsys = count;
@@ -729,7 +687,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         d.st = w.st;
         d.progress = w.progress;
         __atomic_store_n(w.progress, fnorm[i] > 0.0 ? 0 : (uint64_t)kConverged << 32, __ATOMIC_SEQ_CST);
-        ws[i] = &w;
+        progress[i] = w.progress;
         const int n_ph[kMsPhases] = {round8(c->spmv.nwg), 1, round8(c->bj_nwg), std::max(1, c->k),
                                      c->k == 0                ? 0
                                      : coarse_by_rows(c->k) ? coarse_parts(c->k, c->coarse_nt)
@@ -782,7 +740,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         for (int i = 0; i < count; ++i) st[i] = *hs[i]->ws[0].snap;
         return DPCG_OK;
     };
-    const int32_t enq = follow(S, ws.data(), count, max_iter, opt.check_every, [&](int32_t) -> int {
+    const int32_t enq = follow(S, progress.data(), count, max_iter, opt.check_every, [&](int32_t) -> int {
         LAUNCH(launch_ms_spmv_p(S, T, Y, tot[kMsSpmv]));
         if (!fold) LAUNCH(launch_ms_alpha(S, Y, count));
         LAUNCH(launch_ms_update_bj(S, T, Y, tot[kMsBj]));

@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "../../include/dpcg.h"
@@ -158,6 +159,15 @@ struct Workspace {
     int32_t hist_len = 0;
 };
 
+// Tells the host (pinned memory) the flag and the iterations started, so that it can keep a
+// few iterations enqueued without waiting for the stream.  The SpMV's first workgroup does
+// it as the kernel starts: a kernel ends only once the host's bus has taken the store (about
+// 1 us), which the rest of the product hides and the short kernels do not.
+__device__ __forceinline__ void post_progress(uint64_t *progress, int32_t flag, int32_t started) {
+    __hip_atomic_store(progress, (uint64_t)(uint32_t)flag << 32 | (uint32_t)started, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Device state of a multi-RHS solve: one recurrence per column, as State.
 struct BatchState {
     int32_t any;                 // 1 while some column runs (set by the restriction's check)
@@ -172,15 +182,19 @@ struct BatchState {
     double beta[kBatchCols];
     double rr[kBatchCols];
     double aux[kBatchCols];      // per-column scratch (norms)
+    double ry[kBatchCols];       // r_j^T y_j (the restriction's check, from the update's partials)
+    int32_t ran[kBatchCols];     // 1: the column ran in the iteration in flight
+    int32_t pend;                // 1: u lacks the iteration in flight's alpha_j p_j (see k_bprolong_p)
     int32_t nonfinite;
-    int32_t pad2;
 };
 
 // n x kBatchCols row-major vectors (entry (d, j) at d * kBatchCols + j).
 struct BatchWorkspace {
     double *f = nullptr, *u = nullptr, *r = nullptr, *y = nullptr, *z = nullptr, *q = nullptr, *p = nullptr;
     double *g = nullptr, *delta = nullptr;        // k x kBatchCols
-    double *part = nullptr, *part2 = nullptr;     // per-workgroup column partials
+    double *h = nullptr, *hd = nullptr;           // Z^T R (k columns), partial sums of h^T delta
+    double *part = nullptr, *part2 = nullptr, *part3 = nullptr;  // per-workgroup column partials
+    uint64_t *progress = nullptr;                 // pinned, as in Workspace
     BatchState *st = nullptr;                     // device
     BatchState *snap = nullptr;                   // pinned host mirror
     int32_t spmm_nwg = 0, upd_nwg = 0, vec_nwg = 0;
@@ -191,14 +205,14 @@ struct BatchWorkspace {
     uint16_t *pair_ab = nullptr;
     // restriction segments: seg[4 s .. 4 s + 3] = (column, list 0 = Z^T / 1 = (KZ)^T, begin,
     // end), at most kBatchSegEntries entries each; column c owns segments
-    // seg_ptr[c] .. seg_ptr[c + 1] - 1, whose partial sums are added in that order
+    // seg_ptr[c] .. seg_ptr[c + 1] - 1, those of (KZ)^T from seg_ptr[k + 1 + c] on
     int32_t *seg = nullptr, *seg_ptr = nullptr;
     double *seg_part = nullptr;
     int32_t nseg = 0;
     // grouped restriction on the matrix cores, used when runs of vectors share their
     // triplets: gseg[7 s ..] = (first vector, vectors, list, first row entry, first value,
-    // rows, row-list length); vector c adds partial row gcol[3c+2] of segments gcol[3c] ..
-    // gcol[3c+1]-1; zr, zv: the groups' rows and dense blocks of Z
+    // rows, row-list length); vector c adds partial row gcol[4c+3] of segments gcol[4c] ..
+    // gcol[4c+2]-1, those of Z^T before gcol[4c+1]; zr, zv: the groups' rows and dense blocks of Z
     int32_t *gseg = nullptr, *gcol = nullptr, *zr = nullptr;
     double *zv = nullptr;
     int32_t ngseg = 0;
@@ -370,6 +384,48 @@ hipError_t launch_ms_beta(hipStream_t s, const MsTable *tab, const MsSys *sys, i
 hipError_t launch_to_f32(const dpcg_ctx *c, const double *src, int64_t count, float *dst);
 // y += x
 hipError_t launch_add(const dpcg_ctx *c, const double *x, double *y);
+
+// Keeps iterations enqueued on the stream (enqueue(i) for i = 0, 1, ...) until every
+// posted flag leaves kRunning or max_iter have been enqueued.  The
+// SpMV posts the state it finds to pinned memory; the host stays at most
+// min(check_every, kAhead) iterations ahead of the last one started, so a solve neither stops for a read-back
+// nor runs more than kAhead - 1 idle iterations past its end (with a read-back every 16
+// iterations a 10^3 solve took 2.85 ms, now 2.59; 23^3 7.3 -> 6.9 ms; three iterations cover
+// the host's 15 us per iteration of launches).  Returns the iterations enqueued, or a
+// negative status.
+constexpr int kAhead = 3;
+
+template <class Enqueue>
+int32_t follow(hipStream_t s, uint64_t *const *progress, int count, int max_iter, int check_every,
+               const Enqueue &enqueue) {
+    const int ahead = std::min(check_every, kAhead);
+    int32_t enq = 0;
+    uint32_t spins = 0;
+    while (true) {
+        bool running = false;
+        int32_t started = enq;
+        for (int i = 0; i < count; ++i) {
+            const uint64_t v = __atomic_load_n(progress[i], __ATOMIC_RELAXED);
+            if ((int32_t)(v >> 32) != kRunning) continue;
+            running = true;
+            started = std::min(started, (int32_t)(uint32_t)v);
+        }
+        if (!running || enq >= max_iter) return enq;
+        if (enq - started < ahead) {
+            const int e = enqueue(enq);
+            if (e != DPCG_OK) return e;
+            ++enq;
+            spins = 0;
+        } else if ((++spins & 4095) == 0) {
+            // nothing left on the stream (the state tells why), or an error
+            const hipError_t q = hipStreamQuery(s);
+            if (q == hipSuccess) return enq;
+            if (q != hipErrorNotReady) return DPCG_EHIP;
+        } else {
+            __builtin_ia32_pause();
+        }
+    }
+}
 
 // dpcg.cpp: the solve workspace (vectors, k-vectors, partial sums, State) as one block
 // of workspace_bytes(c) bytes carved by carve_workspace, and a solve on a given one

@@ -32,13 +32,6 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
     return (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
-// Fixed-order sum of n partials, valid in every thread.
-__device__ __forceinline__ double reduce_parts(const double *parts, int n, double *lds) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += kThreads) s += parts[i];
-    return block_sum(s, lds);
-}
-
 // Workgroup sum over NW waves (lds >= NW entries); every thread receives the same value.
 template <int NW>
 __device__ __forceinline__ double block_sum_n(double v, double *lds) {
@@ -77,16 +70,20 @@ __device__ __forceinline__ double strided_share(const double *__restrict__ parts
     return a[0];
 }
 
-// As strided_share for a list of at least one entry that mostly fits one round: the
-// round's loads are clamped to the list instead of left to a serial tail.
+// As strided_share, the last round's loads clamped to the list (of at least one entry)
+// instead of left to a serial tail.
 template <int NT, int U>
 __device__ __forceinline__ double masked_share(const double *__restrict__ parts, int n) {
     double a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = parts[min((int)threadIdx.x + u * NT, n - 1)];
+    for (int u = 0; u < U; ++u) a[u] = 0.0;
+    for (int i = threadIdx.x; i < n; i += U * NT) {
+        double v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = (int)threadIdx.x + u * NT < n ? a[u] : 0.0;
-    for (int i = threadIdx.x + U * NT; i < n; i += NT) a[0] += parts[i];
+        for (int u = 0; u < U; ++u) v[u] = parts[min(i + u * NT, n - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] += i + u * NT < n ? v[u] : 0.0;
+    }
 #pragma unroll
     for (int w = 1; w < U; w <<= 1)
 #pragma unroll
@@ -292,15 +289,6 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv(SpmvShape sh, const int32
     k_spmv_body<G, MODE, V>(blockIdx.x, sh, brow_ptr, bcol, bval, nnzb, x, f, y, part);
 }
 
-
-// Tells the host (pinned memory) the flag and the iterations started, so that it can keep a
-// few iterations enqueued without waiting for the stream.  The SpMV's first workgroup does
-// it as the kernel starts: a kernel ends only once the host's bus has taken the store (about
-// 1 us), which the rest of the product hides and the short kernels do not.
-__device__ __forceinline__ void post_progress(uint64_t *progress, int32_t flag, int32_t started) {
-    __hip_atomic_store(progress, (uint64_t)(uint32_t)flag << 32 | (uint32_t)started, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
-}
 
 // Matrix product of Algorithm 1 for iteration i = st->iter: q = K p_i (p_i in buffer
 // i & 1, formed by the prolongation or the beta kernel) and partials of p_i^T q.  Only
@@ -744,8 +732,8 @@ __device__ __forceinline__ void k_restrict_body(int vb, int vg,
     if (st) {
         if (wg_flag(st) != kRunning) return;
         if (vb == 0 && n_rr > 0) {
-            double rr = strided_share<kRestrictThreads, 8>(part_rr, n_rr);
-            double ry = part_ry ? strided_share<kRestrictThreads, 8>(part_ry, n_rr) : 0.0;
+            double rr = masked_share<kRestrictThreads, 8>(part_rr, n_rr);
+            double ry = part_ry ? masked_share<kRestrictThreads, 8>(part_ry, n_rr) : 0.0;
             block_sum2_n<kRestrictWaves>(rr, ry, lds);
             if (threadIdx.x == 0) {
                 const int done = st->iter + iter_offset;
@@ -1153,11 +1141,11 @@ __global__ __launch_bounds__(kThreads) void k_norm_finite(int64_t n, int32_t nwg
 }
 
 // st->aux = sum of n partials of part_a; st->nonfinite = (sum of part_b > 0) when part_b given.
-__global__ __launch_bounds__(kThreads) void k_reduce_aux(const double *__restrict__ part_a,
-                                                         const double *__restrict__ part_b, int n, State *st) {
-    __shared__ double lds[4];
-    const double s = reduce_parts(part_a, n, lds);
-    const double c = part_b ? reduce_parts(part_b, n, lds) : 0.0;
+__global__ __launch_bounds__(1024) void k_reduce_aux(const double *__restrict__ part_a,
+                                                     const double *__restrict__ part_b, int n, State *st) {
+    __shared__ double lds[16];
+    const double s = block_sum_n<16>(masked_share<1024, 8>(part_a, n), lds);
+    const double c = part_b ? block_sum_n<16>(masked_share<1024, 8>(part_b, n), lds) : 0.0;
     if (threadIdx.x == 0) {
         st->aux = s;
         st->nonfinite = c > 0.0 ? 1 : 0;
@@ -1510,7 +1498,7 @@ hipError_t launch_check_finite_norm(const dpcg_ctx *c, const double *a, const do
                        w.part_a, w.part_b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_aux, dim3(1), dim3(kThreads), 0, c->stream, w.part_a, w.part_b, c->vec_nwg,
+    hipLaunchKernelGGL(k_reduce_aux, dim3(1), dim3(1024), 0, c->stream, w.part_a, w.part_b, c->vec_nwg,
                        w.st);
     return hipGetLastError();
 }
@@ -1577,7 +1565,7 @@ hipError_t launch_ms_beta(hipStream_t s, const MsTable *tab, const MsSys *sys, i
 }
 
 hipError_t launch_reduce_aux(const dpcg_ctx *c, Workspace &w, int n_parts) {
-    hipLaunchKernelGGL(k_reduce_aux, dim3(1), dim3(kThreads), 0, c->stream, w.part_a, nullptr, n_parts, w.st);
+    hipLaunchKernelGGL(k_reduce_aux, dim3(1), dim3(1024), 0, c->stream, w.part_a, nullptr, n_parts, w.st);
     return hipGetLastError();
 }
 
