@@ -225,9 +225,7 @@ int dpcg_solve_batch(dpcg_handle h, int32_t nrhs, const double *F, double *U, do
  * device) solves K_i U[i] = F[i] (device arrays of its n_i) with the method of
  * dpcg_solve and its own stopping test.  Each phase of an iteration runs as one kernel
  * launch over the workgroups of every system still iterating, so small systems share
- * the launches instead of queueing 7 of them per iteration each.  Handles that were
- * never tuned get their SpMV lane-group size from dpcg_autotune first.  All work of the
- * call runs on handles[0]'s stream (the others are synchronised first).
+ * the launches instead of queueing them per iteration each.  All work of the call runs on handles[0]'s stream (the others are synchronised first).
  * infos[count] (host, may be NULL).  Returns DPCG_OK when every system converged, else
  * DPCG_EBREAKDOWN if one broke down, else DPCG_NOT_CONVERGED; DPCG_EINVAL (count, a
  * repeated handle, tol, max_iter, record_history or a precision other than FP64),

@@ -595,8 +595,8 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
             for (size_t i = 0; i < own.size(); ++i) hs[i]->stream = own[i];
         }
     } restore{hs, own};
-    for (int i = 0; i < count; ++i)
-        if (!hs[i]->tuned) autotune_spmv(hs[i], 5);
+    // (each handle keeps its SpMV lane-group size: timed alone, a small system's launch latency
+    // hides what the size costs beside the others, and tuning took longer than it gained)
     // norms and finiteness of every right-hand side (and guess)
     std::vector<double> fnorm(count);
     for (int i = 0; i < count; ++i) {
@@ -649,6 +649,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         d.einv_ld = c->einv_ld;
         d.brow_ptr = c->brow_ptr;
         d.bcol = c->bcol;
+        d.bcol16 = c->bcol16;
         d.bval = c->bval;
         d.minv = c->minv;
         d.bj_rowoff = c->bj_rowoff;

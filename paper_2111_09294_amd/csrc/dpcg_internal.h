@@ -245,6 +245,7 @@ struct MsSys {
     int32_t guess, pad;
     int64_t n, nnzb, einv_ld;
     const int32_t *brow_ptr, *bcol;
+    const int16_t *bcol16;  // or null, as in the handle
     const double *bval;
     const double *minv;
     const int32_t *bj_rowoff, *bj_meta, *bj_wg_start;

@@ -1216,6 +1216,16 @@ __device__ __forceinline__ int ms_find(const MsTable *__restrict__ tab, int phas
     return lo;
 }
 
+template <class CI>
+__device__ __forceinline__ void ms_spmv_p(int vb, const SpmvShape &sh, const MsSys &S, const CI *bcol) {
+    switch (S.group) {
+        case 4: k_spmv_p_body<4>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+        case 8: k_spmv_p_body<8>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+        case 16: k_spmv_p_body<16>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+        default: k_spmv_p_body<32>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
+    }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(kSpmvThreads) void k_ms_spmv(const MsTable *__restrict__ tab,
                                                           const MsSys *__restrict__ sys) {
@@ -1224,12 +1234,8 @@ __global__ __launch_bounds__(kSpmvThreads) void k_ms_spmv(const MsTable *__restr
     const int vb = blockIdx.x - tab->off[kMsSpmv][s];
     const SpmvShape sh{S.nb, S.steps, S.spmv_nwg};
     if (MODE == 0) {
-        switch (S.group) {
-            case 4: k_spmv_p_body<4, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
-            case 8: k_spmv_p_body<8, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
-            case 16: k_spmv_p_body<16, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
-            default: k_spmv_p_body<32, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.p0, S.p1, S.q, S.part_a, S.st, S.progress); break;
-        }
+        if (S.bcol16) ms_spmv_p(vb, sh, S, S.bcol16);
+        else ms_spmv_p(vb, sh, S, S.bcol);
     } else {
         if (S.st->flag != kRunning) return;
         switch (S.group) {
