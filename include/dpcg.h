@@ -85,7 +85,7 @@ typedef struct {
     int64_t nnzb;              /* 3x3 blocks of the internal block-CSR copy of K        */
     int64_t k;                 /* deflation vectors (columns of Z)                      */
     int64_t nnz_z;             /* nonzeros of Z                                         */
-    int64_t nnz_kz;            /* nonzeros of K Z                                       */
+    int64_t nnz_kz;            /* stored entries of K Z                                 */
     int64_t nblocks;           /* block-Jacobi blocks                                   */
     int64_t bj_values;         /* sum of squared sizes of the blocks of <= 18 unknowns  */
     int64_t device_bytes;      /* device memory held by the handle                      */

@@ -1291,8 +1291,21 @@ int balloc(dpcg_ctx *c, T **p, size_t count) {
     return DPCG_OK;
 }
 
+// frees an array of the handle (no work on it may be pending) and makes it anew
+template <class T>
+int brealloc(dpcg_ctx *c, T **p, size_t count) {
+    if (*p) {
+        c->allocations.erase(std::find(c->allocations.begin(), c->allocations.end(), (void *)*p));
+        dev_release(*p);
+        *p = nullptr;
+    }
+    return balloc(c, p, count);
+}
+
+int restriction_lists(dpcg_ctx *c);
+
 int ensure_ws(dpcg_ctx *c) {
-    if (c->bws) return DPCG_OK;
+    if (c->bws) return c->bws->stale ? restriction_lists(c) : (int)DPCG_OK;
     auto *b = new BatchWorkspace();
     c->bws = b;
     constexpr int W = kBatchCols;  // the widest layout
@@ -1325,7 +1338,16 @@ int ensure_ws(dpcg_ctx *c) {
     BTRY(balloc(c, &b->st, 1));
     BHIP(hipHostMalloc((void **)&b->snap, sizeof(BatchState) + sizeof(uint64_t), hipHostMallocDefault));
     b->progress = reinterpret_cast<uint64_t *>(b->snap + 1);
-    // restriction segments from the column pointers of Z^T and (KZ)^T
+    return restriction_lists(c);
+}
+
+// The restriction's segments and groups from Z^T and (KZ)^T, on the first batched call and
+// after new values of K (another set of (KZ)^T's entries may be kept).
+int restriction_lists(dpcg_ctx *c) {
+    constexpr int W = kBatchCols;  // the widest layout
+    BatchWorkspace *b = c->bws;
+    BHIP(hipStreamSynchronize(c->stream));
+    const int64_t held = c->device_bytes - b->list_bytes;
     std::vector<int32_t> zp(c->k + 1, 0), kp(c->k + 1, 0), seg, sptr(2 * (size_t)c->k + 1, 0);
     if (c->k > 0) {
         BHIP(hipMemcpyAsync(zp.data(), c->zt_ptr, sizeof(int32_t) * (c->k + 1), hipMemcpyDeviceToHost, c->stream));
@@ -1347,8 +1369,8 @@ int ensure_ws(dpcg_ctx *c) {
     }
     b->nseg = (int32_t)(seg.size() / 4);
     sptr[c->k] = b->nseg;
-    BTRY(balloc(c, &b->seg, std::max<size_t>(4, seg.size())));
-    BTRY(balloc(c, &b->seg_ptr, sptr.size()));
+    BTRY(brealloc(c, &b->seg, std::max<size_t>(4, seg.size())));
+    BTRY(brealloc(c, &b->seg_ptr, sptr.size()));
     // groups of consecutive vectors whose Z columns cover the same triplets and whose
     // (KZ)^T rows coincide; the grouped kernel is used when they hold two vectors or more
     // on average
@@ -1429,10 +1451,10 @@ int ensure_ws(dpcg_ctx *c) {
     }
     b->ngseg = b->grouped ? (int32_t)(gseg.size() / kGroupSeg) : 0;
     if (b->grouped) {
-        BTRY(balloc(c, &b->gseg, std::max<size_t>(kGroupSeg, gseg.size())));
-        BTRY(balloc(c, &b->gcol, gcol.size()));
-        BTRY(balloc(c, &b->zr, std::max<size_t>(1, zr.size())));
-        BTRY(balloc(c, &b->zv, std::max<size_t>(1, zv.size())));
+        BTRY(brealloc(c, &b->gseg, std::max<size_t>(kGroupSeg, gseg.size())));
+        BTRY(brealloc(c, &b->gcol, gcol.size()));
+        BTRY(brealloc(c, &b->zr, std::max<size_t>(1, zr.size())));
+        BTRY(brealloc(c, &b->zv, std::max<size_t>(1, zv.size())));
         if (!gseg.empty())
             BHIP(hipMemcpyAsync(b->gseg, gseg.data(), sizeof(int32_t) * gseg.size(), hipMemcpyHostToDevice, c->stream));
         BHIP(hipMemcpyAsync(b->gcol, gcol.data(), sizeof(int32_t) * gcol.size(), hipMemcpyHostToDevice, c->stream));
@@ -1441,11 +1463,14 @@ int ensure_ws(dpcg_ctx *c) {
         if (!zv.empty())
             BHIP(hipMemcpyAsync(b->zv, zv.data(), sizeof(double) * zv.size(), hipMemcpyHostToDevice, c->stream));
     }
-    BTRY(balloc(c, &b->seg_part,
+    BTRY(brealloc(c, &b->seg_part,
                 std::max<size_t>((size_t)std::max(1, b->nseg) * W, (size_t)b->ngseg * kGroupCols * W)));
     if (!seg.empty()) BHIP(hipMemcpyAsync(b->seg, seg.data(), sizeof(int32_t) * seg.size(), hipMemcpyHostToDevice, c->stream));
     BHIP(hipMemcpyAsync(b->seg_ptr, sptr.data(), sizeof(int32_t) * sptr.size(), hipMemcpyHostToDevice, c->stream));
     BHIP(hipStreamSynchronize(c->stream));
+    b->list_bytes = c->device_bytes - held - b->list_bytes;
+    c->device_bytes = held + b->list_bytes;
+    b->stale = false;
     return DPCG_OK;
 }
 

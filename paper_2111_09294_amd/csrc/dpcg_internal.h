@@ -217,6 +217,8 @@ struct BatchWorkspace {
     double *zv = nullptr;
     int32_t ngseg = 0;
     bool grouped = false;
+    int64_t list_bytes = 0;  // device bytes of these lists
+    bool stale = false;  // (KZ)^T's pattern has changed since the restriction lists were made
 };
 
 // A block-Jacobi block of more than kMaxBlock DoFs; a wave of its apply (tiles (row, j0) ..
@@ -282,6 +284,7 @@ struct dpcg_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     int64_t n = 0, nnz = 0, nnzb = 0, nnz_z = 0, nnz_kz = 0, bj_values = 0, device_bytes = 0;
+    int64_t kz_structure = 0;   // structural entries of K Z (the room of kzt_idx and kzt_val)
     int32_t nb = 0, k = 0, nblocks = 0;
     // K
     int32_t *brow_ptr = nullptr, *bcol = nullptr;

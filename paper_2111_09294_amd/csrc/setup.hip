@@ -787,15 +787,22 @@ constexpr int kBatch = 16;
 constexpr int kSlice = 1024;
 constexpr int kTouchLds = 2048;  // LDS words of the touched-vector bitmap (k <= 65536)
 
+//
+// K z_j is zero on most of its structure: a rigid-body mode stores no energy in an element
+// all of whose nodes move with it, so inside the subdomain (and for the enriched modes inside
+// their supports) only the rounding of the sum is left.  (KZ)^T keeps a triplet of a run of
+// vectors with the same structure (the modes of one subdomain) where one of its entries
+// exceeds that rounding, 4 eps (sum of |K| along the row) (largest |z| there); the rest, a
+// quarter to a third of the entries, is left out.
 struct KzBatch {
     int64_t j0, ncol, lo3, w3, off3, slice0, nslice, bit0;
-    int64_t moff;  // first triplet of the batch's window in the structure masks mk and rb
+    int64_t moff;  // first triplet of the batch's window in the masks mk, rb and km
 };
 
-// clears the batch's touched bits and, when masks, its structure masks
+// clears the batch's touched bits and, when masks, its structure masks and run bits
 __global__ __launch_bounds__(256) void k_kzb_init(const KzBatch *__restrict__ bt, int words, uint32_t *__restrict__ mk,
                                                   uint32_t *__restrict__ rb, uint32_t *__restrict__ touched,
-                                                  int masks) {
+                                                  uint32_t *__restrict__ ends, int masks) {
     const KzBatch B = bt[blockIdx.y];
     if (blockIdx.x >= B.nslice) return;
     const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = min<int64_t>(B.w3, t0 + kSlice);
@@ -807,6 +814,7 @@ __global__ __launch_bounds__(256) void k_kzb_init(const KzBatch *__restrict__ bt
     }
     if (blockIdx.x == 0)
         for (int t = threadIdx.x; t < words; t += 256) touched[B.bit0 + t] = 0u;
+    if (masks && blockIdx.x == 0 && threadIdx.x == 0) ends[blockIdx.y] = 0u;
 }
 
 // one workgroup per (vector, batch): scatter z_j and flag its triplets.  The three rows
@@ -885,26 +893,35 @@ __global__ __launch_bounds__(256) void k_kzb_mark(const KzBatch *__restrict__ bt
     }
 }
 
-// per (slice, vector) counts of structure rows (three per structure triplet), and per
-// slice the number of structure triplets (work items)
+// per (slice, vector) counts of rows (three per triplet of the mask), and per slice the
+// number of triplets.  km null: the structure, and bit b of the batch's ends set where the
+// structures of vectors b and b + 1 differ; else the triplets kept (km, set on mk's triplets).
 __global__ __launch_bounds__(256) void k_kzb_count(const KzBatch *__restrict__ bt, const uint32_t *__restrict__ mk,
-                                                   int32_t *__restrict__ cnt, int32_t *__restrict__ tcnt) {
+                                                   const uint32_t *__restrict__ km, int32_t *__restrict__ cnt,
+                                                   int32_t *__restrict__ tcnt, uint32_t *__restrict__ ends) {
     __shared__ int32_t c_s[kBatch + 1];
+    __shared__ uint32_t e_s;
     const KzBatch B = bt[blockIdx.y];
     if (blockIdx.x >= B.nslice) return;
     if (threadIdx.x <= kBatch) c_s[threadIdx.x] = 0;
+    if (threadIdx.x == 0) e_s = 0u;
     __syncthreads();
+    uint32_t differ = 0u;
     const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = min<int64_t>(B.w3, t0 + kSlice);
     int32_t mine[kBatch + 1];
     for (int b = 0; b <= kBatch; ++b) mine[b] = 0;
     for (int64_t t = t0 + threadIdx.x; t < t1; t += 256) {
-        const uint32_t m = mk[B.moff + t];
+        uint32_t m = mk[B.moff + t];
+        if (km) m = m ? km[B.moff + t] : 0u;
+        differ |= m ^ (m >> 1);
         for (int b = 0; b < kBatch; ++b) mine[b] += 3 * ((m >> b) & 1u);
         mine[kBatch] += m != 0u;
     }
     for (int b = 0; b <= kBatch; ++b)
         if (mine[b]) atomicAdd(&c_s[b], mine[b]);
+    if (!km && differ) atomicOr(&e_s, differ);
     __syncthreads();
+    if (!km && threadIdx.x == 0 && e_s) atomicOr(&ends[blockIdx.y], e_s);
     if (threadIdx.x < kBatch) cnt[(B.slice0 + blockIdx.x) * kBatch + threadIdx.x] = c_s[threadIdx.x];
     if (threadIdx.x == kBatch) tcnt[B.slice0 + blockIdx.x] = c_s[kBatch];
 }
@@ -936,78 +953,101 @@ __global__ void k_kzb_offsets(const KzBatch *__restrict__ bt, int nbat, const in
     kzcnt[B.j0 + b] = run;
 }
 
-// Rank pass: every structure triplet of the slice gets a work item (its triplet, its
-// mask of vectors, and for each vector its output position in (KZ)^T), stored densely
-// per batch in slice order.
+// Every structure triplet of the slice gets a work item, stored densely per batch in slice
+// order.
 struct KzItem {
-    int32_t t, mask;
-    int32_t pos[kBatch];
+    int32_t t, mask;  // its triplet, its vectors
 };
 
-__global__ __launch_bounds__(256) void k_kzb_rank(const KzBatch *__restrict__ bt, const uint32_t *__restrict__ mk,
-                                                  const int32_t *__restrict__ soff, const int32_t *__restrict__ icnt,
-                                                  const int64_t *__restrict__ kzp, KzItem *__restrict__ items) {
-    __shared__ int32_t wave_cnt[4][kBatch + 1];
-    __shared__ int32_t carry[kBatch + 1];
+__global__ __launch_bounds__(256) void k_kzb_items(const KzBatch *__restrict__ bt, const uint32_t *__restrict__ mk,
+                                                   const int32_t *__restrict__ icnt, KzItem *__restrict__ items) {
+    __shared__ int32_t wave_cnt[kSlice / 64];
     const KzBatch B = bt[blockIdx.y];
     if (blockIdx.x >= B.nslice) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (threadIdx.x <= kBatch) carry[threadIdx.x] = 0;
-    __syncthreads();
-    // items of this slice start after the items of the batch's earlier slices
     const int64_t item0 = B.off3 + icnt[B.slice0 + blockIdx.x];
+    const int64_t t0 = (int64_t)blockIdx.x * kSlice;
+    uint32_t m[kSlice / 256];
+    int rank[kSlice / 256];
+#pragma unroll
+    for (int r = 0; r < kSlice / 256; ++r) {
+        const int64_t t = t0 + 256 * r + threadIdx.x;
+        m[r] = t < B.w3 ? mk[B.moff + t] : 0u;
+        const unsigned long long bal = __ballot(m[r] != 0u);
+        rank[r] = __popcll(bal & ((1ull << lane) - 1ull));
+        if (lane == 0) wave_cnt[4 * r + wv] = __popcll(bal);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSlice / 256; ++r) {
+        if (!m[r]) continue;
+        int before = 0;
+        for (int w = 0; w < 4 * r + wv; ++w) before += wave_cnt[w];
+        items[item0 + before + rank[r]] = KzItem{(int32_t)(t0 + 256 * r + threadIdx.x), (int32_t)m[r]};
+    }
+}
+
+// The kept triplets' entries of (KZ)^T from the dense K z, at their ranks within each vector.
+__global__ __launch_bounds__(256) void k_kzb_store(const KzBatch *__restrict__ bt, const uint32_t *__restrict__ mk,
+                                                   const uint32_t *__restrict__ km, const int32_t *__restrict__ soff,
+                                                   const int64_t *__restrict__ kzp, const double *__restrict__ kd,
+                                                   int32_t *__restrict__ kzi, double *__restrict__ kzv) {
+    __shared__ int32_t wave_cnt[2][4][kBatch];
+    const KzBatch B = bt[blockIdx.y];
+    if (blockIdx.x >= B.nslice) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = min<int64_t>(B.w3, t0 + kSlice);
-    for (int64_t c0 = t0; c0 < t1; c0 += 256) {
+    int32_t carry[kBatch];  // rows of the slice's earlier chunks
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) carry[b] = 0;
+    int buf = 0;
+    for (int64_t c0 = t0; c0 < t1; c0 += 256, buf ^= 1) {
         const int64_t t = c0 + threadIdx.x;
-        const uint32_t m = t < t1 ? mk[B.moff + t] : 0u;
-        int32_t rank[kBatch + 1];
-        for (int b = 0; b <= kBatch; ++b) {
-            const bool f = b < kBatch ? ((m >> b) & 1u) : (m != 0u);
-            const unsigned long long bal = __ballot(f);
+        uint32_t m = t < t1 ? mk[B.moff + t] : 0u;
+        if (m) m = km[B.moff + t];
+        int32_t rank[kBatch];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            const unsigned long long bal = __ballot((m >> b) & 1u);
             rank[b] = __popcll(bal & ((1ull << lane) - 1ull));
-            if (lane == 0) wave_cnt[wv][b] = __popcll(bal);
+            if (lane == 0) wave_cnt[buf][wv][b] = __popcll(bal);
         }
         __syncthreads();
-        if (m) {
-            int32_t before[kBatch + 1];
-            for (int b = 0; b <= kBatch; ++b) {
-                before[b] = carry[b];
-                for (int w2 = 0; w2 < wv; ++w2) before[b] += wave_cnt[w2][b];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            int32_t before = carry[b];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                before += w < wv ? wave_cnt[buf][w][b] : 0;
+                carry[b] += wave_cnt[buf][w][b];
             }
-            KzItem it;
-            it.t = (int32_t)t;
-            it.mask = (int32_t)m;
-            for (int b = 0; b < kBatch; ++b)
-                it.pos[b] = (b < B.ncol && ((m >> b) & 1u))
-                                ? (int32_t)(kzp[B.j0 + b] + soff[(B.slice0 + blockIdx.x) * kBatch + b] +
-                                            3 * (before[b] + rank[b]))
-                                : -1;
-            items[item0 + before[kBatch] + rank[kBatch]] = it;
+            if (!((m >> b) & 1u)) continue;
+            const int64_t pos = kzp[B.j0 + b] + soff[(B.slice0 + blockIdx.x) * kBatch + b] + 3 * (before + rank[b]);
+            for (int i = 0; i < 3; ++i) {
+                kzi[pos + i] = (int32_t)(3 * (B.lo3 + t) + i);
+                kzv[pos + i] = kd[(3 * (B.off3 + t) + i) * kBatch + b];
+            }
         }
-        __syncthreads();
-        if (threadIdx.x <= kBatch)
-            carry[threadIdx.x] += wave_cnt[0][threadIdx.x] + wave_cnt[1][threadIdx.x] + wave_cnt[2][threadIdx.x] +
-                                  wave_cnt[3][threadIdx.x];
-        __syncthreads();
     }
 }
 
 // Compute pass: (K z_j) on the three rows of each structure triplet from the packed 3x3
 // blocks.  Sixteen lanes per work item: lane bits 0-1 pick four of the batch's vectors,
 // bits 2-3 a quarter of the block row's blocks; the quarters are combined by a fixed
-// shuffle tree.  Writes (KZ)^T at the ranked positions, the dense kd, and flags the
-// deflation vectors with a nonzero in a structure row as touched.
+// shuffle tree.  Writes the dense kd and the triplet's kept vectors km (see above), and flags
+// the deflation vectors with a nonzero in a structure row as touched.
 __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ bt, const int64_t *__restrict__ nitems,
                                                     const KzItem *__restrict__ items, const int32_t *__restrict__ bptr,
                                                     const int32_t *__restrict__ bcol, const double *__restrict__ bval,
                                                     const double *__restrict__ zd, const uint32_t *__restrict__ rb,
                                                     const int64_t *__restrict__ zp,
-                                                    const int32_t *__restrict__ zc, int32_t *__restrict__ kzi,
-                                                    double *__restrict__ kzv, double *__restrict__ kd,
+                                                    const int32_t *__restrict__ zc, double *__restrict__ kd,
+                                                    uint32_t *__restrict__ km, const uint32_t *__restrict__ ends,
                                                     int words, uint32_t *touched) {
     __shared__ uint32_t tw[kTouchLds];
     const KzBatch B = bt[blockIdx.y];
     const int64_t n_it = nitems[blockIdx.y];
+    const uint32_t run_ends = ends[blockIdx.y];
     const int sub = threadIdx.x & 3, part = (threadIdx.x >> 2) & 3;
     const bool lds_bits = words <= kTouchLds;
     if (lds_bits)
@@ -1020,12 +1060,17 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
     const int64_t x0 = (int64_t)blockIdx.x * per, x1 = min(n_it, x0 + per);
     for (int64_t x = x0 + (threadIdx.x >> 4); x - (threadIdx.x >> 4) < x1; x += 16) {
         const bool live = x < x1;
-        double acc[3][4];
-        for (int i = 0; i < 3; ++i)
+        double acc[3][4], rowsum[3], zmax[4];
+        for (int i = 0; i < 3; ++i) {
+            rowsum[i] = 0.0;
             for (int b = 0; b < 4; ++b) acc[i][b] = 0.0;
+        }
+        for (int b = 0; b < 4; ++b) zmax[b] = 0.0;
         int64_t t = 0, R = 0;
+        uint32_t mask = 0u;
         if (live) {
             t = items[B.off3 + x].t;
+            mask = (uint32_t)items[B.off3 + x].mask;
             R = B.lo3 + t;
             const int64_t beg = bptr[R], mR = bptr[R + 1] - beg;
             const double *rv = bval + 9 * beg;
@@ -1036,10 +1081,12 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
                 if (!(zb & 15u)) continue;  // none of this lane's vectors has support on triplet c
                 double v[9];
                 for (int e = 0; e < 9; ++e) v[e] = rv[e * mR + (q - beg)];
+                for (int i = 0; i < 3; ++i) rowsum[i] += fabs(v[3 * i]) + fabs(v[3 * i + 1]) + fabs(v[3 * i + 2]);
                 const double *z = zd + (3 * (B.off3 + c)) * kBatch + 4 * sub;
                 for (int jj = 0; jj < 3; ++jj)
                     for (int b = 0; b < 4; ++b) {
                         const double zz = ((zb >> b) & 1u) ? z[jj * kBatch + b] : 0.0;
+                        zmax[b] = fmax(zmax[b], fabs(zz));
                         acc[0][b] = fma(v[jj], zz, acc[0][b]);
                         acc[1][b] = fma(v[3 + jj], zz, acc[1][b]);
                         acc[2][b] = fma(v[6 + jj], zz, acc[2][b]);
@@ -1053,18 +1100,28 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
                 v += __shfl_xor(v, 8);
                 acc[i][b] = v;
             }
+        for (int i = 0; i < 3; ++i) {
+            rowsum[i] += __shfl_xor(rowsum[i], 4);
+            rowsum[i] += __shfl_xor(rowsum[i], 8);
+        }
+        uint32_t keep = 0u;  // the lane's vectors with an entry above the rounding of its sum
+        for (int b = 0; b < 4; ++b) {
+            zmax[b] = fmax(zmax[b], __shfl_xor(zmax[b], 4));
+            zmax[b] = fmax(zmax[b], __shfl_xor(zmax[b], 8));
+            for (int i = 0; i < 3; ++i)  // (a NaN is kept)
+                if (!(fabs(acc[i][b]) <= 4.0 * DBL_EPSILON * rowsum[i] * zmax[b])) keep |= 1u << (4 * sub + b);
+        }
+        keep |= (uint32_t)__shfl_xor((int)keep, 1);
+        keep |= (uint32_t)__shfl_xor((int)keep, 2);
         if (!live || part != 0) continue;
+        if (sub == 0) {  // all vectors of a run with one to keep
+            for (int b = 1; b < kBatch; ++b) keep |= ((keep & ~run_ends) >> (b - 1) & 1u) << b;
+            for (int b = kBatch - 2; b >= 0; --b) keep |= ((keep >> (b + 1)) & ~(run_ends >> b) & 1u) << b;
+            km[B.moff + t] = keep & mask;
+        }
         double *o = kd + (3 * (B.off3 + t)) * kBatch + 4 * sub;
         for (int i = 0; i < 3; ++i)
             for (int b = 0; b < 4; ++b) o[i * kBatch + b] = acc[i][b];
-        for (int b = 0; b < 4; ++b) {
-            const int32_t pos = items[B.off3 + x].pos[4 * sub + b];
-            if (pos < 0) continue;
-            for (int i = 0; i < 3; ++i) {
-                kzi[pos + i] = (int32_t)(3 * R + i);
-                kzv[pos + i] = acc[i][b];
-            }
-        }
         if (sub == 0)
             for (int i = 0; i < 3; ++i)
                 for (int64_t e = zp[3 * R + i]; e < zp[3 * R + i + 1]; ++e) {
@@ -1921,7 +1978,7 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         // windows) stays under the budget: 8 GB, under 3% of the device's memory, so that
         // a large system takes few groups, whose launches fill the device better (at 80^3
         // two groups instead of sixteen with 1 GB: 4.7 against 7.7 ms of these kernels)
-        const int64_t per_triplet = 2 * 3 * kBatch * sizeof(double) + 2 * sizeof(uint32_t);
+        const int64_t per_triplet = 2 * 3 * kBatch * sizeof(double) + 3 * sizeof(uint32_t);
         const int64_t budget = int64_t(8) << 30;
         std::vector<int> gcut{0};
         int64_t acc_w = 0, max_group_w = 0, total_w = 0;
@@ -1944,7 +2001,7 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         int32_t *scnt = nullptr, *soff = nullptr, *tcnt = nullptr;
         int64_t *kzcnt = nullptr, *kzp = nullptr;
         double *zd = nullptr, *kd = nullptr;
-        uint32_t *mk = nullptr, *rbits = nullptr, *touched = nullptr;
+        uint32_t *mk = nullptr, *rbits = nullptr, *km = nullptr, *ends = nullptr, *touched = nullptr;
         HT(pool.tmp(&bt_d, nbat));
         HT(hipMemcpyAsync(bt_d, bt.data(), sizeof(KzBatch) * nbat, hipMemcpyHostToDevice, s));
         HT(pool.tmp(&scnt, slices * kBatch));
@@ -1958,6 +2015,8 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         // the values pass of a call with several groups then needs no second marking
         HT(pool.tmp(&mk, std::max<int64_t>(1, total_w)));
         HT(pool.tmp(&rbits, std::max<int64_t>(1, total_w)));
+        HT(pool.tmp(&km, std::max<int64_t>(1, total_w)));
+        HT(pool.tmp(&ends, nbat));
         HT(pool.tmp(&touched, (int64_t)max_group_nb * words));
         int32_t *icnt = nullptr;
         int64_t *nitems = nullptr;
@@ -1975,7 +2034,8 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         // bits are already in rbits) and clear touched bits
         auto prepare = [&](int g0, int g1, bool full) {
             const dim3 gs(max_slices(g0, g1), g1 - g0);
-            hipLaunchKernelGGL(k_kzb_init, gs, dim3(256), 0, s, bt_d + g0, words, mk, rbits, touched, full ? 1 : 0);
+            hipLaunchKernelGGL(k_kzb_init, gs, dim3(256), 0, s, bt_d + g0, words, mk, rbits, touched,
+                               ends + g0, full ? 1 : 0);
             hipLaunchKernelGGL(k_kzb_scatter, dim3(kBatch, g1 - g0), dim3(256), 0, s, bt_d + g0, ztp, zti, ztv, zd,
                                rbits);
             if (full) hipLaunchKernelGGL(k_kzb_mark, gs, dim3(256), 0, s, bt_d + g0, c->brow_ptr, c->bcol, rbits, mk);
@@ -1983,7 +2043,7 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         for (size_t g = 0; g + 1 < gcut.size(); ++g) {
             prepare(gcut[g], gcut[g + 1], true);
             hipLaunchKernelGGL(k_kzb_count, dim3(max_slices(gcut[g], gcut[g + 1]), gcut[g + 1] - gcut[g]), dim3(256),
-                               0, s, bt_d + gcut[g], mk, scnt, tcnt);
+                               0, s, bt_d + gcut[g], mk, (const uint32_t *)nullptr, scnt, tcnt, ends + gcut[g]);
         }
         hipLaunchKernelGGL(k_kzb_offsets, dim3(nbat), dim3(kBatch + 1), 0, s, bt_d, nbat, scnt, tcnt, soff, kzcnt,
                            icnt, nitems);
@@ -2006,8 +2066,8 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
             return DPCG_EBLOCK_NOT_SPD;
         }
         if (nkz > (int64_t)INT32_MAX) return DPCG_EINVAL;
-        if (reuse && nkz != c->nnz_kz) return DPCG_EINVAL;  // the structure of K Z must not change
-        c->nnz_kz = nkz;
+        if (reuse && nkz != c->kz_structure) return DPCG_EINVAL;  // the structure of K Z must not change
+        c->kz_structure = nkz;
         if (!reuse) {
             // the restriction's column order: columns needing more rounds of its loads first,
             // launch order kept within each class (neighbouring columns share their gathers)
@@ -2036,11 +2096,19 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         for (size_t g = 0; g + 1 < gcut.size(); ++g) {
             const int g0 = gcut[g], g1 = gcut[g + 1];
             if (gcut.size() > 2) prepare(g0, g1, false);  // one group: the count pass left it ready
-            hipLaunchKernelGGL(k_kzb_rank, dim3(max_slices(g0, g1), g1 - g0), dim3(256), 0, s, bt_d + g0, mk, soff,
-                               icnt, kzp, items);
+            const dim3 gs(max_slices(g0, g1), g1 - g0);
+            hipLaunchKernelGGL(k_kzb_items, gs, dim3(256), 0, s, bt_d + g0, mk, icnt, items);
             hipLaunchKernelGGL(k_kzb_values, dim3(512, g1 - g0), dim3(256),
                                0, s, bt_d + g0, nitems + g0, items, c->brow_ptr, c->bcol, c->bval, zd, rbits, zp, zc,
-                               c->kzt_idx, c->kzt_val, kd, words, touched);
+                               kd, km, ends + g0, words, touched);
+            // the kept entries' places (those of later groups' vectors come after them)
+            hipLaunchKernelGGL(k_kzb_count, gs, dim3(256), 0, s, bt_d + g0, mk, (const uint32_t *)km, scnt, tcnt,
+                               (uint32_t *)nullptr);
+            hipLaunchKernelGGL(k_kzb_offsets, dim3(g1 - g0), dim3(kBatch + 1), 0, s, bt_d + g0, g1 - g0, scnt, tcnt,
+                               soff, kzcnt, icnt, nitems + g0);
+            HT(scan(s, kzcnt, k, kzp, part));
+            hipLaunchKernelGGL(k_kzb_store, gs, dim3(256), 0, s, bt_d + g0, mk, km, soff, kzp, kd, c->kzt_idx,
+                               c->kzt_val);
             hipLaunchKernelGGL(k_kzb_erows, dim3((k + 3) / 4, g1 - g0), dim3(256), 0, s, bt_d + g0, k, ztp, zti, ztv,
                                kd, mk, touched, eraw, ld);
         }
@@ -2074,14 +2142,17 @@ int coarse_operator(dpcg_ctx *c, Pool &pool, int32_t k, const int64_t *zp, const
         hipLaunchKernelGGL(k_einv_from_lower, dim3((unsigned)coarse_tile_count(cnt)), dim3(256), 0, s, k, ld,
                            (const double *)esc, (const double *)ga, c->einv, c->einv_tiles);
         HT(hipGetLastError());
+        if (!reuse) HT(keep(c, &c->kzt_ptr, k + 1));
+        hipLaunchKernelGGL(k_to_i32, dim3(grid_for(k + 1)), dim3(256), 0, s, kzp, (int64_t)k + 1, c->kzt_ptr);
+        HT(hipMemcpyAsync(nkzp, kzp + k, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        if (c->bws) c->bws->stale = true;  // its restriction lists follow (KZ)^T's pattern
         if (!reuse) {
-            HT(keep(c, &c->kzt_ptr, k + 1));
-            hipLaunchKernelGGL(k_to_i32, dim3(grid_for(k + 1)), dim3(256), 0, s, kzp, (int64_t)k + 1, c->kzt_ptr);
             HT(keep(c, &c->rs_order, k));
             HT(hipMemcpyAsync(c->rs_order, c->rs_order_h.data(), sizeof(int32_t) * k, hipMemcpyHostToDevice, s));
         }
         HT(hipMemcpyAsync(fl + 4, cfail, sizeof(int), hipMemcpyDeviceToHost, s));
         HT(hipStreamSynchronize(s));
+        c->nnz_kz = *nkzp;
         if (fl[4]) return DPCG_ECOARSE_NOT_SPD;
         return DPCG_OK;
     }

@@ -122,3 +122,31 @@ def test_batch_widths(problems, nrhs):
         U, infos = s.solve_batch(torch.as_tensor(C @ X, device=DEV), tol=1e-13)
     err = np.linalg.norm(U.cpu().numpy() - X, axis=0)
     assert all(i["status"] == 0 for i in infos) and np.all(err <= 1e-11 * np.linalg.norm(X, axis=0))
+
+
+def test_kept_entries_of_kz(problems):
+    """(K Z)^T without the entries that are only rounding: g = Z^T a - (K Z)^T b against scipy
+    within the rounding of the sums, fewer stored than structural entries, and another set after
+    a values update (springs to the ground make K Z dense, without them it is sparse again), in
+    single and batched solves of the same handle."""
+    p = problems("penny12")
+    K, Z = p.K_scipy().tocsr(), p.Z_scipy().tocsr()
+    G = K.copy()
+    G.setdiag(1.1 * K.diagonal())
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    rng = np.random.default_rng(5)
+    a, b, X = rng.standard_normal(p.n), rng.standard_normal(p.n), rng.standard_normal((p.n, 5))
+    kept = []
+    with D.Solver.from_problem(p, DEV) as s:
+        for M in (K, G, K):
+            s.update_values(t(M.indptr, torch.int64), t(M.indices, torch.int32), t(M.data, torch.float64))
+            kept.append(s.stats()["nnz_kz"])
+            g = s.restrict(t(a, torch.float64), t(b, torch.float64)).cpu().numpy()
+            scale = abs(Z).T @ np.abs(a) + abs(Z).T @ (abs(M) @ np.abs(b))
+            assert np.all(np.abs(g - (Z.T @ a - Z.T @ (M @ b))) <= 1e-13 * scale)
+            U, infos = s.solve_batch(t(M @ X, torch.float64), tol=1e-12)
+            for j in range(X.shape[1]):
+                u, info = s.solve(t((M @ X)[:, j], torch.float64), tol=1e-12)
+                assert info["status"] == 0 and infos[j]["status"] == 0
+                assert torch.linalg.norm(U[:, j] - u) <= 1e-8 * torch.linalg.norm(u)
+    assert kept[0] == kept[2] < 0.9 * kept[1]
