@@ -899,31 +899,49 @@ __global__ __launch_bounds__(256) void k_kzb_mark(const KzBatch *__restrict__ bt
 __global__ __launch_bounds__(256) void k_kzb_count(const KzBatch *__restrict__ bt, const uint32_t *__restrict__ mk,
                                                    const uint32_t *__restrict__ km, int32_t *__restrict__ cnt,
                                                    int32_t *__restrict__ tcnt, uint32_t *__restrict__ ends) {
-    __shared__ int32_t c_s[kBatch + 1];
+    __shared__ int32_t c_s[4][kBatch + 1];
     __shared__ uint32_t e_s;
     const KzBatch B = bt[blockIdx.y];
     if (blockIdx.x >= B.nslice) return;
-    if (threadIdx.x <= kBatch) c_s[threadIdx.x] = 0;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (threadIdx.x == 0) e_s = 0u;
-    __syncthreads();
-    uint32_t differ = 0u;
-    const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = min<int64_t>(B.w3, t0 + kSlice);
-    int32_t mine[kBatch + 1];
-    for (int b = 0; b <= kBatch; ++b) mine[b] = 0;
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += 256) {
-        uint32_t m = mk[B.moff + t];
-        if (km) m = m ? km[B.moff + t] : 0u;
-        differ |= m ^ (m >> 1);
-        for (int b = 0; b < kBatch; ++b) mine[b] += 3 * ((m >> b) & 1u);
-        mine[kBatch] += m != 0u;
+    const int64_t t0 = (int64_t)blockIdx.x * kSlice;
+    uint32_t m[kSlice / 256], differ = 0u;
+#pragma unroll
+    for (int r = 0; r < kSlice / 256; ++r) {
+        const int64_t t = t0 + 256 * r + threadIdx.x;
+        m[r] = t < B.w3 ? mk[B.moff + t] : 0u;
     }
-    for (int b = 0; b <= kBatch; ++b)
-        if (mine[b]) atomicAdd(&c_s[b], mine[b]);
-    if (!km && differ) atomicOr(&e_s, differ);
+    if (km) {
+#pragma unroll
+        for (int r = 0; r < kSlice / 256; ++r)
+            if (m[r]) m[r] = km[B.moff + t0 + 256 * r + threadIdx.x];
+    }
+    // a wave's counts by ballots, lane b taking vector b's and lane kBatch the triplets':
+    // 6 us over the 3 x 23^3 problem, 37 with seventeen LDS adds per thread
+    int32_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < kSlice / 256; ++r) {
+        differ |= m[r] ^ (m[r] >> 1);
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            const int n = __popcll(__ballot((m[r] >> b) & 1u));
+            mine += lane == b ? 3 * n : 0;
+        }
+        const int n = __popcll(__ballot(m[r] != 0u));
+        mine += lane == kBatch ? n : 0;
+    }
+    if (lane <= kBatch) c_s[wv][lane] = mine;
     __syncthreads();
-    if (!km && threadIdx.x == 0 && e_s) atomicOr(&ends[blockIdx.y], e_s);
-    if (threadIdx.x < kBatch) cnt[(B.slice0 + blockIdx.x) * kBatch + threadIdx.x] = c_s[threadIdx.x];
-    if (threadIdx.x == kBatch) tcnt[B.slice0 + blockIdx.x] = c_s[kBatch];
+    if (!km && differ) atomicOr(&e_s, differ);
+    if (threadIdx.x <= kBatch) {
+        const int32_t n = (c_s[0][threadIdx.x] + c_s[1][threadIdx.x]) + (c_s[2][threadIdx.x] + c_s[3][threadIdx.x]);
+        if (threadIdx.x < kBatch) cnt[(B.slice0 + blockIdx.x) * kBatch + threadIdx.x] = n;
+        else tcnt[B.slice0 + blockIdx.x] = n;
+    }
+    if (km) return;
+    __syncthreads();
+    if (threadIdx.x == 0 && e_s) atomicOr(&ends[blockIdx.y], e_s);
 }
 
 // Per batch (kBatch + 1 threads): thread b < ncol forms the slice offsets within vector
@@ -1092,6 +1110,13 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
                         acc[2][b] = fma(v[6 + jj], zz, acc[2][b]);
                     }
             }
+            // the vectors of the triplet's three rows of Z, over the item's sixteen lanes: a
+            // chain of loads and adds on one lane took the kernel from 95 to 104 us (23^3)
+            const int64_t e1 = zp[3 * R + 3];
+            for (int64_t e = zp[3 * R] + (threadIdx.x & 15); e < e1; e += 16) {
+                const int32_t col = zc[e];
+                atomicOr(&tb[col / 32], 1u << (col % 32));
+            }
         }
         for (int i = 0; i < 3; ++i)
             for (int b = 0; b < 4; ++b) {
@@ -1122,12 +1147,6 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
         double *o = kd + (3 * (B.off3 + t)) * kBatch + 4 * sub;
         for (int i = 0; i < 3; ++i)
             for (int b = 0; b < 4; ++b) o[i * kBatch + b] = acc[i][b];
-        if (sub == 0)
-            for (int i = 0; i < 3; ++i)
-                for (int64_t e = zp[3 * R + i]; e < zp[3 * R + i + 1]; ++e) {
-                    const int32_t col = zc[e];
-                    atomicOr(&tb[col / 32], 1u << (col % 32));
-                }
     }
     if (!lds_bits) return;
     __syncthreads();
