@@ -200,9 +200,9 @@ __device__ __forceinline__ double block_row_span(int row, int beg, int end, int 
     return row_scatter<G>(lg, a0, a1, a2);
 }
 
-template <int G, class XL, class V>
+template <int G, class XL, class V, class CI>
 __device__ __forceinline__ double block_row(int row, int lg, const int32_t *__restrict__ brow_ptr,
-                                            const int32_t *__restrict__ bcol, const V *__restrict__ bval,
+                                            const CI *__restrict__ bcol, const V *__restrict__ bval,
                                             int64_t nnzb, const XL &xl) {
     int beg = 0, end = 0;
     if (row >= 0) {
@@ -246,9 +246,9 @@ __device__ __forceinline__ int step_row(int s, int nb) {
 }
 
 // MODE 0: y = K x.   MODE 1: r = f - K x and ||r||^2 partials.
-template <int G, int MODE, class V>
+template <int G, int MODE, class V, class CI>
 __device__ __forceinline__ void k_spmv_body(int vb, SpmvShape sh, const int32_t *__restrict__ brow_ptr,
-                                                   const int32_t *__restrict__ bcol,
+                                                   const CI *__restrict__ bcol,
                                                    const V *__restrict__ bval, int64_t nnzb,
                                                    const double *__restrict__ x, const double *__restrict__ f,
                                                    double *__restrict__ y, double *__restrict__ part) {
@@ -280,13 +280,13 @@ __device__ __forceinline__ void k_spmv_body(int vb, SpmvShape sh, const int32_t 
     }
 }
 
-template <int G, int MODE, class V>
+template <int G, int MODE, class V, class CI>
 __global__ __launch_bounds__(kSpmvThreads) void k_spmv(SpmvShape sh, const int32_t *__restrict__ brow_ptr,
-                                                   const int32_t *__restrict__ bcol,
+                                                   const CI *__restrict__ bcol,
                                                    const V *__restrict__ bval, int64_t nnzb,
                                                    const double *__restrict__ x, const double *__restrict__ f,
                                                    double *__restrict__ y, double *__restrict__ part) {
-    k_spmv_body<G, MODE, V>(blockIdx.x, sh, brow_ptr, bcol, bval, nnzb, x, f, y, part);
+    k_spmv_body<G, MODE>(blockIdx.x, sh, brow_ptr, bcol, bval, nnzb, x, f, y, part);
 }
 
 
@@ -1178,16 +1178,24 @@ hipError_t spmv_p_g(const dpcg_ctx *c, Workspace &w, hipEvent_t ev0, hipEvent_t 
     return hipGetLastError();
 }
 
+template <int G, int MODE, class V>
+hipError_t spmv_v(const dpcg_ctx *c, const V *bval, const double *x, const double *f, double *y, double *part) {
+    SpmvShape sh{c->nb, c->spmv.steps, c->spmv.nwg};
+    // 16-bit row offsets when the handle has them, as in spmv_p_g (80^3 elements with
+    // a penny crack, FP64: 248 us on the device with 32-bit columns, 239 with these)
+    if (c->bcol16)
+        hipLaunchKernelGGL((k_spmv<G, MODE, V, int16_t>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream, sh,
+                           c->brow_ptr, (const int16_t *)c->bcol16, bval, c->nnzb, x, f, y, part);
+    else
+        hipLaunchKernelGGL((k_spmv<G, MODE, V, int32_t>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream, sh,
+                           c->brow_ptr, (const int32_t *)c->bcol, bval, c->nnzb, x, f, y, part);
+    return hipGetLastError();
+}
+
 template <int G, int MODE>
 hipError_t spmv_g(const dpcg_ctx *c, const double *x, const double *f, double *y, double *part) {
-    SpmvShape sh{c->nb, c->spmv.steps, c->spmv.nwg};
-    if (c->inner32)
-        hipLaunchKernelGGL((k_spmv<G, MODE, float>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream, sh,
-                           c->brow_ptr, c->bcol, (const float *)c->bval32, c->nnzb, x, f, y, part);
-    else
-        hipLaunchKernelGGL((k_spmv<G, MODE, double>), dim3(c->spmv.nwg), dim3(kSpmvThreads), 0, c->stream, sh,
-                           c->brow_ptr, c->bcol, (const double *)c->bval, c->nnzb, x, f, y, part);
-    return hipGetLastError();
+    return c->inner32 ? spmv_v<G, MODE>(c, (const float *)c->bval32, x, f, y, part)
+                      : spmv_v<G, MODE>(c, (const double *)c->bval, x, f, y, part);
 }
 
 __global__ void k_to_f32(const double *__restrict__ src, int64_t count, float *__restrict__ dst) {
@@ -1226,6 +1234,16 @@ __device__ __forceinline__ void ms_spmv_p(int vb, const SpmvShape &sh, const MsS
     }
 }
 
+template <class CI>
+__device__ __forceinline__ void ms_residual(int vb, const SpmvShape &sh, const MsSys &S, const CI *bcol) {
+    switch (S.group) {
+        case 4: k_spmv_body<4, 1>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
+        case 8: k_spmv_body<8, 1>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
+        case 16: k_spmv_body<16, 1>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
+        default: k_spmv_body<32, 1>(vb, sh, S.brow_ptr, bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
+    }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(kSpmvThreads) void k_ms_spmv(const MsTable *__restrict__ tab,
                                                           const MsSys *__restrict__ sys) {
@@ -1238,12 +1256,8 @@ __global__ __launch_bounds__(kSpmvThreads) void k_ms_spmv(const MsTable *__restr
         else ms_spmv_p(vb, sh, S, S.bcol);
     } else {
         if (S.st->flag != kRunning) return;
-        switch (S.group) {
-            case 4: k_spmv_body<4, 1, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
-            case 8: k_spmv_body<8, 1, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
-            case 16: k_spmv_body<16, 1, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
-            default: k_spmv_body<32, 1, double>(vb, sh, S.brow_ptr, S.bcol, S.bval, S.nnzb, S.u, S.f, S.r, S.part_b); break;
-        }
+        if (S.bcol16) ms_residual(vb, sh, S, S.bcol16);
+        else ms_residual(vb, sh, S, S.bcol);
     }
 }
 
