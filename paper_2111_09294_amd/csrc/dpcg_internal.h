@@ -37,11 +37,13 @@ constexpr int kDenseStrip = 8;    // tiles of one tile row per wave of its apply
 constexpr int kMaxElemDofs = 256; // largest element (DoFs) of dpcg_element_gradient
 constexpr int kCoarseTile = 64;   // E^-1 kept as the lower-triangle tiles of this size
 constexpr int kAlphaParts = 64;   // workgroups of the first stage of p^T q
-// Up to this many p^T q partials the update's workgroups add them all themselves (eight
-// loads per thread, in flight with the tile's own: the update takes the same 4.9 us at 23^3
-// and the first stage's 2.7 us and launch go); above, where every workgroup would read more
-// than 16 KB for the sum, the first stage makes kAlphaParts.
-constexpr int kFoldParts = 2048;
+// Up to this many p^T q partials the update's workgroups add them all themselves (two, eight
+// or eighteen loads per thread, in flight with the tile's own: the update takes the same
+// 4.9 us at 23^3 and the first stage's 2.7 us and launch go); above, where every workgroup
+// would read more than 36 KB for the sum, the first stage makes kAlphaParts.  Against a
+// line at 2048: 3700 partials (30^3) 13.77 -> 13.41 ms per update and solve, nine systems of
+// 450 to 2500 15.3 -> 14.95 ms; at 8900 (40^3) folding costs (9.6 -> 10.5 ms).
+constexpr int kFoldParts = 4608;
 __host__ __device__ inline bool fold_alpha(int32_t parts) { return parts <= kFoldParts; }
 constexpr int kRestrictRound = 4096;  // list entries per round of the restriction's loads (threads x depth)
 

@@ -502,10 +502,13 @@ __device__ __forceinline__ void k_update_bj_body(int vb,
         d1 = tile_start[t0 + 1];
     }
     // up to kAlphaParts sums (the first stage's), one per lane of every wave, or the SpMV's
-    // own partials over the workgroup's threads
+    // own partials over the workgroup's threads, in one round of as few loads as cover them
     const bool folded = n_pq > kAlphaParts;
-    double pq = folded ? masked_share<kThreads, kFoldParts / kThreads>(part_pq, n_pq)
-                       : ((t & 63) < n_pq ? part_pq[t & 63] : 0.0);
+    double pq = 0.0;
+    if (!folded) pq = (t & 63) < n_pq ? part_pq[t & 63] : 0.0;
+    else if (n_pq <= 2 * kThreads) pq = masked_share<kThreads, 2>(part_pq, n_pq);
+    else if (n_pq <= 8 * kThreads) pq = masked_share<kThreads, 8>(part_pq, n_pq);
+    else pq = masked_share<kThreads, kFoldParts / kThreads>(part_pq, n_pq);
     const int32_t flag = st->flag, it = st->iter;
     const double rho0 = st->rho[0], rho1 = st->rho[1];
     const double *p = (it & 1) ? p1 : p0;

@@ -65,11 +65,12 @@ def test_coarse_product_forms(k):
     assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
 
 
-@pytest.mark.parametrize("nb", [1, 85, 86, 4096, 4097, 131072, 131073])
+@pytest.mark.parametrize("nb", [1, 85, 86, 4096, 4097, 32768, 32769, 131072, 131073, 294912, 294913])
 def test_step_length_partials(nb):
-    """p^T q from up to 64 partials, from the SpMV's own up to 2048 (64 block rows each), and
-    through a first stage above; 85 block rows fill one tile of the update, 86 start another.
-    Blocks of 6 unknowns, the last one of 3 where nb is odd."""
+    """p^T q from up to 64 partials, from the SpMV's own up to 4608 (64 block rows each; in
+    rounds of at most 512, 2048 and 4608), and through a first stage above; 85 block rows
+    fill one tile of the update, 86 start another.  Blocks of 6 unknowns, the last one of 3
+    where nb is odd."""
     K = chain(nb)
     x = np.random.default_rng(3).standard_normal(3 * nb)
     with solver(K, [0] if nb > 1 else [], block=6) as s:
