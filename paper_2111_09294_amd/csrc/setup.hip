@@ -1253,6 +1253,7 @@ __global__ void k_symmetrise(int32_t k, int64_t ld, const double *__restrict__ e
 }
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
+typedef double dbl2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------- symmetric sweeps
 // The coarse matrix and the dense block-Jacobi blocks are symmetric positive definite, so
@@ -1273,7 +1274,8 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // so each lower tile costs one 64 x 64 x 64 product on the matrix cores, and a sweep
 // reads and writes the lower triangle once: a quarter of the work of the full 32-wide
 // sweeps over every tile.  The panel kernel stores T and the column panel C_I = A_Ip in
-// buffers of their own, so the sweep updates the matrix in place.  In a numpy model on
+// buffers of their own, so the sweep updates the matrix in place.  (The dense blocks, whose
+// sweeps are bound by that traffic and not by the chain of pivot inverses, run two at a time.)  In a numpy model on
 // the Jacobi-scaled coarse matrices of the 40^3 and 80^3 workloads this form leaves
 // max |I - E E^-1| at the level of the full 32-wide sweeps (80^3: 2.6e-3 against 2.9e-3).
 constexpr int kCb = 64;
@@ -1434,6 +1436,29 @@ __device__ __forceinline__ void cb_mfma(const double *X, const double *Y, dbl4 (
     }
 }
 
+// acc += X^T Y for 64 x 64 tiles X, Y in memory, both with the summed index first, in
+// cb_mfma's split with the rows and the columns of a quadrant's two 16-wide blocks
+// interleaved: a lane's operands, like its results, are pairs of neighbours, read from memory
+// 256 contiguous bytes per 16 lanes without LDS.
+__device__ __forceinline__ int fma_row(int b, int v) {
+    return ((threadIdx.x >> 6) >> 1) * 32 + 2 * (((threadIdx.x & 63) >> 4) + 4 * v) + (b >> 1);
+}
+__device__ __forceinline__ int fma_col(int b) { return ((threadIdx.x >> 6) & 1) * 32 + 2 * (threadIdx.x & 15) + (b & 1); }
+
+__device__ __forceinline__ void cb_fma(const double *__restrict__ X, const double *__restrict__ Y, dbl4 (&acc)[4]) {
+    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, kq = l >> 4;
+    X += kq * kCb + (wv >> 1) * 32 + 2 * (l & 15);
+    Y += kq * kCb + (wv & 1) * 32 + 2 * (l & 15);
+#pragma unroll 2
+    for (int s4 = 0; s4 < kCb; s4 += 4) {
+        const dbl2 x = *(const dbl2 *)(X + s4 * kCb), y = *(const dbl2 *)(Y + s4 * kCb);
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.y, acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.x, acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.y, acc[3], 0, 0, 0);
+    }
+}
+
 // The lower tiles (I, J), I >= J, of a matrix under inversion: row-major ld x ld (the coarse
 // matrix) or packed tile after tile (a dense block).
 struct RowTiles {
@@ -1503,16 +1528,16 @@ __global__ __launch_bounds__(256) void k_cgj_first_pivot(double *A, int64_t ld, 
 // for J > p the transpose of the stored (J, p), sign +1), T_J = P A_pJ into tbuf[J], and
 // the column tile A_Jp = s A_pJ^T into cbuf[J] (s = +1 for J > p, -1 for J < p: block row
 // J is swept, block row p not yet).  Both buffers hold nt tiles of 64 x 64, row-major.
-template <class M>
-__device__ __forceinline__ void panel_body(int p, int J, const M &mat, const double *__restrict__ P,
-                                           double *__restrict__ cbuf, double *__restrict__ tbuf) {
+__global__ __launch_bounds__(256) void k_cgj_panel(int p, double *A0, int64_t ld, const double *__restrict__ P,
+                                                   double *__restrict__ cbuf, double *__restrict__ tbuf) {
+    const int J = blockIdx.x;
     __shared__ double S[kCb * kCbLd], Y[kCb * kCbLd];
     if (J == p) return;
     // all loads (coalesced, row-major) before the first LDS store: P, and the stored
     // tile (p, J) for J < p or (J, p) for J > p, which is A_pJ transposed
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
+    const RowTiles mat{A0, ld};
     const double *A = J < p ? mat.tile(p, J) : mat.tile(J, p);
-    const int64_t ld = mat.stride();
     double pv[16], yv[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
@@ -1544,21 +1569,20 @@ __device__ __forceinline__ void panel_body(int p, int J, const M &mat, const dou
         for (int v = 0; v < 4; ++v) tj[cb_row(b, v) * kCb + cb_col(b)] = acc[b][v];
 }
 
-__global__ __launch_bounds__(256) void k_cgj_panel(int p, double *A, int64_t ld, const double *__restrict__ P,
-                                                   double *__restrict__ cbuf, double *__restrict__ tbuf) {
-    panel_body(p, blockIdx.x, RowTiles{A, ld}, P, cbuf, tbuf);
-}
-
-// Sweep p of lower tile (I, J), in place.  The workgroup of the next pivot tile (p + 1, p + 1)
-// also inverts it into Pnext (P and Pnext are distinct buffers).
-template <class M>
-__device__ __forceinline__ void sweep_body(int p, int I, int J, const M &mat, int32_t kdim,
-                                           const double *__restrict__ P, double *__restrict__ Pnext,
-                                           const double *__restrict__ cbuf, const double *__restrict__ tbuf,
-                                           const double *__restrict__ diag0, int *fail, int failval) {
+// Sweep p of the lower tiles, in place, one workgroup each.  The workgroup of the next pivot
+// tile (p + 1, p + 1) also inverts it into Pnext (P and Pnext are distinct buffers).  The
+// tiles, numbered row by row, are rotated so that this one is dispatched first: its inverse is
+// the critical path of the sweep, overlapped with the other tiles.
+__global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *A0, int64_t ld, int32_t kdim,
+                                                   const double *__restrict__ P, double *__restrict__ Pnext,
+                                                   const double *__restrict__ cbuf, const double *__restrict__ tbuf,
+                                                   const double *__restrict__ diag0, int *fail) {
     __shared__ double X[kCb * kCbLd], Y[kCb * kCbLd];
-    double *A = mat.tile(I, J);
-    const int64_t ld = mat.stride();
+    const int64_t ntl = (int64_t)nt * (nt + 1) / 2;
+    const int64_t first = p + 1 < nt ? (int64_t)(p + 1) * (p + 2) / 2 + (p + 1) : 0;
+    int I, J;
+    lower_tile((blockIdx.x + first) % ntl, I, J);
+    double *A = RowTiles{A0, ld}.tile(I, J);
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     if (I == p || J == p) {
         // pivot tile P; row p: T_J; column p: -T_I^T (transposed through LDS)
@@ -1624,21 +1648,8 @@ __device__ __forceinline__ void sweep_body(int p, int I, int J, const M &mat, in
         const bool bad = pivot_inverse64(Y, diag0, (int64_t)I * kCb, kdim);
 #pragma unroll
         for (int q = 0; q < 16; ++q) Pnext[(ta + 4 * q) * kCb + tb] = Y[(ta + 4 * q) * kCbLd + tb];
-        if (bad && threadIdx.x == 0) pivot_failed(fail, failval);
+        if (bad && threadIdx.x == 0) pivot_failed(fail, -1);
     }
-}
-
-// The tiles, numbered row by row, are rotated so that the next pivot tile is dispatched first:
-// its inverse is the critical path of the sweep, overlapped with the other tiles.
-__global__ __launch_bounds__(256) void k_cgj_sweep(int p, int nt, double *A, int64_t ld, int32_t kdim,
-                                                   const double *__restrict__ P, double *__restrict__ Pnext,
-                                                   const double *__restrict__ cbuf, const double *__restrict__ tbuf,
-                                                   const double *__restrict__ diag0, int *fail) {
-    const int64_t ntl = (int64_t)nt * (nt + 1) / 2;
-    const int64_t first = p + 1 < nt ? (int64_t)(p + 1) * (p + 2) / 2 + (p + 1) : 0;
-    int I, J;
-    lower_tile((blockIdx.x + first) % ntl, I, J);
-    sweep_body(p, I, J, RowTiles{A, ld}, kdim, P, Pnext, cbuf, tbuf, diag0, fail, -1);
 }
 
 // The final E^-1 from the lower tiles of the inverse X of the scaled matrix: F = S X S,
@@ -1759,6 +1770,28 @@ __global__ __launch_bounds__(256) void k_dense_gather(const GjMat *__restrict__ 
     }
 }
 
+// The dense blocks take two pivot tiles p and q = p + 1 at a time (one where a matrix ends):
+// a sweep reads and writes every tile once, so two in one pass halve that traffic.  With
+// L = A_qp, the second sweep's rows are formed from the first's,
+//   P = A_pp^-1,  T1_J = P A_pJ,  B_qJ = A_qJ - L T1_J,  P' = B_qq^-1,  T2_J = P' B_qJ,
+// B_qp being -L P, and a tile's update is the two products together,
+//   B_IJ = A_IJ - A_Ip T1_J - B_Iq T2_J;
+// in row p it starts from T1_J, in column p from -T1_I^T, in the pivot tile from P, all without
+// the first product; row q is T2_J, column q -T2_I^T, its pivot tile P'.  The column tiles
+// A_Ip and B_Iq are signed transposes of row tiles, so -s A_pI and -s B_qI are kept (s = +1
+// for I > p, else -1): the summed index first, as cb_fma reads them.
+struct GjBufs {
+    double *c1, *t1, *c2, *t2;  // a matrix's tiles: -s A_pJ, T1_J, -s B_qJ, T2_J
+};
+__device__ __forceinline__ GjBufs gj_bufs(const GjMat &G, double *cbuf, double *tbuf) {
+    const int64_t o = 2 * G.row0 * (kCb * kCb), n = (int64_t)G.nt * (kCb * kCb);
+    return {cbuf + o, tbuf + o, cbuf + o + n, tbuf + o + n};
+}
+// P of pivot tile p (i = 0) or P' (i = 1): two pairs per matrix, used in turn
+__device__ __forceinline__ double *gj_pivot(double *P, int mi, int p, int i) {
+    return P + ((int64_t)mi * 4 + (p & 2) + i) * (kCb * kCb);
+}
+
 __global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict__ mats, int count, double *W,
                                                          const double *__restrict__ diag0, double *__restrict__ P,
                                                          int *fail) {
@@ -1766,41 +1799,263 @@ __global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict
         const GjMat G = mats[mi];
         __syncthreads();
         first_pivot_body(PackedTiles{W + G.tile0 * (kCb * kCb)}, G.size, diag0 + G.row0 * kCb,
-                         P + (int64_t)mi * 2 * kCb * kCb, fail, G.block);
+                         gj_pivot(P, mi, 0, 0), fail, G.block);
     }
 }
 
-// panels and sweep p over the first count matrices (those with more than p pivot tiles)
-__global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restrict__ mats, int count, double *W,
-                                                   const double *__restrict__ P, double *__restrict__ cbuf,
-                                                   double *__restrict__ tbuf) {
-    const int mi = gj_find<&GjMat::row0>(mats, count, blockIdx.x);
-    const GjMat G = mats[mi];
-    panel_body(p, (int)(blockIdx.x - G.row0), PackedTiles{W + G.tile0 * (kCb * kCb)},
-               P + ((int64_t)mi * 2 + (p & 1)) * (kCb * kCb), cbuf + G.row0 * (kCb * kCb), tbuf + G.row0 * (kCb * kCb));
+__device__ __forceinline__ void cb_to_lds(const dbl4 (&acc)[4], double *S) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) S[cb_row(b, v) * kCbLd + cb_col(b)] = acc[b][v];
 }
 
-// The first count workgroups take the matrices' next pivot tiles (the longest ones), the
-// others every other tile.
-__global__ __launch_bounds__(256) void k_gjb_sweep(int p, const GjMat *__restrict__ mats, int count, double *W,
-                                                   double *P, const double *__restrict__ cbuf,
-                                                   const double *__restrict__ tbuf, const double *__restrict__ diag0,
-                                                   int *fail) {
+// S becomes the symmetric matrix of its lower half
+__device__ __forceinline__ void mirror_lower(double *S) {
+    const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;
+    double v[16];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int a = ta + 4 * q;
+        v[q] = a >= tb ? S[a * kCbLd + tb] : S[tb * kCbLd + a];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = v[q];
+    __syncthreads();
+}
+
+// P' of the first count matrices (those with a pivot tile p + 1)
+__global__ __launch_bounds__(256) void k_gjb_pivot2(int p, const GjMat *__restrict__ mats, int count,
+                                                    const double *__restrict__ W, double *Pm,
+                                                    const double *__restrict__ diag0, int *fail) {
+    __shared__ double S[kCb * kCbLd], Y[kCb * kCbLd];
+    const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
+    for (int mi = blockIdx.x; mi < count; mi += gridDim.x) {
+        const GjMat G = mats[mi];
+        const double *A = W + G.tile0 * (kCb * kCb);
+        const int64_t row = (int64_t)(p + 1) * (p + 2) / 2;
+        const double *L = A + (row + p) * (kCb * kCb), *Aqq = L + kCb * kCb;
+        const double *P = gj_pivot(Pm, mi, p, 0);
+        double *P2 = gj_pivot(Pm, mi, p, 1);
+        double lv[16], sr[16];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            lv[q] = L[(ta + 4 * q) * kCb + tb];
+            S[(ta + 4 * q) * kCbLd + tb] = P[(ta + 4 * q) * kCb + tb];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Y[tb * kCbLd + ta + 4 * q] = lv[q];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sr[4 * b + v] = Aqq[cb_row(b, v) * kCb + cb_col(b)];
+        __syncthreads();
+        dbl4 acc[4];
+        cb_mfma(S, Y, acc);  // P L^T
+        __syncthreads();
+        cb_to_lds(acc, Y);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = lv[q];
+        __syncthreads();
+        cb_mfma(S, Y, acc);
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[b][v] = sr[4 * b + v] - acc[b][v];
+        cb_to_lds(acc, S);
+        mirror_lower(S);
+        const bool bad = pivot_inverse64(S, diag0 + G.row0 * kCb, (int64_t)(p + 1) * kCb, G.size);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) P2[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
+        if (bad && threadIdx.x == 0) pivot_failed(fail, G.block);
+    }
+}
+
+// Row tiles J of the pivot tiles p and p + 1, one workgroup each, over the first count
+// matrices (those with more than p pivot tiles)
+__global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restrict__ mats, int count,
+                                                   const double *__restrict__ W, double *Pm, double *cbuf,
+                                                   double *tbuf) {
+    __shared__ double S[kCb * kCbLd], Y[kCb * kCbLd];
+    const int mi = gj_find<&GjMat::row0>(mats, count, blockIdx.x);
+    const GjMat G = mats[mi];
+    const int J = (int)(blockIdx.x - G.row0);
+    const bool two = p + 1 < G.nt;
+    if (two ? J == p + 1 : J == p) return;
+    const PackedTiles T{const_cast<double *>(W) + G.tile0 * (kCb * kCb)};
+    const GjBufs B = gj_bufs(G, cbuf, tbuf);
+    const double *P = gj_pivot(Pm, mi, p, 0), *P2 = gj_pivot(Pm, mi, p, 1), *L = T.tile(p + 1, p);
+    const int64_t o = (int64_t)J * (kCb * kCb);
+    const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
+    const double s = J > p ? 1.0 : -1.0;
+    // all loads (coalesced, row-major) before the first LDS store: P, the stored tile (p, J)
+    // or (J, p), the latter A_pJ transposed, and the same of row p + 1 with L
+    double pv[16], yv[16], lv[16], wv2[16];
+    const double *A1 = J < p ? T.tile(p, J) : T.tile(J, p), *A2 = J < p ? T.tile(p + 1, J) : T.tile(J, p + 1);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int e = (ta + 4 * q) * kCb + tb;
+        pv[q] = P[e];
+        yv[q] = J != p ? A1[e] : 0.0;
+        lv[q] = two ? L[e] : 0.0;
+        wv2[q] = two && J != p ? A2[e] : 0.0;
+    }
+    dbl4 acc[4];
+    if (J != p) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int a = ta + 4 * q;
+            S[a * kCbLd + tb] = pv[q];
+            if (J < p) Y[a * kCbLd + tb] = yv[q];
+            else Y[tb * kCbLd + a] = yv[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int a = ta + 4 * q;
+            B.c1[o + a * kCb + tb] = -s * Y[a * kCbLd + tb];
+        }
+        cb_mfma(S, Y, acc);  // T1_J
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) B.t1[o + cb_row(b, v) * kCb + cb_col(b)] = acc[b][v];
+        if (!two) return;
+        __syncthreads();
+        cb_to_lds(acc, Y);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Y[(ta + 4 * q) * kCbLd + tb] = pv[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        S[(ta + 4 * q) * kCbLd + tb] = lv[q];
+        pv[q] = P2[(ta + 4 * q) * kCb + tb];
+    }
+    __syncthreads();
+    cb_mfma(S, Y, acc);  // L T1_J, or L P where J = p
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int a = ta + 4 * q;
+        if (J < p) S[a * kCbLd + tb] = wv2[q];
+        else S[tb * kCbLd + a] = wv2[q];  // zero where J = p
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double x = S[cb_row(b, v) * kCbLd + cb_col(b)] - acc[b][v];
+            Y[cb_row(b, v) * kCbLd + cb_col(b)] = x;
+            B.c2[o + cb_row(b, v) * kCb + cb_col(b)] = -s * x;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = pv[q];
+    __syncthreads();
+    cb_mfma(S, Y, acc);  // T2_J
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) B.t2[o + cb_row(b, v) * kCb + cb_col(b)] = acc[b][v];
+}
+
+// The first count workgroups take the matrices' next pivot tiles (the longest ones: they also
+// invert them), the others every other tile.  A tile is read and written once per two pivot
+// tiles, past the caches (the row and column tiles, which every tile's products read, stay
+// there), the products' operands come from memory and the four workgroups a CU holds hide it:
+// eight blocks of 4400 unknowns take 350 us a pair (operands staged through LDS, one pivot
+// tile a pass: 605; without the bound on registers 455; with cached tiles 367).  Matrix cores
+// and traffic alone would take 250 and 220.
+__global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__restrict__ mats, int count, double *W,
+                                                   double *Pm, double *cbuf, double *tbuf,
+                                                   const double *__restrict__ diag0, int *fail) {
+    __shared__ double S[kCb * kCbLd];
     const bool pivots = (int)blockIdx.x < count;
-    const int64_t t = (int64_t)blockIdx.x - count;
+    const int64_t t = pivots ? 0 : xcd_remap((int)blockIdx.x - count, (int)gridDim.x - count);
     const int mi = pivots ? (int)blockIdx.x : gj_find<&GjMat::tile0>(mats, count, t);
     const GjMat G = mats[mi];
-    int I = p + 1, J = p + 1;
+    int I = p + 2, J = p + 2;
     if (pivots) {
         if (I >= G.nt) return;
     } else {
         lower_tile(t - G.tile0, I, J);
-        if (I == p + 1 && J == p + 1) return;
+        if (I == p + 2 && J == p + 2) return;
     }
-    double *Pm = P + (int64_t)mi * 2 * (kCb * kCb);
-    sweep_body(p, I, J, PackedTiles{W + G.tile0 * (kCb * kCb)}, G.size, Pm + (p & 1) * (kCb * kCb),
-               Pm + ((p + 1) & 1) * (kCb * kCb), cbuf + G.row0 * (kCb * kCb), tbuf + G.row0 * (kCb * kCb),
-               diag0 + G.row0 * kCb, fail, G.block);
+    const bool two = p + 1 < G.nt;
+    double *A = PackedTiles{W + G.tile0 * (kCb * kCb)}.tile(I, J);
+    const GjBufs B = gj_bufs(G, cbuf, tbuf);
+    const int64_t oi = (int64_t)I * (kCb * kCb), oj = (int64_t)J * (kCb * kCb);
+    const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
+    const int last = two ? p + 1 : p;  // the pivot row and column with no product after it
+    if (I == last || J == last) {
+        // pivot tile; row: T_J; column: -T_I^T (transposed through LDS)
+        const double *tl = two ? B.t2 : B.t1;
+        const double *src = I == last && J == last ? gj_pivot(Pm, mi, p, two ? 1 : 0) : tl + (I == last ? oj : oi);
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = src[(ta + 4 * q) * kCb + tb];
+        if (J == last && I != last) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = v[q];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = -S[tb * kCbLd + ta + 4 * q];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) A[(ta + 4 * q) * kCb + tb] = v[q];
+        return;
+    }
+    const double *base = A;
+    if (I == p) base = J == p ? gj_pivot(Pm, mi, p, 0) : B.t1 + oj;
+    else if (J == p) base = B.t1 + oi;
+    const bool column = J == p && I != p;
+    dbl4 acc[4];
+    if (column || I == J) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int a = fma_row(b, v), c = fma_col(b);
+                // a diagonal tile's lower half
+                const double x = base[column || a < c ? c * kCb + a : a * kCb + c];
+                acc[b][v] = column ? -x : x;
+            }
+    } else {
+#pragma unroll
+        for (int b = 0; b < 4; b += 2)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const dbl2 x = __builtin_nontemporal_load((const dbl2 *)(base + fma_row(b, v) * kCb + fma_col(b)));
+                acc[b][v] = x.x;
+                acc[b + 1][v] = x.y;
+            }
+    }
+    if (I != p && J != p) cb_fma(B.c1 + oi, B.t1 + oj, acc);
+    if (two) cb_fma(B.c2 + oi, B.t2 + oj, acc);
+#pragma unroll
+    for (int b = 0; b < 4; b += 2)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            __builtin_nontemporal_store(dbl2{acc[b][v], acc[b + 1][v]},
+                                        (dbl2 *)(A + fma_row(b, v) * kCb + fma_col(b)));
+    if (pivots) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[fma_row(b, v) * kCbLd + fma_col(b)] = acc[b][v];
+        mirror_lower(S);
+        const bool bad = pivot_inverse64(S, diag0 + G.row0 * kCb, (int64_t)I * kCb, G.size);
+        double *Pn = gj_pivot(Pm, mi, p + 2, 0);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Pn[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
+        if (bad && threadIdx.x == 0) pivot_failed(fail, G.block);
+    }
 }
 
 // The inverse S X S (S the scale) from X's lower triangle, as the apply reads it: lower tiles
@@ -2204,9 +2459,9 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     HT(pool.tmp(&W, tiles[count] * kTile));
     HT(pool.tmp(&diag0, rows[count] * kCb));
     HT(pool.tmp(&scale, rows[count] * kCb));
-    HT(pool.tmp(&pv, (int64_t)count * 2 * kTile));
-    HT(pool.tmp(&cbuf, rows[count] * kTile));
-    HT(pool.tmp(&tbuf, rows[count] * kTile));
+    HT(pool.tmp(&pv, (int64_t)count * 4 * kTile));
+    HT(pool.tmp(&cbuf, 2 * rows[count] * kTile));
+    HT(pool.tmp(&tbuf, 2 * rows[count] * kTile));
     HT(hipMemcpyAsync(md, m.data(), sizeof(GjMat) * count, hipMemcpyHostToDevice, s));
     HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[count] * kCb, s));
     HT(hipMemsetAsync(W, 0, sizeof(double) * tiles[count] * kTile, s));
@@ -2215,9 +2470,13 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     hipLaunchKernelGGL(k_dense_scale, rgrid, dim3(256), 0, s, md, count, kp, kc, kv, scale);
     hipLaunchKernelGGL(k_dense_gather, rgrid, dim3(256), 0, s, md, count, kp, kc, kv, scale, W, diag0);
     hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, count, W, diag0, pv, bad_flag);
-    int active = count;
-    for (int p = 0; p < m[0].nt; ++p) {
+    int active = count, active2 = count;
+    for (int p = 0; p < m[0].nt; p += 2) {
         while (active > 0 && m[active - 1].nt <= p) --active;
+        while (active2 > 0 && m[active2 - 1].nt <= p + 1) --active2;
+        if (active2 > 0)
+            hipLaunchKernelGGL(k_gjb_pivot2, dim3(std::min(active2, 65535)), dim3(256), 0, s, p, md, active2, W, pv,
+                               diag0, bad_flag);
         hipLaunchKernelGGL(k_gjb_panel, dim3((unsigned)rows[active]), dim3(256), 0, s, p, md, active, W, pv, cbuf, tbuf);
         hipLaunchKernelGGL(k_gjb_sweep, dim3((unsigned)(tiles[active] + active)), dim3(256), 0, s, p, md, active, W, pv,
                            cbuf, tbuf, diag0, bad_flag);
