@@ -47,11 +47,11 @@ WORKLOADS = {
 SPMV_TRAFFIC = {
     "workload": "penny80",
     "sources": {
-        "paper_2111_09294_amd/csrc/kernels.hip": "9184e2300ba6de0e7e9657e77a8c4bb8355af437fa3be6de05a3e341df1b7577",
-        "paper_2111_09294_amd/csrc/dpcg_internal.h": "09b37faadb31f46c783ea09d232a204d9f7c117366662471a83d34623f83b69c"
+        "paper_2111_09294_amd/csrc/kernels.hip": "cd87ef1526adb7f3509d596c5c9bb243f9b4cbd2cab540a08d1b743698135ccd",
+        "paper_2111_09294_amd/csrc/dpcg_internal.h": "cb4023fb85ca6580a205bb118493a9cd2958b7ac120d1a9eb09a4d907e364566"
     },
-    "fetch_bytes": 1444818874,
-    "write_bytes": 16007888,
+    "fetch_bytes": 1444866294,
+    "write_bytes": 16007168,
 }
 SPMV_SOURCES = ("paper_2111_09294_amd/csrc/kernels.hip", "paper_2111_09294_amd/csrc/dpcg_internal.h")
 
