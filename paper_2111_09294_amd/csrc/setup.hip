@@ -1716,6 +1716,7 @@ struct GjMat {
     int64_t row0;   // first tile row (prefix of nt): its panels, its diagonal and scale (64 each)
     int64_t out;    // first entry of its inverse in dinv
     int32_t nt, size, start, block;
+    int64_t buf0, piv0;  // first tile of its row buffers and of its pivot inverses
 };
 
 // last matrix whose first tile (row) is <= wg
@@ -1797,12 +1798,13 @@ struct GjBufs {
     double *c1, *t1, *c2, *t2;  // a matrix's tiles: -s A_pJ, T1_J, -s B_qJ, T2_J
 };
 __device__ __forceinline__ GjBufs gj_bufs(const GjMat &G, double *cbuf, double *tbuf) {
-    const int64_t o = 2 * G.row0 * (kCb * kCb), n = (int64_t)G.nt * (kCb * kCb);
+    const int64_t o = G.buf0 * (kCb * kCb), n = (int64_t)G.nt * (kCb * kCb);
     return {cbuf + o, tbuf + o, cbuf + o + n, tbuf + o + n};
 }
-// P of pivot tile p (i = 0) or P' (i = 1): two pairs per matrix, used in turn
-__device__ __forceinline__ double *gj_pivot(double *P, int mi, int p, int i) {
-    return P + ((int64_t)mi * 4 + (p & 2) + i) * (kCb * kCb);
+// P of pivot tile p (i = 0) or P' (i = 1): two pairs per matrix, used in turn (as many tiles of
+// them as it has pivots)
+__device__ __forceinline__ double *gj_pivot(double *P, const GjMat &G, int p, int i) {
+    return P + (G.piv0 + (p & 2) + i) * (kCb * kCb);
 }
 
 __global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict__ mats, int count, double *W,
@@ -1812,7 +1814,7 @@ __global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict
         const GjMat G = mats[mi];
         __syncthreads();
         first_pivot_body(PackedTiles{W + G.tile0 * (kCb * kCb)}, G.size, diag0 + G.row0 * kCb,
-                         gj_pivot(P, mi, 0, 0), fail, G.block);
+                         gj_pivot(P, G, 0, 0), fail, G.block);
     }
 }
 
@@ -1850,8 +1852,8 @@ __global__ __launch_bounds__(256) void k_gjb_pivot2(int p, const GjMat *__restri
         const double *A = W + G.tile0 * (kCb * kCb);
         const int64_t row = (int64_t)(p + 1) * (p + 2) / 2;
         const double *L = A + (row + p) * (kCb * kCb), *Aqq = L + kCb * kCb;
-        const double *P = gj_pivot(Pm, mi, p, 0);
-        double *P2 = gj_pivot(Pm, mi, p, 1);
+        const double *P = gj_pivot(Pm, G, p, 0);
+        double *P2 = gj_pivot(Pm, G, p, 1);
         double lv[16], sr[16];
         __syncthreads();
 #pragma unroll
@@ -1901,7 +1903,7 @@ __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restric
     if (two ? J == p + 1 : J == p) return;
     const PackedTiles T{const_cast<double *>(W) + G.tile0 * (kCb * kCb)};
     const GjBufs B = gj_bufs(G, cbuf, tbuf);
-    const double *P = gj_pivot(Pm, mi, p, 0), *P2 = gj_pivot(Pm, mi, p, 1), *L = T.tile(p + 1, p);
+    const double *P = gj_pivot(Pm, G, p, 0), *P2 = gj_pivot(Pm, G, p, 1), *L = T.tile(p + 1, p);
     const int64_t o = (int64_t)J * (kCb * kCb);
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     const double s = J > p ? 1.0 : -1.0;
@@ -2009,7 +2011,7 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
     if (I == last || J == last) {
         // pivot tile; row: T_J; column: -T_I^T (transposed through LDS)
         const double *tl = two ? B.t2 : B.t1;
-        const double *src = I == last && J == last ? gj_pivot(Pm, mi, p, two ? 1 : 0) : tl + (I == last ? oj : oi);
+        const double *src = I == last && J == last ? gj_pivot(Pm, G, p, two ? 1 : 0) : tl + (I == last ? oj : oi);
         double v[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) v[q] = src[(ta + 4 * q) * kCb + tb];
@@ -2025,7 +2027,7 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
         return;
     }
     const double *base = A;
-    if (I == p) base = J == p ? gj_pivot(Pm, mi, p, 0) : B.t1 + oj;
+    if (I == p) base = J == p ? gj_pivot(Pm, G, p, 0) : B.t1 + oj;
     else if (J == p) base = B.t1 + oi;
     const bool column = J == p && I != p;
     dbl4 acc[4];
@@ -2064,7 +2066,7 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
             for (int v = 0; v < 4; ++v) S[fma_row(b, v) * kCbLd + fma_col(b)] = acc[b][v];
         mirror_lower(S);
         const bool bad = pivot_inverse64(S, diag0 + G.row0 * kCb, (int64_t)I * kCb, G.size);
-        double *Pn = gj_pivot(Pm, mi, p + 2, 0);
+        double *Pn = gj_pivot(Pm, G, p + 2, 0);
 #pragma unroll
         for (int q = 0; q < 16; ++q) Pn[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
         if (bad && threadIdx.x == 0) pivot_failed(fail, G.block);
@@ -2459,9 +2461,14 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     }
     std::stable_sort(m.begin(), m.end(), [](const GjMat &a, const GjMat &b) { return a.nt > b.nt; });
     std::vector<int64_t> tiles(count + 1, 0), rows(count + 1, 0);
+    int64_t bufs = 0, pivs = 0;  // row buffers: none where the only tile is the pivot
     for (int i = 0; i < count; ++i) {
         m[i].tile0 = tiles[i];
         m[i].row0 = rows[i];
+        m[i].buf0 = bufs;
+        m[i].piv0 = pivs;
+        bufs += m[i].nt > 1 ? 2 * m[i].nt : 0;
+        pivs += std::min(m[i].nt, 4);
         tiles[i + 1] = tiles[i] + coarse_tile_count(m[i].nt);
         rows[i + 1] = rows[i] + m[i].nt;
     }
@@ -2472,9 +2479,9 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     HT(pool.tmp(&W, tiles[count] * kTile));
     HT(pool.tmp(&diag0, rows[count] * kCb));
     HT(pool.tmp(&scale, rows[count] * kCb));
-    HT(pool.tmp(&pv, (int64_t)count * 4 * kTile));
-    HT(pool.tmp(&cbuf, 2 * rows[count] * kTile));
-    HT(pool.tmp(&tbuf, 2 * rows[count] * kTile));
+    HT(pool.tmp(&pv, pivs * kTile));
+    HT(pool.tmp(&cbuf, std::max<int64_t>(1, bufs) * kTile));
+    HT(pool.tmp(&tbuf, std::max<int64_t>(1, bufs) * kTile));
     HT(hipMemcpyAsync(md, m.data(), sizeof(GjMat) * count, hipMemcpyHostToDevice, s));
     HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[count] * kCb, s));
     HT(hipMemsetAsync(W, 0, sizeof(double) * tiles[count] * kTile, s));
