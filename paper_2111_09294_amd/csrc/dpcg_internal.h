@@ -391,42 +391,43 @@ hipError_t launch_to_f32(const dpcg_ctx *c, const double *src, int64_t count, fl
 // y += x
 hipError_t launch_add(const dpcg_ctx *c, const double *x, double *y);
 
-// Keeps iterations enqueued on the stream (enqueue(i) for i = 0, 1, ...) until every
-// posted flag leaves kRunning or max_iter have been enqueued.  The
-// SpMV posts the state it finds to pinned memory; the host stays at most
-// min(check_every, kAhead) iterations ahead of the last one started, so a solve neither stops for a read-back
-// nor runs more than kAhead - 1 idle iterations past its end (with a read-back every 16
-// iterations a 10^3 solve took 2.85 ms, now 2.59; 23^3 7.3 -> 6.9 ms; three iterations cover
-// the host's 15 us per iteration of launches).  Returns the iterations enqueued, or a
-// negative status.
+// Keeps iterations enqueued on the stream (enqueue(i) for i = 0, 1, ...) until every posted
+// flag leaves kRunning or max_iter have been enqueued.  The SpMV posts the state it finds to
+// pinned memory; the host stays at most min(check_every, kAhead) iterations ahead of the last
+// one started, so a solve neither stops for a read-back nor runs more than kAhead - 1 idle
+// iterations past its end (with a read-back every 16 iterations a 10^3 solve took 2.85 ms,
+// now 2.59; 23^3 7.3 -> 6.9 ms; three iterations cover the host's 15 us per iteration of
+// launches).  Waiting turns ask the stream now and then, for an error and in case a word does
+// not move.  An idle stream says only that everything enqueued so far has run: the host may
+// have lost its core since it read the words, so they are read again, and a system that runs
+// goes on.  Returns the iterations enqueued, or a negative status.
 constexpr int kAhead = 3;
 
 template <class Enqueue>
 int32_t follow(hipStream_t s, uint64_t *const *progress, int count, int max_iter, int check_every,
                const Enqueue &enqueue) {
     const int ahead = std::min(check_every, kAhead);
-    int32_t enq = 0;
+    int32_t enq = 0, over = 0;  // enqueued, of these known to have run
     uint32_t spins = 0;
     while (true) {
         bool running = false;
         int32_t started = enq;
         for (int i = 0; i < count; ++i) {
-            const uint64_t v = __atomic_load_n(progress[i], __ATOMIC_RELAXED);
+            const uint64_t v = __atomic_load_n(progress[i], __ATOMIC_ACQUIRE);
             if ((int32_t)(v >> 32) != kRunning) continue;
             running = true;
             started = std::min(started, (int32_t)(uint32_t)v);
         }
         if (!running || enq >= max_iter) return enq;
-        if (enq - started < ahead) {
+        if (enq - std::max(started, over) < ahead) {
             const int e = enqueue(enq);
             if (e != DPCG_OK) return e;
             ++enq;
             spins = 0;
         } else if ((++spins & 4095) == 0) {
-            // nothing left on the stream (the state tells why), or an error
             const hipError_t q = hipStreamQuery(s);
-            if (q == hipSuccess) return enq;
-            if (q != hipErrorNotReady) return DPCG_EHIP;
+            if (q == hipSuccess) over = enq;
+            else if (q != hipErrorNotReady) return DPCG_EHIP;
         } else {
             __builtin_ia32_pause();
         }
