@@ -528,8 +528,10 @@ __device__ __forceinline__ void k_update_bj_body(int vb,
         bj_first(m, meta, mv);
     };
     load();
-    if (flag != kRunning) return;
+    // workgroup 0 may set the flag meanwhile: a wave leaves only once its workgroup's sum is
+    // whole, and the others then find the same breakdown in it
     pq = folded ? block_sum(pq, lds) : wave_sum(pq);
+    if (flag != kRunning) return;
     const double alpha = ((it & 1) ? rho1 : rho0) / pq;
     if (!(pq > 0.0) || !isfinite(pq) || !isfinite(alpha)) {
         if (vb == 0 && threadIdx.x == 0) {

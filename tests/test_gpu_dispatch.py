@@ -98,6 +98,35 @@ def test_step_length_partials(nb):
     assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
 
 
+@pytest.mark.parametrize("nb", [4162, 294912])
+def test_breakdown_keeps_the_last_iterate(nb):
+    """A breakdown of the second step with p^T q summed by the update (66 and 4608 partials):
+    u stays what one iteration made it, bit for bit and every time, alone and among other
+    systems.  K is block diagonal in pairs [[A, 2A], [2A, A]], M^-1 K has the eigenvalues 3
+    and -1 only, so from f in both eigenspaces (f^T M^-1 K M^-1 f > 0) the second direction's
+    p^T K p is negative."""
+    import scipy.sparse as sp
+    A = np.array([[4.0, 1.0, 0.5], [1.0, 3.0, 0.2], [0.5, 0.2, 2.0]])
+    K = sp.kron(sp.identity(nb // 2), np.block([[A, 2 * A], [2 * A, A]])).tocsr()
+    K.sort_indices()
+    x = np.random.default_rng(6).uniform(0.5, 1.5, (nb // 2, 3)) @ A
+    f = torch.as_tensor(np.concatenate([2 * x, 0 * x], 1).reshape(-1), device=DEV)
+    C = chain(700)
+    y = np.random.default_rng(7).standard_normal(2100)
+    g = torch.as_tensor(C @ y, device=DEV)
+    with solver(K, []) as s, solver(C, [0]) as healthy, solver(K, []) as other:
+        one, ref = s.solve(f, tol=1e-13, max_iter=1, raise_on_error=False)
+        assert ref["status"] == D.abi.NOT_CONVERGED and ref["iterations"] == 1
+        for _ in range(3):
+            u, info = s.solve(f, tol=1e-13, raise_on_error=False)
+            assert info["status"] == D.abi.EBREAKDOWN and info["bad_index"] == 1 and info["iterations"] == 1
+            assert torch.equal(u, one) and info["rel_res_true"] == ref["rel_res_true"]
+            us, infos = D.solve_many([healthy, s, other], [g, f, f], tol=1e-13, raise_on_error=False)
+            assert [i["status"] for i in infos] == [0, D.abi.EBREAKDOWN, D.abi.EBREAKDOWN]
+            assert torch.equal(us[1], one) and torch.equal(us[2], one)
+            assert np.linalg.norm(us[0].cpu().numpy() - y) <= 1e-11 * np.linalg.norm(y)
+
+
 @pytest.mark.parametrize("sizes", [[19, 31, 32, 33, 5], [63, 64, 65, 12], [96, 97, 128, 129], [255, 256, 257, 3, 18],
                                    [513, 24, 1000]])
 def test_dense_block_tiles(sizes):
