@@ -2030,8 +2030,11 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
     if (I == p) base = J == p ? gj_pivot(Pm, G, p, 0) : B.t1 + oj;
     else if (J == p) base = B.t1 + oi;
     const bool column = J == p && I != p;
-    dbl4 acc[4];
-    if (column || I == J) {
+    // of a diagonal tile only the lower half is kept: the wave of the quarter above it would start
+    // from the quarter below, which another wave is overwriting, and has nothing to do
+    const bool above = I == J && __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1;
+    dbl4 acc[4] = {};
+    if (!above && (column || I == J)) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -2041,7 +2044,7 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
                 const double x = base[column || a < c ? c * kCb + a : a * kCb + c];
                 acc[b][v] = column ? -x : x;
             }
-    } else {
+    } else if (!above) {
 #pragma unroll
         for (int b = 0; b < 4; b += 2)
 #pragma unroll
@@ -2051,14 +2054,16 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
                 acc[b + 1][v] = x.y;
             }
     }
-    if (I != p && J != p) cb_fma(B.c1 + oi, B.t1 + oj, acc);
-    if (two) cb_fma(B.c2 + oi, B.t2 + oj, acc);
+    if (!above) {
+        if (I != p && J != p) cb_fma(B.c1 + oi, B.t1 + oj, acc);
+        if (two) cb_fma(B.c2 + oi, B.t2 + oj, acc);
 #pragma unroll
-    for (int b = 0; b < 4; b += 2)
+        for (int b = 0; b < 4; b += 2)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            __builtin_nontemporal_store(dbl2{acc[b][v], acc[b + 1][v]},
-                                        (dbl2 *)(A + fma_row(b, v) * kCb + fma_col(b)));
+            for (int v = 0; v < 4; ++v)
+                __builtin_nontemporal_store(dbl2{acc[b][v], acc[b + 1][v]},
+                                            (dbl2 *)(A + fma_row(b, v) * kCb + fma_col(b)));
+    }
     if (pivots) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)

@@ -151,6 +151,22 @@ def test_dense_block_tiles(sizes):
         assert np.all(np.abs(y32[a:b] - ref) <= 1.01 * bound + (b - a) * 4e-15 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("sizes", [[129, 64], [192, 193], [257, 320, 500]])
+def test_dense_inverses_repeat(sizes):
+    """Blocks of two to eight tiles of the sweeps, set up again: the same inverses, bit for bit."""
+    n = -(-sum(sizes) // 3) * 3
+    K = chain(n // 3, seed=9)
+    bp = np.cumsum([0] + sizes + ([n - sum(sizes)] if n > sum(sizes) else []))
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    r = t(np.random.default_rng(10).standard_normal(n), torch.float64)
+    ys = []
+    for _ in range(4):
+        with D.Solver(n, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), 0, None,
+                      None, None, t(bp, torch.int32)) as s:
+            ys.append(s.bj_apply(r))
+    assert all(torch.equal(y, ys[0]) for y in ys[1:])
+
+
 @pytest.mark.parametrize("nrhs", [1, 7, 8, 9, 16, 17, 32])
 def test_batch_widths(problems, nrhs):
     """The batch layout's widths (8, 16, 32 columns): K X of an enriched mesh entry by entry
