@@ -180,8 +180,9 @@ void choose_shapes(dpcg_ctx *c) {
     c->spmv.nwg = c->spmv.steps;  // one row step per workgroup (more per workgroup measured slower)
     if (c->spmv.nwg >= 8) c->spmv.nwg = (c->spmv.nwg + 7) & ~7;
     c->vec_nwg = round_grid((int)std::min<int64_t>((c->n + kThreads - 1) / kThreads, 1024));
-    // two rows per thread: half the workgroups, each forming rho once (four measured slower)
-    c->prolong_nwg = round_grid((int)std::min<int64_t>((c->n + 2 * kThreads - 1) / (2 * kThreads), 16384));
+    // two rows per thread: half the workgroups, each forming rho once (four measured slower);
+    // rounded up, so that no thread is left a third row
+    c->prolong_nwg = round8((int)std::min<int64_t>((c->n + 2 * kThreads - 1) / (2 * kThreads), 16384));
     // one tile each, rounded up to a multiple of 8 (partials reduced by one workgroup)
     c->bj_nwg = c->bj_ntiles <= 65536 ? round8(std::max(1, c->bj_ntiles)) : 65536;
 }
@@ -643,7 +644,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         d.bj_nwg = c->bj_nwg;
         d.vec_nwg = c->vec_nwg;
         d.guess = guess ? 1 : 0;
-        d.pad = 0;
+        d.prolong_nwg = c->prolong_nwg;
         d.n = c->n;
         d.nnzb = c->nnzb;
         d.einv_ld = c->einv_ld;
@@ -694,7 +695,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
                                      : coarse_by_rows(c->k) ? coarse_parts(c->k, c->coarse_nt)
                                                             : (int)coarse_tile_count(c->coarse_nt),
                                      coarse_by_rows(c->k) ? 0 : c->coarse_nt,
-                                     round8(c->vec_nwg)};
+                                     round8(c->vec_nwg), c->prolong_nwg};
         fold = fold && fold_alpha(c->spmv.nwg);
         for (int ph = 0; ph < kMsPhases; ++ph) {
             tab.off[ph][i] = tot[ph];
@@ -748,7 +749,7 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
         LAUNCH(launch_ms_restrict(S, T, Y, tot[kMsRestrict], 1, 1, 1, max_iter));
         LAUNCH(launch_ms_coarse(S, T, Y, tot[kMsCoarse], 2));
         LAUNCH(launch_ms_coarse_sum(S, T, Y, tot[kMsCoarseSum], 2));
-        LAUNCH(launch_ms_prolong(S, T, Y, tot[kMsVec], 2, 0));
+        LAUNCH(launch_ms_prolong(S, T, Y, tot[kMsProlong], 2, 0));
         return DPCG_OK;
     });
     if (enq < 0) return enq;

@@ -241,12 +241,12 @@ struct DenseRow {
 // workspace and its state) and, per phase, the prefix offsets of the systems'
 // workgroups in the launch grid.
 constexpr int kMaxSystems = 64;
-enum MsPhase { kMsSpmv = 0, kMsAlpha, kMsBj, kMsRestrict, kMsCoarse, kMsCoarseSum, kMsVec, kMsPhases };
+enum MsPhase { kMsSpmv = 0, kMsAlpha, kMsBj, kMsRestrict, kMsCoarse, kMsCoarseSum, kMsVec, kMsProlong, kMsPhases };
 
 struct MsSys {
     int32_t nb, steps, spmv_nwg, group;
     int32_t k, bj_ntiles, bj_nwg, vec_nwg;
-    int32_t guess, pad;
+    int32_t guess, prolong_nwg;
     int64_t n, nnzb, einv_ld;
     const int32_t *brow_ptr, *bcol;
     const int16_t *bcol16;  // or null, as in the handle

@@ -1062,7 +1062,10 @@ __device__ __forceinline__ void k_prolong_p_body(int vb, int64_t n, int32_t nwg,
         pold[i] = pp[dc];
     }
     double hs = masked_share<kThreads, kCoarseRowsMax / kCoarseRowWaves / kThreads>(hparts, nhp);
-    if (z_col) {
+    bool entries = false;
+#pragma unroll
+    for (int i = 0; i < R; ++i) entries = entries || e0[i] < e1[i];
+    if (__any(entries)) {  // a Z of few rows leaves most waves none (9.3 -> 6.5 us at 900,000 unknowns)
         int32_t zc[R][4];
         double zv[R][4];
 #pragma unroll
@@ -1338,12 +1341,16 @@ __global__ __launch_bounds__(kThreads) void k_ms_coarse_sum(const MsTable *__res
 }
 
 // mode 0: u = u_{-1} + Z delta (no state); mode 1: z = y + Z delta with r^T z partials;
-// mode 2: the fused prolongation, beta and search direction of an iteration
+// mode 2: the fused prolongation, beta and search direction of an iteration, on the single
+// solve's grid, which gives most threads their two rows (on the other modes' grid, of about one
+// row per thread, it read the next workgroup's rows and threw them away: six systems of 60,000
+// unknowns 9.5 us, now 7.6)
 __global__ __launch_bounds__(kThreads) void k_ms_prolong(const MsTable *__restrict__ tab,
                                                          const MsSys *__restrict__ sys, int mode, int advance) {
-    const int s = ms_find(tab, kMsVec, blockIdx.x);
+    const int phase = mode == 2 ? kMsProlong : kMsVec;
+    const int s = ms_find(tab, phase, blockIdx.x);
     const MsSys &S = sys[s];
-    const int vb = blockIdx.x - tab->off[kMsVec][s];
+    const int vb = blockIdx.x - tab->off[phase][s];
     if (mode == 0) {
         if (S.st->flag != kRunning) return;
         if (S.k > 0)
@@ -1356,7 +1363,7 @@ __global__ __launch_bounds__(kThreads) void k_ms_prolong(const MsTable *__restri
         k_prolong_body(vb, S.n, S.vec_nwg, S.z_ptr, S.z_col, S.z_val, S.delta, S.y, S.z, S.r, S.part_c, S.st,
                        advance);
     } else {
-        k_prolong_p_body(vb, S.n, S.vec_nwg, S.z_ptr, S.z_col, S.z_val, S.delta, S.y, S.hdp,
+        k_prolong_p_body(vb, S.n, S.prolong_nwg, S.z_ptr, S.z_col, S.z_val, S.delta, S.y, S.hdp,
                          coarse_parts(S.k, S.coarse_nt), S.p0, S.p1, S.st);
     }
 }

@@ -151,6 +151,25 @@ def test_dense_block_tiles(sizes):
         assert np.all(np.abs(y32[a:b] - ref) <= 1.01 * bound + (b - a) * 4e-15 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("nbs", [[1, 170, 171, 86], [1365, 1366, 2730, 2731], [20000, 87382, 5], [174762, 174763]])
+def test_many_prolongation_grid(nbs):
+    """Several systems at the edges of the prolongation's grid (512 rows per workgroup, from
+    eight workgroups on a multiple of eight): the single solves' iterates, bit for bit."""
+    Ks = [chain(nb, seed=i) for i, nb in enumerate(nbs)]
+    xs = [np.random.default_rng(11 + i).standard_normal(3 * nb) for i, nb in enumerate(nbs)]
+    fs = [torch.as_tensor(K @ x, device=DEV) for K, x in zip(Ks, xs)]
+    ss = [solver(K, np.arange(0, 3 * nb, 97) if nb > 1 else []) for K, nb in zip(Ks, nbs)]
+    try:
+        us, infos = D.solve_many(ss, fs, tol=1e-13)
+        for s, f, u, x, i in zip(ss, fs, us, xs, infos):
+            one, ref = s.solve(f, tol=1e-13)
+            assert i["status"] == 0 and i["iterations"] == ref["iterations"] and torch.equal(u, one)
+            assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
+    finally:
+        for s in ss:
+            s.close()
+
+
 @pytest.mark.parametrize("sizes", [[129, 64], [192, 193], [257, 320, 500]])
 def test_dense_inverses_repeat(sizes):
     """Blocks of two to eight tiles of the sweeps, set up again: the same inverses, bit for bit."""
