@@ -792,8 +792,8 @@ constexpr int kTouchLds = 2048;  // LDS words of the touched-vector bitmap (k <=
 // all of whose nodes move with it, so inside the subdomain (and for the enriched modes inside
 // their supports) only the rounding of the sum is left.  (KZ)^T keeps a triplet of a run of
 // vectors with the same structure (the modes of one subdomain) where one of its entries
-// exceeds that rounding, 4 eps (sum of |K| along the row) (largest |z| there); the rest, a
-// quarter to a third of the entries, is left out.
+// exceeds that rounding, 4 eps sum_j |K_ij| |z_j| of its own row i; the rest, a quarter to a
+// third of the entries, is left out.
 struct KzBatch {
     int64_t j0, ncol, lo3, w3, off3, slice0, nslice, bit0;
     int64_t moff;  // first triplet of the batch's window in the masks mk, rb and km
@@ -1078,12 +1078,9 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
     const int64_t x0 = (int64_t)blockIdx.x * per, x1 = min(n_it, x0 + per);
     for (int64_t x = x0 + (threadIdx.x >> 4); x - (threadIdx.x >> 4) < x1; x += 16) {
         const bool live = x < x1;
-        double acc[3][4], rowsum[3], zmax[4];
-        for (int i = 0; i < 3; ++i) {
-            rowsum[i] = 0.0;
-            for (int b = 0; b < 4; ++b) acc[i][b] = 0.0;
-        }
-        for (int b = 0; b < 4; ++b) zmax[b] = 0.0;
+        double acc[3][4], mag[3][4];  // (K z)_i and sum |K_ij| |z_j|
+        for (int i = 0; i < 3; ++i)
+            for (int b = 0; b < 4; ++b) acc[i][b] = mag[i][b] = 0.0;
         int64_t t = 0, R = 0;
         uint32_t mask = 0u;
         if (live) {
@@ -1099,15 +1096,14 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
                 if (!(zb & 15u)) continue;  // none of this lane's vectors has support on triplet c
                 double v[9];
                 for (int e = 0; e < 9; ++e) v[e] = rv[e * mR + (q - beg)];
-                for (int i = 0; i < 3; ++i) rowsum[i] += fabs(v[3 * i]) + fabs(v[3 * i + 1]) + fabs(v[3 * i + 2]);
                 const double *z = zd + (3 * (B.off3 + c)) * kBatch + 4 * sub;
                 for (int jj = 0; jj < 3; ++jj)
                     for (int b = 0; b < 4; ++b) {
                         const double zz = ((zb >> b) & 1u) ? z[jj * kBatch + b] : 0.0;
-                        zmax[b] = fmax(zmax[b], fabs(zz));
-                        acc[0][b] = fma(v[jj], zz, acc[0][b]);
-                        acc[1][b] = fma(v[3 + jj], zz, acc[1][b]);
-                        acc[2][b] = fma(v[6 + jj], zz, acc[2][b]);
+                        for (int i = 0; i < 3; ++i) {
+                            acc[i][b] = fma(v[3 * i + jj], zz, acc[i][b]);
+                            mag[i][b] = fma(fabs(v[3 * i + jj]), fabs(zz), mag[i][b]);
+                        }
                     }
             }
             // the vectors of the triplet's three rows of Z, over the item's sixteen lanes: a
@@ -1118,24 +1114,17 @@ __global__ __launch_bounds__(256) void k_kzb_values(const KzBatch *__restrict__ 
                 atomicOr(&tb[col / 32], 1u << (col % 32));
             }
         }
+        uint32_t keep = 0u;  // the lane's vectors with an entry above the rounding of its sum
         for (int i = 0; i < 3; ++i)
             for (int b = 0; b < 4; ++b) {
-                double v = acc[i][b];
-                v += __shfl_xor(v, 4);
-                v += __shfl_xor(v, 8);
-                acc[i][b] = v;
+                acc[i][b] += __shfl_xor(acc[i][b], 4);
+                acc[i][b] += __shfl_xor(acc[i][b], 8);
+                mag[i][b] += __shfl_xor(mag[i][b], 4);
+                mag[i][b] += __shfl_xor(mag[i][b], 8);
+                // (a NaN is kept, and what no finite bound covers)
+                if (!(fabs(acc[i][b]) <= 4.0 * DBL_EPSILON * mag[i][b] && isfinite(mag[i][b])))
+                    keep |= 1u << (4 * sub + b);
             }
-        for (int i = 0; i < 3; ++i) {
-            rowsum[i] += __shfl_xor(rowsum[i], 4);
-            rowsum[i] += __shfl_xor(rowsum[i], 8);
-        }
-        uint32_t keep = 0u;  // the lane's vectors with an entry above the rounding of its sum
-        for (int b = 0; b < 4; ++b) {
-            zmax[b] = fmax(zmax[b], __shfl_xor(zmax[b], 4));
-            zmax[b] = fmax(zmax[b], __shfl_xor(zmax[b], 8));
-            for (int i = 0; i < 3; ++i)  // (a NaN is kept)
-                if (!(fabs(acc[i][b]) <= 4.0 * DBL_EPSILON * rowsum[i] * zmax[b])) keep |= 1u << (4 * sub + b);
-        }
         keep |= (uint32_t)__shfl_xor((int)keep, 1);
         keep |= (uint32_t)__shfl_xor((int)keep, 2);
         if (!live || part != 0) continue;

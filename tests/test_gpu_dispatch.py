@@ -234,3 +234,33 @@ def test_kept_entries_of_kz(problems):
                 assert info["status"] == 0 and infos[j]["status"] == 0
                 assert torch.linalg.norm(U[:, j] - u) <= 1e-8 * torch.linalg.norm(u)
     assert kept[0] == kept[2] < 0.9 * kept[1]
+
+
+def test_small_entries_of_kz_are_kept():
+    """Entries of K Z far below (sum |K|) (max |z|) of their row, but not below the rounding of
+    their own sum: rows of tiny couplings and tiny components beside large ones.  Each g is one
+    product of two entries or a sum of two, without cancellation: 4 eps."""
+    import scipy.sparse as sp
+    rng = np.random.default_rng(12)
+    nb = 40
+    K = sp.lil_matrix((3 * nb, 3 * nb))
+    K.setdiag(rng.uniform(1.0, 2.0, 3 * nb))
+    for d in range(0, 60, 3):  # triplet d couples to its partner by 1e-20
+        K[d, d + 60] = K[d + 60, d] = 1e-20 * rng.uniform(1.0, 2.0)
+    K = K.tocsr()
+    K.sort_indices()
+    Z = np.zeros((3 * nb, 2))
+    Z[:60, 0] = 1e-18 * rng.uniform(1.0, 2.0, 60)  # tiny beside its partner's
+    Z[60:, 0] = rng.uniform(1.0, 2.0, 60)
+    Z[60:, 1] = rng.uniform(1.0, 2.0, 60)          # reaches the first half by the couplings only
+    Zs = sp.csr_matrix(Z)
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    zero, KZ = torch.zeros(3 * nb, dtype=torch.float64, device=DEV), K @ Z
+    with D.Solver(3 * nb, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), 2,
+                  t(Zs.indptr, torch.int64), t(Zs.indices, torch.int32), t(Zs.data, torch.float64),
+                  t(np.arange(0, 3 * nb + 1, 3), torch.int32)) as s:
+        for d in range(0, 3 * nb, 7):
+            b = zero.clone()
+            b[d] = 1.0
+            g = s.restrict(zero, b).cpu().numpy()
+            assert np.all(np.abs(g + KZ[d]) <= 4 * np.finfo(float).eps * np.abs(KZ[d])), (d, g, KZ[d])
