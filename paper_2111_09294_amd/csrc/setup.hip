@@ -1416,21 +1416,24 @@ __device__ __forceinline__ bool pivot_inverse64(double *S, const double *__restr
 // X Y for 64 x 64 tiles X, Y in LDS (row stride kCbLd) on the matrix cores: wave w of the
 // 256 threads computes the 32 x 32 quadrant (w / 2, w % 2) as 2 x 2 blocks of 16 x 16,
 // sixteen v_mfma_f64_16x16x4f64 steps each.  Result item v of block b = 2 bi + bj of lane
-// l is element (cb_row(b, v), cb_col(b)) of the product.
+// l is element (cb_row(b, v), cb_col(b)) of the product.  XT, YT: X or Y is kept transposed.
 __device__ __forceinline__ int cb_row(int b, int v) {
     return ((threadIdx.x >> 6) >> 1) * 32 + (b >> 1) * 16 + ((threadIdx.x & 63) >> 4) + 4 * v;
 }
 __device__ __forceinline__ int cb_col(int b) { return ((threadIdx.x >> 6) & 1) * 32 + (b & 1) * 16 + (threadIdx.x & 15); }
 
+template <bool XT = false, bool YT = false>
 __device__ __forceinline__ void cb_mfma(const double *X, const double *Y, dbl4 (&acc)[4]) {
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, kq = l >> 4;
     const int r0 = (wv >> 1) * 32 + (l & 15), c0 = (wv & 1) * 32 + (l & 15);
+    auto x = [&](int r, int k) { return XT ? X[k * kCbLd + r] : X[r * kCbLd + k]; };
+    auto y = [&](int k, int c) { return YT ? Y[c * kCbLd + k] : Y[k * kCbLd + c]; };
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[b] = dbl4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int s4 = 0; s4 < kCb; s4 += 4) {
-        const double x0 = X[r0 * kCbLd + s4 + kq], x1 = X[(r0 + 16) * kCbLd + s4 + kq];
-        const double y0 = Y[(s4 + kq) * kCbLd + c0], y1 = Y[(s4 + kq) * kCbLd + c0 + 16];
+        const double x0 = x(r0, s4 + kq), x1 = x(r0 + 16, s4 + kq);
+        const double y0 = y(s4 + kq, c0), y1 = y(s4 + kq, c0 + 16);
         acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0], 0, 0, 0);
         acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[1], 0, 0, 0);
         acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[2], 0, 0, 0);
@@ -1692,14 +1695,12 @@ __global__ __launch_bounds__(256) void k_einv_from_lower(int32_t k, int64_t ld, 
 
 // ---------------------------------------------------------------- dense blocks
 // Block-Jacobi blocks of more than kMaxBlock DoFs (subdomain-sized blocks).  The lower
-// triangle of K_BB, Jacobi-scaled, is gathered into packed 64 x 64 tiles (the identity beyond
-// the block's size) and inverted by the symmetric sweeps above, batched over the blocks: the
-// table is sorted by tiles, most first, so the blocks that still have a pivot tile p form a
-// prefix, and sweep p runs the tiles of that prefix in one launch.  A failed pivot lowers the
-// flag to the block's index.
-// Bound by the traffic of the tiles (64 KB each per sweep): 69 sweeps of 300 us and panels of
-// 18 us for 8 blocks of 4,400 DoFs, 4.1 TB/s and 34 TFLOP/s; sweeps of 32 pivots over every
-// tile of both triangles took 138 launches of 570 us.
+// triangle of K_BB, Jacobi-scaled, is inverted as 64 x 64 tiles (the identity beyond the block's
+// size): blocks of one or two tiles each by a workgroup in LDS (k_gjb_small), larger ones
+// gathered into packed tiles and inverted by the symmetric sweeps above, batched over the
+// blocks: the table is sorted by tiles, most first, so the blocks that still have a pivot tile
+// p form a prefix, and a sweep of pivot tiles p and p + 1 runs the tiles of that prefix in one
+// launch.  A failed pivot lowers the flag to the block's index.
 struct GjMat {
     int64_t tile0;  // first lower tile (prefix of nt (nt + 1) / 2), also its place in the work buffer
     int64_t row0;   // first tile row (prefix of nt): its panels, its diagonal and scale (64 each)
@@ -2067,17 +2068,12 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
     }
 }
 
-// The inverse S X S (S the scale) from X's lower triangle, as the apply reads it: lower tiles
-// of kDenseTile^2, diagonal ones whole, zero beyond the block.  One workgroup per 64 x 64 tile.
-__global__ __launch_bounds__(256) void k_gjb_finish(const GjMat *__restrict__ mats, int count,
-                                                    const double *__restrict__ W, const double *__restrict__ scale,
-                                                    double *__restrict__ dinv) {
+// Tile (I, J) of the inverse S X S (S the scale) from X's lower triangle (X: the 64 x 64 tile,
+// row stride ldx, times sign), as the apply reads it: lower tiles of kDenseTile^2, diagonal
+// ones whole, zero beyond the block.
+__device__ __forceinline__ void store_inverse(const GjMat &G, int I, int J, const double *X, int ldx, double sign,
+                                              const double *sc, double *__restrict__ dinv) {
     constexpr int T = kDenseTile;
-    const int mi = gj_find<&GjMat::tile0>(mats, count, blockIdx.x);
-    const GjMat G = mats[mi];
-    int I, J;
-    lower_tile(blockIdx.x - G.tile0, I, J);
-    const double *X = W + (int64_t)blockIdx.x * (kCb * kCb), *sc = scale + G.row0 * kCb;
     const int ntd = (G.size + T - 1) / T;
     for (int e = threadIdx.x; e < kCb * kCb; e += 256) {
         const int sub = e / (T * T), a = e / T % T, b = e % T;
@@ -2085,9 +2081,120 @@ __global__ __launch_bounds__(256) void k_gjb_finish(const GjMat *__restrict__ ma
         if (It >= ntd || Jt > It) continue;
         const int r = It * T + a, c = Jt * T + b, hi = max(r, c), lo = min(r, c);
         double v = 0.0;
-        if (hi < G.size) v = (X[(hi - I * kCb) * kCb + lo - J * kCb] * sc[lo]) * sc[hi];
+        if (hi < G.size) v = (sign * X[(hi - I * kCb) * ldx + lo - J * kCb] * sc[lo]) * sc[hi];
         dinv[G.out + ((int64_t)It * (It + 1) / 2 + Jt) * (T * T) + a * T + b] = v;
     }
+}
+
+// one workgroup per 64 x 64 tile
+__global__ __launch_bounds__(256) void k_gjb_finish(const GjMat *__restrict__ mats, int count,
+                                                    const double *__restrict__ W, const double *__restrict__ scale,
+                                                    double *__restrict__ dinv) {
+    const int mi = gj_find<&GjMat::tile0>(mats, count, blockIdx.x);
+    const GjMat G = mats[mi];
+    int I, J;
+    lower_tile(blockIdx.x - G.tile0, I, J);
+    store_inverse(G, I, J, W + (int64_t)blockIdx.x * (kCb * kCb), kCb, 1.0, scale + G.row0 * kCb, dinv);
+}
+
+// Rows [r0, min(r0 + 64, size)) of the block into the 64 x 64 tile S of columns [c0, c0 + 64),
+// the entries with column <= row, zero elsewhere; with diag the rows' diagonal entries go there.
+// Sixteen lanes per row.  Starts and ends with a barrier.
+__device__ __forceinline__ void gather_tile(const GjMat &G, int r0, int c0, const int64_t *__restrict__ ptr,
+                                            const int32_t *__restrict__ idx, const double *__restrict__ val,
+                                            double *S, double *diag) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < kCb * kCbLd; e += 256) S[e] = 0.0;
+    __syncthreads();
+    for (int i = r0 + (threadIdx.x >> 4); i < min(r0 + kCb, G.size); i += 16) {
+        const int64_t g = (int64_t)G.start + i, e1 = ptr[g + 1];
+        for (int64_t e = ptr[g] + (threadIdx.x & 15); e < e1; e += 16) {
+            const int64_t c = (int64_t)idx[e] - G.start;
+            if (c < c0 || c > i || (c >= c0 + kCb && c != i)) continue;
+            const double v = val[e];
+            if (c < c0 + kCb) S[(i - r0) * kCbLd + (int)c - c0] = v;
+            if (diag && c == i) diag[i] = v;
+        }
+    }
+    __syncthreads();
+}
+
+// S scaled, as gathered; a diagonal tile (r0 == c0) also gets the identity beyond the block and
+// its upper half.  Ends with a barrier.
+__device__ __forceinline__ void scale_tile(const GjMat &G, int r0, int c0, const double *sc, double *S) {
+    for (int e = threadIdx.x; e < kCb * kCb; e += 256) {
+        const int a = e / kCb, b = e % kCb, i = r0 + a, c = c0 + b;
+        if (i < G.size) S[a * kCbLd + b] = (S[a * kCbLd + b] * sc[i]) * sc[c];
+        else if (r0 == c0 && a == b) S[a * kCbLd + b] = 1.0;
+    }
+    if (r0 == c0) mirror_lower(S);
+    else __syncthreads();
+}
+
+// The blocks of up to 64 (NT = 1) and up to 128 unknowns (NT = 2), one workgroup each from K's
+// rows to the stored inverse with everything in LDS: no work buffers, one launch.  With
+// A = [A_00, L^T; L, A_11] and P = A_00^-1, T = L P, P' = (A_11 - T L^T)^-1, V = P' T the
+// inverse is [P + T^T V, -V^T; -V, P'].  Bound by the pivot inverses' chains; registers are not
+// bounded further (spilling for four workgroups per CU took 0.1 ms more, blocks of 19 to 64).
+// Setup of 180,000 unknowns in blocks of one size, in ms: here / by the 64-wide sweeps above /
+// by sweeps of 32 pivots before them:
+//   19: 0.83 / 1.41 / 1.00   32: 0.63 / 0.97 / 0.74   64: 0.58 / 0.75 / 0.89
+//   65: 0.76 / 1.36 / 1.09   96: 0.69 / 1.11 / 0.88  128: 0.70 / 1.01 / 1.94
+template <int NT>
+__global__ __launch_bounds__(256, 2) void k_gjb_small(const GjMat *__restrict__ mats,
+                                                      const int64_t *__restrict__ ptr,
+                                                      const int32_t *__restrict__ idx,
+                                                      const double *__restrict__ val, double *__restrict__ dinv,
+                                                      int *fail) {
+    __shared__ double S[NT][kCb * kCbLd], sc[NT * kCb], dg[NT * kCb];
+    const GjMat G = mats[blockIdx.x];
+    const int t = threadIdx.x;
+    if (t < NT * kCb) dg[t] = 0.0;
+    gather_tile(G, 0, 0, ptr, idx, val, S[0], dg);
+    if constexpr (NT == 2) gather_tile(G, kCb, 0, ptr, idx, val, S[1], dg);
+    if (t < NT * kCb) {
+        const double d = dg[t];
+        sc[t] = d > 0.0 ? 1.0 / sqrt(d) : 1.0;  // as k_dense_scale
+        dg[t] = (d * sc[t]) * sc[t];
+    }
+    __syncthreads();
+    scale_tile(G, 0, 0, sc, S[0]);
+    if constexpr (NT == 2) scale_tile(G, kCb, 0, sc, S[1]);
+    bool bad = pivot_inverse64(S[0], dg, 0, G.size);
+    if constexpr (NT == 2) {
+        dbl4 p[4], acc[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) p[b][v] = S[0][cb_row(b, v) * kCbLd + cb_col(b)];
+        cb_mfma(S[1], S[0], acc);  // T = L P
+        __syncthreads();
+        cb_to_lds(acc, S[0]);
+        __syncthreads();
+        cb_mfma<false, true>(S[0], S[1], acc);  // T L^T
+        gather_tile(G, kCb, kCb, ptr, idx, val, S[1], nullptr);
+        scale_tile(G, kCb, kCb, sc, S[1]);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[1][cb_row(b, v) * kCbLd + cb_col(b)] -= acc[b][v];
+        mirror_lower(S[1]);
+        bad |= pivot_inverse64(S[1], dg, kCb, G.size);
+        store_inverse(G, 1, 1, S[1], kCbLd, 1.0, sc, dinv);
+        cb_mfma(S[1], S[0], acc);  // V = P' T
+        __syncthreads();
+        cb_to_lds(acc, S[1]);
+        __syncthreads();
+        store_inverse(G, 1, 0, S[1], kCbLd, -1.0, sc, dinv);
+        cb_mfma<true, false>(S[0], S[1], acc);  // T^T V
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 4; ++b) p[b] += acc[b];
+        cb_to_lds(p, S[0]);
+        __syncthreads();
+    }
+    store_inverse(G, 0, 0, S[0], kCbLd, 1.0, sc, dinv);
+    if (bad && t == 0) pivot_failed(fail, G.block);
 }
 
 __global__ void k_to_i64(const int32_t *__restrict__ a, int64_t n, int64_t *__restrict__ out) {
@@ -2454,37 +2561,49 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
         m[i] = GjMat{0, 0, D.off, (D.size + kCb - 1) / kCb, D.size, D.start, D.block};
     }
     std::stable_sort(m.begin(), m.end(), [](const GjMat &a, const GjMat &b) { return a.nt > b.nt; });
-    std::vector<int64_t> tiles(count + 1, 0), rows(count + 1, 0);
-    int64_t bufs = 0, pivs = 0;  // row buffers: none where the only tile is the pivot
-    for (int i = 0; i < count; ++i) {
+    // most tiles first: [0, big) take the sweeps, then the blocks of two tiles and of one
+    int big = 0, one = count;
+    while (big < count && m[big].nt > 2) ++big;
+    while (one > big && m[one - 1].nt == 1) --one;
+    std::vector<int64_t> tiles(big + 1, 0), rows(big + 1, 0);
+    int64_t bufs = 0, pivs = 0;
+    for (int i = 0; i < big; ++i) {
         m[i].tile0 = tiles[i];
         m[i].row0 = rows[i];
         m[i].buf0 = bufs;
         m[i].piv0 = pivs;
-        bufs += m[i].nt > 1 ? 2 * m[i].nt : 0;
+        bufs += 2 * m[i].nt;
         pivs += std::min(m[i].nt, 4);
         tiles[i + 1] = tiles[i] + coarse_tile_count(m[i].nt);
         rows[i + 1] = rows[i] + m[i].nt;
     }
-    constexpr int64_t kTile = kCb * kCb;
     GjMat *md = nullptr;
-    double *W = nullptr, *diag0 = nullptr, *scale = nullptr, *pv = nullptr, *cbuf = nullptr, *tbuf = nullptr;
     HT(pool.tmp(&md, count));
-    HT(pool.tmp(&W, tiles[count] * kTile));
-    HT(pool.tmp(&diag0, rows[count] * kCb));
-    HT(pool.tmp(&scale, rows[count] * kCb));
-    HT(pool.tmp(&pv, pivs * kTile));
-    HT(pool.tmp(&cbuf, std::max<int64_t>(1, bufs) * kTile));
-    HT(pool.tmp(&tbuf, std::max<int64_t>(1, bufs) * kTile));
     HT(hipMemcpyAsync(md, m.data(), sizeof(GjMat) * count, hipMemcpyHostToDevice, s));
-    HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[count] * kCb, s));
-    HT(hipMemsetAsync(W, 0, sizeof(double) * tiles[count] * kTile, s));
-    const int gy = std::min(count, 65535);
+    if (one > big)
+        hipLaunchKernelGGL(k_gjb_small<2>, dim3(one - big), dim3(256), 0, s, (const GjMat *)md + big, kp, kc, kv,
+                           c->dinv, bad_flag);
+    if (count > one)
+        hipLaunchKernelGGL(k_gjb_small<1>, dim3(count - one), dim3(256), 0, s, (const GjMat *)md + one, kp, kc, kv,
+                           c->dinv, bad_flag);
+    HT(hipGetLastError());
+    if (big == 0) return DPCG_OK;
+    constexpr int64_t kTile = kCb * kCb;
+    double *W = nullptr, *diag0 = nullptr, *scale = nullptr, *pv = nullptr, *cbuf = nullptr, *tbuf = nullptr;
+    HT(pool.tmp(&W, tiles[big] * kTile));
+    HT(pool.tmp(&diag0, rows[big] * kCb));
+    HT(pool.tmp(&scale, rows[big] * kCb));
+    HT(pool.tmp(&pv, pivs * kTile));
+    HT(pool.tmp(&cbuf, bufs * kTile));
+    HT(pool.tmp(&tbuf, bufs * kTile));
+    HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[big] * kCb, s));
+    HT(hipMemsetAsync(W, 0, sizeof(double) * tiles[big] * kTile, s));
+    const int gy = std::min(big, 65535);
     const dim3 rgrid(std::min(1024, (m[0].nt * kCb + 3) / 4), gy);
-    hipLaunchKernelGGL(k_dense_scale, rgrid, dim3(256), 0, s, md, count, kp, kc, kv, scale);
-    hipLaunchKernelGGL(k_dense_gather, rgrid, dim3(256), 0, s, md, count, kp, kc, kv, scale, W, diag0);
-    hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, count, W, diag0, pv, bad_flag);
-    int active = count, active2 = count;
+    hipLaunchKernelGGL(k_dense_scale, rgrid, dim3(256), 0, s, md, big, kp, kc, kv, scale);
+    hipLaunchKernelGGL(k_dense_gather, rgrid, dim3(256), 0, s, md, big, kp, kc, kv, scale, W, diag0);
+    hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, big, W, diag0, pv, bad_flag);
+    int active = big, active2 = big;
     for (int p = 0; p < m[0].nt; p += 2) {
         while (active > 0 && m[active - 1].nt <= p) --active;
         while (active2 > 0 && m[active2 - 1].nt <= p + 1) --active2;
@@ -2495,7 +2614,7 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
         hipLaunchKernelGGL(k_gjb_sweep, dim3((unsigned)(tiles[active] + active)), dim3(256), 0, s, p, md, active, W, pv,
                            cbuf, tbuf, diag0, bad_flag);
     }
-    hipLaunchKernelGGL(k_gjb_finish, dim3((unsigned)tiles[count]), dim3(256), 0, s, md, count, W, scale, c->dinv);
+    hipLaunchKernelGGL(k_gjb_finish, dim3((unsigned)tiles[big]), dim3(256), 0, s, md, big, W, scale, c->dinv);
     HT(hipGetLastError());
     return DPCG_OK;
 }

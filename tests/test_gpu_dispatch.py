@@ -151,6 +151,45 @@ def test_dense_block_tiles(sizes):
         assert np.all(np.abs(y32[a:b] - ref) <= 1.01 * bound + (b - a) * 4e-15 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("seed", [0, 1])
+def test_many_small_dense_blocks(seed):
+    """Blocks of 19 to 130 unknowns, every size twice in a mixed order, each against LAPACK."""
+    rng = np.random.default_rng(20 + seed)
+    sizes = rng.permutation(np.repeat(np.arange(19, 131), 2))
+    n = -(-int(sizes.sum()) // 3) * 3
+    K = chain(n // 3, seed=21 + seed)
+    d = 10.0 ** rng.uniform(-3, 3, n)  # rows of unequal scale
+    import scipy.sparse as sp
+    K = (sp.diags(d) @ K @ sp.diags(d)).tocsr()
+    K = (0.5 * (K + K.T)).tocsr()
+    K.sort_indices()
+    bp = np.concatenate([[0], np.cumsum(sizes)])
+    bp = np.concatenate([bp, [n]]) if n > bp[-1] else bp
+    r = rng.standard_normal(n) * d
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    with D.Solver(n, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), 0, None, None,
+                  None, t(bp, torch.int32)) as s:
+        y = s.bj_apply(t(r, torch.float64)).cpu().numpy()
+    for a, b in zip(bp[:-1], bp[1:]):
+        ref = np.linalg.solve(K[a:b, a:b].toarray() / d[a:b, None] / d[None, a:b], r[a:b] / d[a:b])
+        assert np.linalg.norm(y[a:b] * d[a:b] - ref) <= (b - a) * 4e-15 * np.linalg.norm(ref), (a, b)
+
+
+@pytest.mark.parametrize("size, bad", [(19, 0), (40, 39), (64, 17), (65, 64), (100, 30), (128, 127), (129, 128)])
+def test_small_dense_block_that_is_not_spd(size, bad):
+    """A negative diagonal entry, in the first and in the second tile: the block's index."""
+    n = 4 * 3 * size
+    K = chain(n // 3, seed=22).tolil()
+    K[2 * size + bad, 2 * size + bad] = -1.0
+    K = K.tocsr()
+    K.sort_indices()
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    with pytest.raises(D.DpcgError) as e:
+        D.Solver(n, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), 0, None, None,
+                 None, t(np.arange(0, n + 1, size), torch.int32))
+    assert e.value.code == D.abi.EBLOCK_NOT_SPD and e.value.info.bad_index == 2
+
+
 @pytest.mark.parametrize("nbs", [[1, 170, 171, 86], [1365, 1366, 2730, 2731], [20000, 87382, 5], [174762, 174763]])
 def test_many_prolongation_grid(nbs):
     """Several systems at the edges of the prolongation's grid (512 rows per workgroup, from
