@@ -160,25 +160,13 @@ void set_spmv_group(dpcg_ctx *c, int g) {
     c->spmv.group = g;
     const int rows_per_step = 4 * 64 / g;  // 4 waves per SpMV workgroup
     c->spmv.steps = (int)((c->nb + rows_per_step - 1) / rows_per_step);
-    c->spmv.nwg = c->spmv.steps;  // one row step per workgroup (more per workgroup measured slower)
-    if (c->spmv.nwg >= 8) c->spmv.nwg = (c->spmv.nwg + 7) & ~7;
+    // one row step per workgroup (more per workgroup measured slower), rounded up to a multiple
+    // of 8 (XCD-aware mapping); the extra workgroups find an empty step range
+    c->spmv.nwg = round8(c->spmv.steps);
 }
 
 void choose_shapes(dpcg_ctx *c) {
-    const double avg = c->nb ? (double)c->nnzb / c->nb : 1.0;
-    // lanes per block row: one pass over a typical row (measured on gfx950: 32 lanes for
-    // rows of ~30 blocks beat 16 lanes with two passes); dpcg_autotune measures instead
-    int g = 32;
-    if (avg <= 6) g = 4;
-    else if (avg <= 12) g = 8;
-    else if (avg <= 20) g = 16;
-    c->spmv.group = g;
-    const int rows_per_step = 4 * 64 / g;  // 4 waves per SpMV workgroup
-    c->spmv.steps = (int)((c->nb + rows_per_step - 1) / rows_per_step);
-    // one step per workgroup, rounded up to a multiple of 8 (XCD-aware mapping); the
-    // extra workgroups find an empty step range
-    c->spmv.nwg = c->spmv.steps;  // one row step per workgroup (more per workgroup measured slower)
-    if (c->spmv.nwg >= 8) c->spmv.nwg = (c->spmv.nwg + 7) & ~7;
+    set_spmv_group(c, spmv_lanes(c->nb, c->nnzb, c->longest_row));
     c->vec_nwg = round_grid((int)std::min<int64_t>((c->n + kThreads - 1) / kThreads, 1024));
     // two rows per thread: half the workgroups, each forming rho once (four measured slower);
     // rounded up, so that no thread is left a third row
@@ -596,8 +584,8 @@ int solve_many_impl(dpcg_handle *hs, int32_t count, const double *const *F, doub
             for (size_t i = 0; i < own.size(); ++i) hs[i]->stream = own[i];
         }
     } restore{hs, own};
-    // (each handle keeps its SpMV lane-group size: timed alone, a small system's launch latency
-    // hides what the size costs beside the others, and tuning took longer than it gained)
+    // (each handle keeps its SpMV lane-group size: tuning took as long as a solve of small
+    // systems, and what it finds beyond spmv_lanes' choice is within the noise of its timings)
     // norms and finiteness of every right-hand side (and guess)
     std::vector<double> fnorm(count);
     for (int i = 0; i < count; ++i) {

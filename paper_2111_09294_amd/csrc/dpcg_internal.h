@@ -45,6 +45,20 @@ constexpr int kAlphaParts = 64;   // workgroups of the first stage of p^T q
 // 450 to 2500 15.3 -> 14.95 ms; at 8900 (40^3) folding costs (9.6 -> 10.5 ms).
 constexpr int kFoldParts = 4608;
 __host__ __device__ inline bool fold_alpha(int32_t parts) { return parts <= kFoldParts; }
+// Lanes per block row of the SpMV (4, 8, 16, 32; dpcg_autotune measures instead) from the mean
+// row length, and more while the longest row's chain gains more by it than the launch of twice
+// as many lanes costs: a group takes 0.29 us per pass over its row, and 10^6 lanes 6 us.
+// Measured times of 1,500 to 200,000 block rows, 3 to 33 blocks each, with and without six
+// rows of 16 to 400 more: the choice is within 10% of the fastest size.  The mean alone (up to
+// 6, 12 and 20 blocks) was not: 56 us against 33 with six rows of 400 among 200,000 of 5, 39
+// against 12.5 among 20,000; 18.0 against 15.8 without.
+constexpr int kLongRowMean = 22;  // above, all rows take 32 lanes
+inline int spmv_lanes(int32_t nb, int64_t nnzb, int32_t longest) {
+    const double mean = nb > 0 ? (double)nnzb / nb : 1.0;
+    int g = mean <= 4 ? 4 : mean <= 10 ? 8 : mean <= kLongRowMean ? 16 : 32;
+    while (g < 32 && longest > g && 0.29 * longest / (2 * g) > 6e-6 * nb * g) g *= 2;
+    return g;
+}
 constexpr int kRestrictRound = 4096;  // list entries per round of the restriction's loads (threads x depth)
 
 // tile (I, J), I >= J, of the lower triangle of a matrix of nt x nt tiles: index I (I + 1) / 2 + J
@@ -336,6 +350,7 @@ struct dpcg_ctx {
     int32_t vec_nwg = 0;       // grid of the elementwise kernels (one DoF per thread)
     dpcg::Workspace ws[2];     // [0] forward solves, [1] adjoint solves
     int32_t part_cap = 0;      // entries of each workspace partial-sum array
+    int32_t longest_row = 0;   // blocks of the longest block row (0 where the mean is above kLongRowMean)
     bool tuned = false;        // SpMV lane-group size chosen by measurement (dpcg_autotune)
     std::vector<void *> allocations;
     double setup_ms = 0.0;

@@ -672,6 +672,14 @@ __global__ void k_bcol16(int64_t nnzb, const int32_t *__restrict__ brow, const i
     }
 }
 
+// *longest (0 on entry) becomes the largest number of blocks in a row.
+__global__ __launch_bounds__(256) void k_longest_row(int32_t nb, const int32_t *__restrict__ ptr, int *longest) {
+    int m = 0;
+    for (int r = blockIdx.x * 256 + threadIdx.x; r < nb; r += gridDim.x * 256) m = max(m, ptr[r + 1] - ptr[r]);
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) atomicMax(longest, m);
+}
+
 // ---------------------------------------------------------------- Z^T
 // Z^T by a stable counting sort over chunks of Z's entries in row-major order.  Pass 1
 // counts each chunk's entries per column into cnt[c * nch + w]; an exclusive scan in
@@ -2791,12 +2799,15 @@ int gpu_setup(dpcg_ctx *c, int64_t n, const int64_t *kp, const int32_t *kc, cons
                        c->bcol, c->bval, brow);
     // block columns as 16-bit offsets from their row for the iteration SpMV (kept when
     // every offset fits: read back at the end of setup)
-    int *b16bad = nullptr;
-    HT(pool.tmp(&b16bad, 1));
+    int *b16bad = nullptr;  // [1]: the longest row
+    HT(pool.tmp(&b16bad, 2));
     HT(keep(c, &c->bcol16, nnzb));
-    HT(hipMemsetAsync(b16bad, 0, sizeof(int), s));
+    HT(hipMemsetAsync(b16bad, 0, 2 * sizeof(int), s));
     hipLaunchKernelGGL(k_bcol16, dim3(grid_for(nnzb)), dim3(256), 0, s, nnzb, (const int32_t *)brow,
                        (const int32_t *)c->bcol, c->bcol16, b16bad);
+    if (nnzb <= (int64_t)kLongRowMean * nb)
+        hipLaunchKernelGGL(k_longest_row, dim3(grid_for(nb, 256, 256)), dim3(256), 0, s, nb,
+                           (const int32_t *)c->brow_ptr, b16bad + 1);
     // The symmetry test and the small block-Jacobi inverses do not feed K Z, E or E^-1:
     // they run on the side stream beside that chain (whose kernels are latency bound and
     // leave most of the chip idle), joined before their flags are read.  Dense blocks
@@ -2875,9 +2886,10 @@ int gpu_setup(dpcg_ctx *c, int64_t n, const int64_t *kp, const int32_t *kc, cons
             return DPCG_EBLOCK_NOT_SPD;
         }
     }
-    int b16 = 0;
-    HT(hipMemcpy(&b16, b16bad, sizeof(int), hipMemcpyDeviceToHost));
-    if (b16) c->bcol16 = nullptr;  // an offset does not fit: the SpMV reads the int32 columns
+    int b16[2] = {};
+    HT(hipMemcpy(b16, b16bad, sizeof(b16), hipMemcpyDeviceToHost));
+    if (b16[0]) c->bcol16 = nullptr;  // an offset does not fit: the SpMV reads the int32 columns
+    c->longest_row = b16[1];
     return DPCG_OK;
 }
 

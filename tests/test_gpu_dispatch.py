@@ -151,6 +151,31 @@ def test_dense_block_tiles(sizes):
         assert np.all(np.abs(y32[a:b] - ref) <= 1.01 * bound + (b - a) * 4e-15 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("nb, long", [(40, 30), (1500, 64), (20000, 300), (120000, 300)])
+def test_few_long_rows(nb, long):
+    """Two block rows far longer than the rest, which set the SpMV's lanes per row: the product
+    entry by entry (two sums of at most m products differ by 2 m eps (|K| |x|)), and alone and
+    among other systems the same iterates, bit for bit."""
+    import scipy.sparse as sp
+    rng = np.random.default_rng(30)
+    K = chain(nb)
+    rows = 3 * rng.choice(nb, 2, replace=False)
+    I, J = np.repeat(rows, long), 3 * np.concatenate([rng.choice(nb, long, replace=False) for _ in rows])
+    C = sp.csr_matrix((np.full(len(I), 0.3 / long), (I, J)), shape=K.shape)
+    K = (K + C + C.T).tocsr()
+    K.sort_indices()
+    x = rng.standard_normal(3 * nb)
+    f = torch.as_tensor(K @ x, device=DEV)
+    m = int(np.diff(K.indptr).max())
+    with solver(K, [0, 5]) as s, solver(chain(7), []) as other:
+        y = s.spmv(torch.as_tensor(x, device=DEV)).cpu().numpy()
+        assert np.all(np.abs(y - K @ x) <= 2 * m * np.finfo(float).eps * (abs(K) @ np.abs(x)))
+        u, info = s.solve(f, tol=1e-13)
+        us, _ = D.solve_many([other, s], [torch.ones(21, dtype=torch.float64, device=DEV), f], tol=1e-13)
+        assert info["status"] == 0 and torch.equal(us[1], u)
+    assert np.linalg.norm(u.cpu().numpy() - x) <= 1e-11 * np.linalg.norm(x)
+
+
 @pytest.mark.parametrize("seed", [0, 1])
 def test_many_small_dense_blocks(seed):
     """Blocks of 19 to 130 unknowns, every size twice in a mixed order, each against LAPACK."""
