@@ -1502,10 +1502,12 @@ __device__ __forceinline__ void lower_tile(int64_t tid, int &I, int &J) {
     J = (int)(tid - (int64_t)I * (I + 1) / 2);
 }
 
-// P_0 = A_00^-1 (symmetrised) from the first diagonal tile's lower half.
+// P_0 = A_00^-1 (symmetrised) from the first diagonal tile's lower half; A_00 whole to orig when
+// given.
 template <class M>
 __device__ __forceinline__ void first_pivot_body(const M &mat, int32_t kdim, const double *__restrict__ diag0,
-                                                 double *__restrict__ P, int *fail, int failval) {
+                                                 double *__restrict__ P, double *__restrict__ orig, int *fail,
+                                                 int failval) {
     __shared__ double S[kCb * kCbLd];
     const double *A = mat.tile(0, 0);
     const int64_t ld = mat.stride();
@@ -1520,6 +1522,7 @@ __device__ __forceinline__ void first_pivot_body(const M &mat, int32_t kdim, con
     for (int q = 0; q < 16; ++q) {
         const int a = ta + 4 * q;
         sv[q] = a >= tb ? S[a * kCbLd + tb] : S[tb * kCbLd + a];
+        if (orig) orig[a * kCb + tb] = sv[q];
     }
     __syncthreads();
 #pragma unroll
@@ -1534,7 +1537,7 @@ __device__ __forceinline__ void first_pivot_body(const M &mat, int32_t kdim, con
 __global__ __launch_bounds__(256) void k_cgj_first_pivot(double *A, int64_t ld, int32_t kdim,
                                                          const double *__restrict__ diag0, double *__restrict__ P,
                                                          int *fail) {
-    first_pivot_body(RowTiles{A, ld}, kdim, diag0, P, fail, -1);
+    first_pivot_body(RowTiles{A, ld}, kdim, diag0, P, nullptr, fail, -1);
 }
 
 // Panel of sweep p, workgroup J != p: the tile A_pJ (stored below the diagonal for J < p;
@@ -1792,6 +1795,14 @@ __global__ __launch_bounds__(256) void k_dense_gather(const GjMat *__restrict__ 
 // the first product; row q is T2_J, column q -T2_I^T, its pivot tile P'.  The column tiles
 // A_Ip and B_Iq are signed transposes of row tiles, so -s A_pI and -s B_qI are kept (s = +1
 // for I > p, else -1): the summed index first, as cb_fma reads them.
+//
+// T1_J = P A_pJ by the explicit inverse leaves the residual A_pJ - A_pp T1_J at eps cond(A_pp),
+// which the tiles not yet swept take over: errors grew with the square of the condition.  One
+// step of refinement, T1_J += P (A_pJ - A_pp T1_J), and the same for T2_J, for the rows J still
+// to be swept keeps elimination's accuracy (in a model further refinement changes nothing).
+// Error of M^-1 r, blocks of 80 / 129 / 256 / 800 unknowns with condition 1e6: 8.9e-12, 1.5e-11,
+// 1.5e-11, 1.2e-11; without 1.1e-8, 7.6e-10, 5.7e-11, 1.6e-11 (sweeps of 32 pivots: 2.0e-10,
+// 3.0e-11, 9.3e-12, 5.8e-12).
 struct GjBufs {
     double *c1, *t1, *c2, *t2;  // a matrix's tiles: -s A_pJ, T1_J, -s B_qJ, T2_J
 };
@@ -1801,18 +1812,19 @@ __device__ __forceinline__ GjBufs gj_bufs(const GjMat &G, double *cbuf, double *
 }
 // P of pivot tile p (i = 0) or P' (i = 1): two pairs per matrix, used in turn (as many tiles of
 // them as it has pivots)
+// (and, in an array of the same layout, of A_pp and B_qq)
 __device__ __forceinline__ double *gj_pivot(double *P, const GjMat &G, int p, int i) {
     return P + (G.piv0 + (p & 2) + i) * (kCb * kCb);
 }
 
 __global__ __launch_bounds__(256) void k_gjb_first_pivot(const GjMat *__restrict__ mats, int count, double *W,
                                                          const double *__restrict__ diag0, double *__restrict__ P,
-                                                         int *fail) {
+                                                         double *__restrict__ orig, int *fail) {
     for (int mi = blockIdx.x; mi < count; mi += gridDim.x) {
         const GjMat G = mats[mi];
         __syncthreads();
         first_pivot_body(PackedTiles{W + G.tile0 * (kCb * kCb)}, G.size, diag0 + G.row0 * kCb,
-                         gj_pivot(P, G, 0, 0), fail, G.block);
+                         gj_pivot(P, G, 0, 0), gj_pivot(orig, G, 0, 0), fail, G.block);
     }
 }
 
@@ -1839,10 +1851,50 @@ __device__ __forceinline__ void mirror_lower(double *S) {
     __syncthreads();
 }
 
-// P' of the first count matrices (those with a pivot tile p + 1)
-__global__ __launch_bounds__(256) void k_gjb_pivot2(int p, const GjMat *__restrict__ mats, int count,
-                                                    const double *__restrict__ W, double *Pm,
-                                                    const double *__restrict__ diag0, int *fail) {
+// the LDS tile Y in a product's result layout
+__device__ __forceinline__ void cb_from_lds(const double *Y, dbl4 (&y)[4]) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[b][v] = Y[cb_row(b, v) * kCbLd + cb_col(b)];
+}
+
+// S (LDS) becomes the 64 x 64 tile A in memory
+__device__ __forceinline__ void tile_to_lds(const double *__restrict__ A, double *S) {
+    const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;
+    double v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = A[(ta + 4 * q) * kCb + tb];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = v[q];
+}
+
+// t += P (y - A t), t and y in the result layout, P and A = P^-1 tiles in memory; S and Y are
+// LDS tiles to use, which the caller may still be reading.  Ends without a barrier.
+__device__ __forceinline__ void refine(const double *__restrict__ P, const double *__restrict__ A,
+                                       const dbl4 (&y)[4], dbl4 (&t)[4], double *S, double *Y) {
+    dbl4 x[4];
+    __syncthreads();
+    tile_to_lds(A, S);
+    cb_to_lds(t, Y);
+    __syncthreads();
+    cb_mfma(S, Y, x);
+    __syncthreads();
+    tile_to_lds(P, S);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) x[b] = y[b] - x[b];
+    cb_to_lds(x, Y);
+    __syncthreads();
+    cb_mfma(S, Y, x);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) t[b] += x[b];
+}
+
+// P' of the first count matrices (those with a pivot tile p + 1), and T1_q
+__global__ __launch_bounds__(256, 2) void k_gjb_pivot2(int p, const GjMat *__restrict__ mats, int count,
+                                                    const double *__restrict__ W, double *Pm, double *orig,
+                                                    double *cbuf, double *tbuf, const double *__restrict__ diag0,
+                                                    int *fail) {
     __shared__ double S[kCb * kCbLd], Y[kCb * kCbLd];
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     for (int mi = blockIdx.x; mi < count; mi += gridDim.x) {
@@ -1851,36 +1903,41 @@ __global__ __launch_bounds__(256) void k_gjb_pivot2(int p, const GjMat *__restri
         const int64_t row = (int64_t)(p + 1) * (p + 2) / 2;
         const double *L = A + (row + p) * (kCb * kCb), *Aqq = L + kCb * kCb;
         const double *P = gj_pivot(Pm, G, p, 0);
-        double *P2 = gj_pivot(Pm, G, p, 1);
-        double lv[16], sr[16];
+        double *P2 = gj_pivot(Pm, G, p, 1), *O2 = gj_pivot(orig, G, p, 1);
+        double *t1 = gj_bufs(G, cbuf, tbuf).t1 + (int64_t)(p + 1) * (kCb * kCb);
+        double lv[16];
         __syncthreads();
+        tile_to_lds(P, S);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            lv[q] = L[(ta + 4 * q) * kCb + tb];
-            S[(ta + 4 * q) * kCbLd + tb] = P[(ta + 4 * q) * kCb + tb];
-        }
+        for (int q = 0; q < 16; ++q) lv[q] = L[(ta + 4 * q) * kCb + tb];
 #pragma unroll
         for (int q = 0; q < 16; ++q) Y[tb * kCbLd + ta + 4 * q] = lv[q];
+        __syncthreads();
+        dbl4 t[4], y[4], acc[4];
+        cb_mfma(S, Y, t);  // T1_q = P L^T
+        cb_from_lds(Y, y);
+        refine(P, gj_pivot(orig, G, p, 0), y, t, S, Y);
+        __syncthreads();
+        cb_to_lds(t, Y);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = lv[q];
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sr[4 * b + v] = Aqq[cb_row(b, v) * kCb + cb_col(b)];
-        __syncthreads();
-        dbl4 acc[4];
-        cb_mfma(S, Y, acc);  // P L^T
-        __syncthreads();
-        cb_to_lds(acc, Y);
-#pragma unroll
-        for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = lv[q];
+            for (int v = 0; v < 4; ++v) {
+                t1[cb_row(b, v) * kCb + cb_col(b)] = t[b][v];
+                y[b][v] = Aqq[cb_row(b, v) * kCb + cb_col(b)];
+            }
         __syncthreads();
         cb_mfma(S, Y, acc);
         __syncthreads();
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[b][v] = sr[4 * b + v] - acc[b][v];
+        for (int b = 0; b < 4; ++b) acc[b] = y[b] - acc[b];
         cb_to_lds(acc, S);
         mirror_lower(S);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) O2[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
+        __syncthreads();
         const bool bad = pivot_inverse64(S, diag0 + G.row0 * kCb, (int64_t)(p + 1) * kCb, G.size);
 #pragma unroll
         for (int q = 0; q < 16; ++q) P2[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
@@ -1891,8 +1948,8 @@ __global__ __launch_bounds__(256) void k_gjb_pivot2(int p, const GjMat *__restri
 // Row tiles J of the pivot tiles p and p + 1, one workgroup each, over the first count
 // matrices (those with more than p pivot tiles)
 __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restrict__ mats, int count,
-                                                   const double *__restrict__ W, double *Pm, double *cbuf,
-                                                   double *tbuf) {
+                                                   const double *__restrict__ W, double *Pm, double *orig,
+                                                   double *cbuf, double *tbuf) {
     __shared__ double S[kCb * kCbLd], Y[kCb * kCbLd];
     const int mi = gj_find<&GjMat::row0>(mats, count, blockIdx.x);
     const GjMat G = mats[mi];
@@ -1905,24 +1962,23 @@ __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restric
     const int64_t o = (int64_t)J * (kCb * kCb);
     const int tb = threadIdx.x & 63, ta = threadIdx.x >> 6;  // element (ta + 4 q, tb)
     const double s = J > p ? 1.0 : -1.0;
-    // all loads (coalesced, row-major) before the first LDS store: P, the stored tile (p, J)
-    // or (J, p), the latter A_pJ transposed, and the same of row p + 1 with L
-    double pv[16], yv[16], lv[16], wv2[16];
+    // loads coalesced, row-major: the stored tile (p, J) or (J, p), the latter A_pJ transposed,
+    // and the same of row p + 1, or T1_q where J = p: B_qp = -T1_q^T
     const double *A1 = J < p ? T.tile(p, J) : T.tile(J, p), *A2 = J < p ? T.tile(p + 1, J) : T.tile(J, p + 1);
+    if (J == p) A2 = B.t1 + (int64_t)(p + 1) * (kCb * kCb);
+    double yv[16], wv2[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int e = (ta + 4 * q) * kCb + tb;
-        pv[q] = P[e];
         yv[q] = J != p ? A1[e] : 0.0;
-        lv[q] = two ? L[e] : 0.0;
-        wv2[q] = two && J != p ? A2[e] : 0.0;
+        wv2[q] = two ? A2[e] : 0.0;
     }
-    dbl4 acc[4];
+    dbl4 acc[4], y[4];
     if (J != p) {
+        tile_to_lds(P, S);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int a = ta + 4 * q;
-            S[a * kCbLd + tb] = pv[q];
             if (J < p) Y[a * kCbLd + tb] = yv[q];
             else Y[tb * kCbLd + a] = yv[q];
         }
@@ -1933,6 +1989,10 @@ __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restric
             B.c1[o + a * kCb + tb] = -s * Y[a * kCbLd + tb];
         }
         cb_mfma(S, Y, acc);  // T1_J
+        if (J > p) {
+            cb_from_lds(Y, y);
+            refine(P, gj_pivot(orig, G, p, 0), y, acc, S, Y);
+        }
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -1940,38 +2000,31 @@ __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restric
         if (!two) return;
         __syncthreads();
         cb_to_lds(acc, Y);
-    } else {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) Y[(ta + 4 * q) * kCbLd + tb] = pv[q];
+        tile_to_lds(L, S);
+        __syncthreads();
+        cb_mfma(S, Y, acc);  // L T1_J
+        __syncthreads();
     }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        S[(ta + 4 * q) * kCbLd + tb] = lv[q];
-        pv[q] = P2[(ta + 4 * q) * kCb + tb];
-    }
-    __syncthreads();
-    cb_mfma(S, Y, acc);  // L T1_J, or L P where J = p
-    __syncthreads();
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int a = ta + 4 * q;
         if (J < p) S[a * kCbLd + tb] = wv2[q];
-        else S[tb * kCbLd + a] = wv2[q];  // zero where J = p
+        else S[tb * kCbLd + a] = wv2[q];
     }
     __syncthreads();
+    cb_from_lds(S, y);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) y[b] = J != p ? y[b] - acc[b] : -y[b];  // B_qJ
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const double x = S[cb_row(b, v) * kCbLd + cb_col(b)] - acc[b][v];
-            Y[cb_row(b, v) * kCbLd + cb_col(b)] = x;
-            B.c2[o + cb_row(b, v) * kCb + cb_col(b)] = -s * x;
-        }
+        for (int v = 0; v < 4; ++v) B.c2[o + cb_row(b, v) * kCb + cb_col(b)] = -s * y[b][v];
+    cb_to_lds(y, Y);
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 16; ++q) S[(ta + 4 * q) * kCbLd + tb] = pv[q];
+    tile_to_lds(P2, S);
     __syncthreads();
     cb_mfma(S, Y, acc);  // T2_J
+    if (J > p + 1) refine(P2, gj_pivot(orig, G, p, 1), y, acc, S, Y);
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -1986,7 +2039,7 @@ __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restric
 // tile a pass: 605; without the bound on registers 455; with cached tiles 367).  Matrix cores
 // and traffic alone would take 250 and 220.
 __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__restrict__ mats, int count, double *W,
-                                                   double *Pm, double *cbuf, double *tbuf,
+                                                   double *Pm, double *orig, double *cbuf, double *tbuf,
                                                    const double *__restrict__ diag0, int *fail) {
     __shared__ double S[kCb * kCbLd];
     const bool pivots = (int)blockIdx.x < count;
@@ -2068,8 +2121,11 @@ __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__rest
 #pragma unroll
             for (int v = 0; v < 4; ++v) S[fma_row(b, v) * kCbLd + fma_col(b)] = acc[b][v];
         mirror_lower(S);
+        double *Pn = gj_pivot(Pm, G, p + 2, 0), *On = gj_pivot(orig, G, p + 2, 0);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) On[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
+        __syncthreads();
         const bool bad = pivot_inverse64(S, diag0 + G.row0 * kCb, (int64_t)I * kCb, G.size);
-        double *Pn = gj_pivot(Pm, G, p + 2, 0);
 #pragma unroll
         for (int q = 0; q < 16; ++q) Pn[(ta + 4 * q) * kCb + tb] = S[(ta + 4 * q) * kCbLd + tb];
         if (bad && threadIdx.x == 0) pivot_failed(fail, G.block);
@@ -2141,13 +2197,13 @@ __device__ __forceinline__ void scale_tile(const GjMat &G, int r0, int c0, const
 
 // The blocks of up to 64 (NT = 1) and up to 128 unknowns (NT = 2), one workgroup each from K's
 // rows to the stored inverse with everything in LDS: no work buffers, one launch.  With
-// A = [A_00, L^T; L, A_11] and P = A_00^-1, T = L P, P' = (A_11 - T L^T)^-1, V = P' T the
-// inverse is [P + T^T V, -V^T; -V, P'].  Bound by the pivot inverses' chains; registers are not
+// A = [A_00, L^T; L, A_11] and P = A_00^-1, T = L P (refined once, as the sweeps' rows, with
+// A_00 gathered again), P' = (A_11 - T L^T)^-1, V = P' T the inverse is [P + T^T V, -V^T; -V, P'].  Bound by the pivot inverses' chains; registers are not
 // bounded further (spilling for four workgroups per CU took 0.1 ms more, blocks of 19 to 64).
 // Setup of 180,000 unknowns in blocks of one size, in ms: here / by the 64-wide sweeps above /
 // by sweeps of 32 pivots before them:
 //   19: 0.83 / 1.41 / 1.00   32: 0.63 / 0.97 / 0.74   64: 0.58 / 0.75 / 0.89
-//   65: 0.76 / 1.36 / 1.09   96: 0.69 / 1.11 / 0.88  128: 0.70 / 1.01 / 1.94
+//   65: 0.86 / 1.36 / 1.09   96: 0.77 / 1.11 / 0.88  128: 0.74 / 1.01 / 1.94
 template <int NT>
 __global__ __launch_bounds__(256, 2) void k_gjb_small(const GjMat *__restrict__ mats,
                                                       const int64_t *__restrict__ ptr,
@@ -2170,14 +2226,27 @@ __global__ __launch_bounds__(256, 2) void k_gjb_small(const GjMat *__restrict__ 
     if constexpr (NT == 2) scale_tile(G, kCb, 0, sc, S[1]);
     bool bad = pivot_inverse64(S[0], dg, 0, G.size);
     if constexpr (NT == 2) {
-        dbl4 p[4], acc[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) p[b][v] = S[0][cb_row(b, v) * kCbLd + cb_col(b)];
-        cb_mfma(S[1], S[0], acc);  // T = L P
+        dbl4 p[4], l[4], tt[4], acc[4];
+        cb_from_lds(S[0], p);
+        cb_from_lds(S[1], l);
+        cb_mfma(S[1], S[0], tt);  // T = L P
         __syncthreads();
-        cb_to_lds(acc, S[0]);
+        cb_to_lds(tt, S[1]);
+        gather_tile(G, 0, 0, ptr, idx, val, S[0], nullptr);
+        scale_tile(G, 0, 0, sc, S[0]);
+        cb_mfma(S[1], S[0], acc);  // T A_00
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[b] = l[b] - acc[b];
+        cb_to_lds(acc, S[1]);
+        cb_to_lds(p, S[0]);
+        __syncthreads();
+        cb_mfma(S[1], S[0], acc);  // (L - T A_00) P
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 4; ++b) tt[b] += acc[b];
+        cb_to_lds(tt, S[0]);
+        cb_to_lds(l, S[1]);
         __syncthreads();
         cb_mfma<false, true>(S[0], S[1], acc);  // T L^T
         gather_tile(G, kCb, kCb, ptr, idx, val, S[1], nullptr);
@@ -2597,11 +2666,13 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     HT(hipGetLastError());
     if (big == 0) return DPCG_OK;
     constexpr int64_t kTile = kCb * kCb;
-    double *W = nullptr, *diag0 = nullptr, *scale = nullptr, *pv = nullptr, *cbuf = nullptr, *tbuf = nullptr;
+    double *W = nullptr, *diag0 = nullptr, *scale = nullptr, *pv = nullptr, *orig = nullptr, *cbuf = nullptr,
+           *tbuf = nullptr;
     HT(pool.tmp(&W, tiles[big] * kTile));
     HT(pool.tmp(&diag0, rows[big] * kCb));
     HT(pool.tmp(&scale, rows[big] * kCb));
     HT(pool.tmp(&pv, pivs * kTile));
+    HT(pool.tmp(&orig, pivs * kTile));
     HT(pool.tmp(&cbuf, bufs * kTile));
     HT(pool.tmp(&tbuf, bufs * kTile));
     HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[big] * kCb, s));
@@ -2610,17 +2681,19 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     const dim3 rgrid(std::min(1024, (m[0].nt * kCb + 3) / 4), gy);
     hipLaunchKernelGGL(k_dense_scale, rgrid, dim3(256), 0, s, md, big, kp, kc, kv, scale);
     hipLaunchKernelGGL(k_dense_gather, rgrid, dim3(256), 0, s, md, big, kp, kc, kv, scale, W, diag0);
-    hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, big, W, diag0, pv, bad_flag);
+    hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, big, W, diag0, pv, orig,
+                       bad_flag);
     int active = big, active2 = big;
     for (int p = 0; p < m[0].nt; p += 2) {
         while (active > 0 && m[active - 1].nt <= p) --active;
         while (active2 > 0 && m[active2 - 1].nt <= p + 1) --active2;
         if (active2 > 0)
             hipLaunchKernelGGL(k_gjb_pivot2, dim3(std::min(active2, 65535)), dim3(256), 0, s, p, md, active2, W, pv,
-                               diag0, bad_flag);
-        hipLaunchKernelGGL(k_gjb_panel, dim3((unsigned)rows[active]), dim3(256), 0, s, p, md, active, W, pv, cbuf, tbuf);
+                               orig, cbuf, tbuf, diag0, bad_flag);
+        hipLaunchKernelGGL(k_gjb_panel, dim3((unsigned)rows[active]), dim3(256), 0, s, p, md, active, W, pv, orig,
+                           cbuf, tbuf);
         hipLaunchKernelGGL(k_gjb_sweep, dim3((unsigned)(tiles[active] + active)), dim3(256), 0, s, p, md, active, W, pv,
-                           cbuf, tbuf, diag0, bad_flag);
+                           orig, cbuf, tbuf, diag0, bad_flag);
     }
     hipLaunchKernelGGL(k_gjb_finish, dim3((unsigned)tiles[big]), dim3(256), 0, s, md, big, W, scale, c->dinv);
     HT(hipGetLastError());

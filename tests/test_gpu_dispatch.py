@@ -234,6 +234,34 @@ def test_many_prolongation_grid(nbs):
             s.close()
 
 
+@pytest.mark.parametrize("m", [48, 80, 96, 129, 160, 400])
+def test_dense_inverse_accuracy(m):
+    """M^-1 r of blocks with condition 1e6, spectra spread evenly over it: a backward stable
+    inverse leaves a forward error of a modest multiple of eps cond; the line is drawn at one.
+    (Rows by an explicit pivot inverse, unrefined, leave up to eps cond^2: 50 eps cond at 80.)"""
+    import scipy.sparse as sp
+    rng = np.random.default_rng(40 + m)
+    blocks = []
+    for _ in range(3):
+        Q = np.linalg.qr(rng.standard_normal((m, m)))[0]
+        S = Q * np.logspace(0, -6, m) @ Q.T
+        blocks.append(0.5 * (S + S.T))
+    K = sp.block_diag(blocks).tocsr()
+    K.sort_indices()
+    r = rng.standard_normal(3 * m)
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), device=DEV).to(dt)  # noqa: E731
+    with D.Solver(3 * m, t(K.indptr, torch.int64), t(K.indices, torch.int32), t(K.data, torch.float64), 0, None,
+                  None, None, t(np.arange(0, 3 * m + 1, m), torch.int32)) as s:
+        y = s.bj_apply(t(r, torch.float64)).cpu().numpy()
+    for i, S in enumerate(blocks):
+        rb = r[i * m:(i + 1) * m]
+        x = np.linalg.solve(S, rb).astype(np.longdouble)
+        for _ in range(4):  # refined in extended precision
+            x = x + np.linalg.solve(S, (rb - S.astype(np.longdouble) @ x).astype(float))
+        err = float(np.linalg.norm(y[i * m:(i + 1) * m] - x) / np.linalg.norm(x))
+        assert err <= np.finfo(float).eps * 1e6, (i, err)
+
+
 @pytest.mark.parametrize("sizes", [[129, 64], [192, 193], [257, 320, 500]])
 def test_dense_inverses_repeat(sizes):
     """Blocks of two to eight tiles of the sweeps, set up again: the same inverses, bit for bit."""
