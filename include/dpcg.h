@@ -52,7 +52,8 @@ enum {
 
 typedef struct {
     int32_t max_iter;          /* iteration cap (K p products); default 20000            */
-    int32_t check_every;       /* most iterations enqueued ahead of the last known state; default 16 */
+    int32_t check_every;       /* most iterations enqueued ahead of the last known state, up to
+                                  3 (larger values, the default 16 among them, mean 3)  */
     int32_t use_initial_guess; /* 1: u (or lambda) holds u_{-1} of Algorithm 2 on entry */
     int32_t record_history;    /* 1: keep ||r_i||/||f|| for i = 0..iterations            */
     int32_t precision;         /* DPCG_PREC_FP64 (default) or DPCG_PREC_MIXED            */
@@ -124,7 +125,7 @@ void dpcg_default_options(dpcg_options *opt);
  *       Larger blocks (the subdomain-sized blocks of Sec. 3.4: all unknowns of
  *       one subdomain, numbered consecutively) keep an explicit FP64 inverse (the
  *       lower triangle of 32 x 32 tiles), made by Gauss-Jordan sweeps
- *       at setup and applied by a dense matrix-vector kernel each iteration;
+ *       at setup and applied by a dense matrix-vector product each iteration;
  *       dpcg_solve_batch and dpcg_solve_many refuse handles with such blocks
  *       (DPCG_EINVAL).
  *   stream: hipStream_t (may be NULL for the default stream) on which all of the
@@ -213,7 +214,7 @@ int dpcg_solve_adjoint(dpcg_handle h, const double *g, double *lambda, double to
  * when every column converged, else DPCG_EBREAKDOWN if some column broke down, else
  * DPCG_NOT_CONVERGED; DPCG_EINVAL for nrhs outside [1, 32], tol <= 0, max_iter < 0,
  * record_history or a precision other than DPCG_PREC_FP64; DPCG_ENONFINITE; DPCG_EHIP.
- * The first call makes the handle's multi-RHS workspace (8 n x 32 and 2 k x 32
+ * The first call makes the handle's multi-RHS workspace (7 n x 32 and 3 k x 32
  * doubles).  SpMV timing (dpcg_set_timing) covers the batched product kernel.
  */
 int dpcg_solve_batch(dpcg_handle h, int32_t nrhs, const double *F, double *U, double tol,
@@ -225,7 +226,9 @@ int dpcg_solve_batch(dpcg_handle h, int32_t nrhs, const double *F, double *U, do
  * device) solves K_i U[i] = F[i] (device arrays of its n_i) with the method of
  * dpcg_solve and its own stopping test.  Each phase of an iteration runs as one kernel
  * launch over the workgroups of every system still iterating, so small systems share
- * the launches instead of queueing them per iteration each.  All work of the call runs on handles[0]'s stream (the others are synchronised first).
+ * the launches instead of queueing them per iteration each.  Each handle keeps its SpMV
+ * lane-group size (the setup's, or dpcg_autotune's).  All work of the call runs on
+ * handles[0]'s stream (the others are synchronised first).
  * infos[count] (host, may be NULL).  Returns DPCG_OK when every system converged, else
  * DPCG_EBREAKDOWN if one broke down, else DPCG_NOT_CONVERGED; DPCG_EINVAL (count, a
  * repeated handle, tol, max_iter, record_history or a precision other than FP64),
@@ -252,7 +255,7 @@ int dpcg_update_values(dpcg_handle h, const int64_t *k_rowptr, const int32_t *k_
 
 /* Times the SpMV kernel for each lane-group size (4, 8, 16, 32 lanes per block row;
  * reps launches each, HIP events) and keeps the fastest for every later solve of the
- * handle.  Returns the chosen size, or a negative status. */
+ * handle, in place of the one that setup chose from the row lengths.  Returns the chosen size, or a negative status. */
 int dpcg_autotune(dpcg_handle h, int32_t reps);
 
 /* Releases every resource of the handle (NULL is a no-op). */

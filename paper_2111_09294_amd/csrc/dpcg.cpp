@@ -1,6 +1,6 @@
 // Host side of the dpcg C ABI: argument checks, handle and workspace management, launch
-// shapes, and the solve driver that enqueues the iteration kernels and polls the device
-// flag.  The setup factorisations run on the GPU (setup.hip).
+// shapes, and the solve driver that enqueues the iteration kernels and follows the device.
+// The setup factorisations run on the GPU (setup.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -131,8 +131,9 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Solver state shared by the kernels of one solve; lives in device memory.  Every
-// field is written by exactly one thread of one kernel, and read only by kernels
-// that run after that one in stream order.
+// field is written by exactly one thread of a kernel, and read by kernels that run after
+// that one in stream order.  Other workgroups of the kernel that sets the flag may find it
+// old or new: none may leave in part on it.
 struct State {
     int32_t flag;        // kRunning, kConverged, kMaxIter, kBreakdown
     int32_t iter;        // index i of the iteration in flight (advanced by the restriction when
@@ -142,7 +143,6 @@ struct State {
     double thr;          // tol * ||f||_2
     double rho[2];       // rho_i = r_i^T z_i in slot i & 1 (beta kernel or fused prolongation),
                          // so rho_{i-1} stays readable
-    double alpha;        // alpha_i (k_alpha)
     double beta;         // beta_{i-1} (as rho; 0 at i = 0)
     double rr;           // ||r||^2 of the last check
     double aux;          // scratch scalar for one-off reductions
@@ -159,11 +159,11 @@ struct Workspace {
     double *h = nullptr;        // Z^T r for the fused prolongation
     double *cpart = nullptr;    // coarse product: contribution of tile pair (X, Y) to delta_X,
                                 // nt x nt x kCoarseTile
-    double *hdp = nullptr;      // per tile row X of delta: sum of h_j delta_j over its entries
+    double *hdp = nullptr;      // coarse_parts() sums of h_j delta_j (in cpart's room by rows)
     double *part_a = nullptr;   // partial sums (p^T q, r^T r, r^T z); sized max grid
     double *part_b = nullptr;
     double *part_c = nullptr;
-    double *part_d = nullptr;   // kAlphaParts first-stage sums of p^T q
+    double *part_d = nullptr;   // kAlphaParts first-stage sums of p^T q (above kFoldParts)
     double *rout = nullptr;     // mixed precision: FP64 residual f - K u of the refinement
     double *dcor = nullptr;     // mixed precision: correction of one inner solve
     State *st = nullptr;        // device

@@ -1,13 +1,18 @@
 // HIP kernels (gfx950, wave64) of one deflated block-Jacobi CG iteration.
 //
 // One iteration of Algorithm 1 preconditioned by Algorithm 3 runs as five kernels:
-//   spmv_p       p_i = z_i + beta p_{i-1} (formed on the fly), q = K p_i, p_i^T q partials
+//   spmv_p       q = K p_i, p_i^T q partials; tells the host how far the solve is
 //   update_bj    alpha = rho_i / p^T q; u += alpha p; r -= alpha q; ||r||^2 partials;
-//                y = M^{-1} r over whole blocks staged in LDS
+//                y = M^{-1} r over whole blocks staged in LDS; r^T y partials
 //   restrict     convergence test; g = Z^T r - (K Z)^T y  (the two right-hand sides of
-//                Algorithm 3's coarse solves, merged by linearity, with Z^T K y = (KZ)^T y)
-//   coarse       delta = E^{-1} g  (both coarse solves at once: lambda - mu = delta)
-//   prolong      z = y + Z delta; r^T z partials; advance the iteration counter
+//                Algorithm 3's coarse solves, merged by linearity, with Z^T K y = (KZ)^T y);
+//                h = Z^T r; advance the iteration counter
+//   coarse       delta = E^{-1} g  (both coarse solves at once: lambda - mu = delta); above
+//                kCoarseRowsMax deflation vectors in two launches
+//   prolong_p    rho = r^T y + h^T delta, beta, p_{i+1} = y + Z delta + beta p_i
+// and a first stage of p^T q above kFoldParts partials (alpha).  With dense block-Jacobi blocks
+// the update leaves them to two kernels of their own, and prolong (z = y + Z delta, r^T z
+// partials) and beta_p take the place of prolong_p.
 // Global reductions are two-stage and fixed-order (per-workgroup partials, then a
 // sequential-per-thread + fixed-tree sum), so results are bitwise reproducible.  No
 // floating-point atomics are used.  Convergence and breakdown are decided on the
@@ -1024,15 +1029,16 @@ __global__ __launch_bounds__(kThreads) void k_prolong(int64_t n, int32_t nwg, co
 
 // The prolongation of Algorithm 3 fused with beta and the new search direction of
 // Algorithm 1.  With h = Z^T r from the restriction, r^T z = r^T y + h^T delta exactly, so
-// rho_i is r^T y (summed by the restriction) plus the fixed-order sum of the k entries
-// (several systems per launch) or tile-row sums (single system) of h_j delta_j left by
-// the coarse product: every workgroup forms the same bits of rho_i
+// rho_i is r^T y (summed by the restriction) plus the fixed-order sum of the coarse_parts()
+// sums of h_j delta_j left by the coarse product (of kCoarseRowWaves rows up to kCoarseRowsMax
+// vectors, of a tile row above): every workgroup forms the same bits of rho_i
 // and of beta_{i-1} = rho_i / rho_{i-1} and writes p_i = y + Z delta + beta_{i-1} p_{i-1}
 // into buffer i & 1 directly (z itself is never stored).  The restriction has already
 // advanced the iteration.  Workgroup 0 stores rho_i in slot i & 1 and tests it.
 // Everything that does not need rho is loaded before the one barrier (two rows per thread,
 // their first four Z entries together), so the chain is row pointers, columns, delta (6.4 ->
-// 5.6 us at 10^3, 8.0 -> 6.5 us at 23^3, 29.2 -> 27.7 us at 80^3).
+// 5.6 us at 10^3, 8.0 -> 6.5 us at 23^3, 29.2 -> 27.7 us at 80^3; 4.6, 5.4 and 25.8 us since no
+// thread is left a third row).
 __device__ __forceinline__ void k_prolong_p_body(int vb, int64_t n, int32_t nwg, const int32_t *__restrict__ z_ptr,
                                                  const int32_t *__restrict__ z_col, const double *__restrict__ z_val,
                                                  const double *__restrict__ delta, const double *__restrict__ y,
@@ -1061,6 +1067,7 @@ __device__ __forceinline__ void k_prolong_p_body(int vb, int64_t n, int32_t nwg,
         v[i] = y[dc];
         pold[i] = pp[dc];
     }
+    static_assert(kCoarseRowsMax / kCoarseRowWaves % kThreads == 0, "the rows' partials in one round");
     double hs = masked_share<kThreads, kCoarseRowsMax / kCoarseRowWaves / kThreads>(hparts, nhp);
     bool entries = false;
 #pragma unroll
@@ -1315,8 +1322,8 @@ __global__ __launch_bounds__(kRestrictThreads) void k_ms_restrict(const MsTable 
     }
 }
 
-// the coarse product (as launch_coarse: one stage by rows, or tiles and their sum); with_state 0: the start (no
-// state), 1: with the state, 2: also the tile-row sums of h_j delta_j for the prolongation
+// the coarse product (as launch_coarse: one stage by rows, or tiles and their sum); with_state
+// 0: the start (no state), 1: with the state, 2: also the sums of h_j delta_j for the prolongation
 __global__ __launch_bounds__(kThreads) void k_ms_coarse(const MsTable *__restrict__ tab, const MsSys *__restrict__ sys,
                                                         int with_state) {
     const int s = ms_find(tab, kMsCoarse, blockIdx.x);

@@ -795,7 +795,6 @@ constexpr int kBatch = 16;
 constexpr int kSlice = 1024;
 constexpr int kTouchLds = 2048;  // LDS words of the touched-vector bitmap (k <= 65536)
 
-//
 // K z_j is zero on most of its structure: a rigid-body mode stores no energy in an element
 // all of whose nodes move with it, so inside the subdomain (and for the enriched modes inside
 // their supports) only the rounding of the sum is left.  (KZ)^T keeps a triplet of a run of
@@ -2035,9 +2034,9 @@ __global__ __launch_bounds__(256) void k_gjb_panel(int p, const GjMat *__restric
 // invert them), the others every other tile.  A tile is read and written once per two pivot
 // tiles, past the caches (the row and column tiles, which every tile's products read, stay
 // there), the products' operands come from memory and the four workgroups a CU holds hide it:
-// eight blocks of 4400 unknowns take 350 us a pair (operands staged through LDS, one pivot
-// tile a pass: 605; without the bound on registers 455; with cached tiles 367).  Matrix cores
-// and traffic alone would take 250 and 220.
+// eight blocks of 4150 unknowns take 337 us a pair, panel and second pivot 98 (as first written
+// 350; operands staged through LDS, one pivot tile a pass: 605; without the bound on registers
+// 455; with cached tiles 367).  Matrix cores and traffic alone would take 250 and 220.
 __global__ __launch_bounds__(256, 4) void k_gjb_sweep(int p, const GjMat *__restrict__ mats, int count, double *W,
                                                    double *Pm, double *orig, double *cbuf, double *tbuf,
                                                    const double *__restrict__ diag0, int *fail) {
