@@ -47,11 +47,11 @@ WORKLOADS = {
 SPMV_TRAFFIC = {
     "workload": "penny80",
     "sources": {
-        "paper_2111_09294_amd/csrc/kernels.hip": "cd87ef1526adb7f3509d596c5c9bb243f9b4cbd2cab540a08d1b743698135ccd",
-        "paper_2111_09294_amd/csrc/dpcg_internal.h": "cb4023fb85ca6580a205bb118493a9cd2958b7ac120d1a9eb09a4d907e364566"
+        "paper_2111_09294_amd/csrc/kernels.hip": "a42524bcd3ea85868ff5ceb677402a72ca808657aa82d3d0051e7d2d86cdad1b",
+        "paper_2111_09294_amd/csrc/dpcg_internal.h": "c5747053868802d79f90b1d0f6e7b313993b2b7ddb73cef8ef23da21575f2a98"
     },
-    "fetch_bytes": 1444866294,
-    "write_bytes": 16007168,
+    "fetch_bytes": 1444873462,
+    "write_bytes": 16006963,
 }
 SPMV_SOURCES = ("paper_2111_09294_amd/csrc/kernels.hip", "paper_2111_09294_amd/csrc/dpcg_internal.h")
 
