@@ -1304,8 +1304,7 @@ int brealloc(dpcg_ctx *c, T **p, size_t count) {
 
 int restriction_lists(dpcg_ctx *c);
 
-int ensure_ws(dpcg_ctx *c) {
-    if (c->bws) return c->bws->stale ? restriction_lists(c) : (int)DPCG_OK;
+int make_ws(dpcg_ctx *c) {
     auto *b = new BatchWorkspace();
     c->bws = b;
     constexpr int W = kBatchCols;  // the widest layout
@@ -1336,9 +1335,29 @@ int ensure_ws(dpcg_ctx *c) {
     BTRY(balloc(c, &b->part2, np));
     BTRY(balloc(c, &b->part3, (size_t)b->upd_nwg * W));
     BTRY(balloc(c, &b->st, 1));
-    BHIP(hipHostMalloc((void **)&b->snap, sizeof(BatchState) + sizeof(uint64_t), hipHostMallocDefault));
+    if (hipHostMalloc((void **)&b->snap, sizeof(BatchState) + sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
+        b->snap = nullptr;
+        (void)hipGetLastError();
+        return DPCG_EHIP;
+    }
     b->progress = reinterpret_cast<uint64_t *>(b->snap + 1);
     return restriction_lists(c);
+}
+
+// The handle's multi-RHS workspace, made whole or not at all: after a failed allocation what
+// was made of it is given back, and a later call starts anew.
+int ensure_ws(dpcg_ctx *c) {
+    if (c->bws) return c->bws->stale ? restriction_lists(c) : (int)DPCG_OK;
+    const size_t held = c->allocations.size();
+    const int64_t bytes = c->device_bytes;
+    const int e = make_ws(c);
+    if (e == DPCG_OK) return e;
+    (void)hipStreamSynchronize(c->stream);
+    for (size_t i = held; i < c->allocations.size(); ++i) dev_release(c->allocations[i]);
+    c->allocations.resize(held);
+    c->device_bytes = bytes;
+    release_batch(c);
+    return e;
 }
 
 // The restriction's segments and groups from Z^T and (KZ)^T, on the first batched call and

@@ -52,7 +52,10 @@ hipError_t dev_alloc(void **p, size_t bytes) {
         }
     }
     e = hipMalloc(p, sz);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // not left for the next launch's check to find
+        return e;
+    }
     std::lock_guard<std::mutex> lk(c.m);
     c.owner[*p] = {dev, sz};
     return hipSuccess;
@@ -83,7 +86,10 @@ hipError_t host_alloc(void **p, size_t bytes) {
         }
     }
     hipError_t e = hipHostMalloc(p, sz, hipHostMallocDefault);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
     std::lock_guard<std::mutex> lk(c.m);
     c.owner[*p] = {-1, sz};
     return hipSuccess;
