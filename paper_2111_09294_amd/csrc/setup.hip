@@ -674,10 +674,13 @@ __global__ void k_bcol16(int64_t nnzb, const int32_t *__restrict__ brow, const i
 
 // *longest (0 on entry) becomes the largest number of blocks in a row.
 __global__ __launch_bounds__(256) void k_longest_row(int32_t nb, const int32_t *__restrict__ ptr, int *longest) {
+    __shared__ int ms[4];
     int m = 0;
     for (int r = blockIdx.x * 256 + threadIdx.x; r < nb; r += gridDim.x * 256) m = max(m, ptr[r + 1] - ptr[r]);
     for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) atomicMax(longest, m);
+    if ((threadIdx.x & 63) == 0) ms[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(longest, max(max(ms[0], ms[1]), max(ms[2], ms[3])));
 }
 
 // ---------------------------------------------------------------- Z^T
@@ -1732,39 +1735,44 @@ __device__ __forceinline__ int gj_find(const GjMat *__restrict__ m, int count, i
 }
 
 // scale_i = 1 / sqrt(K_ii) of the matrices' rows (1 where K_ii <= 0 or is absent, whose pivot
-// then fails the SPD test, and beyond the block's size), one wave per row
+// then fails the SPD test, and beyond the block's size), one thread per row, which searches its
+// increasing columns (a wave per row that read all of them took 85 us for 180,000 rows, this 14)
 __global__ __launch_bounds__(256) void k_dense_scale(const GjMat *__restrict__ mats, int count,
                                                      const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
                                                      const double *__restrict__ val, double *__restrict__ scale) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int mi = blockIdx.y; mi < count; mi += gridDim.y) {
         const GjMat G = mats[mi];
-        for (int i = blockIdx.x * 4 + wave; i < G.nt * kCb; i += gridDim.x * 4) {
+        for (int i = blockIdx.x * 256 + threadIdx.x; i < G.nt * kCb; i += gridDim.x * 256) {
             double d = 0.0;
             if (i < G.size) {
-                const int64_t g = (int64_t)G.start + i;
-                for (int64_t e = ptr[g] + lane; e < ptr[g + 1]; e += 64)
-                    if (idx[e] == g) d = val[e];
+                const int64_t g = (int64_t)G.start + i, end = ptr[g + 1];
+                int64_t lo = ptr[g], hi = end;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if (idx[mid] < g) lo = mid + 1;
+                    else hi = mid;
+                }
+                if (lo < end && idx[lo] == g) d = val[lo];
             }
-            d = wave_sum(d);  // at most one lane holds it
-            if (lane == 0) scale[G.row0 * kCb + i] = d > 0.0 ? 1.0 / sqrt(d) : 1.0;
+            scale[G.row0 * kCb + i] = d > 0.0 ? 1.0 / sqrt(d) : 1.0;
         }
     }
 }
 
-// rows of matrix blockIdx.y (grid-stride): the scaled lower-triangle entries of K_BB, their
-// diagonal to diag0, the identity beyond the block's size.  W and diag0 are zero on entry.
+// rows of matrix blockIdx.y (grid-stride), sixteen lanes each: the scaled lower-triangle entries
+// of K_BB, their diagonal to diag0, the identity beyond the block's size (73 -> 40 us against a
+// wave each).  W and diag0 are zero on entry.
 __global__ __launch_bounds__(256) void k_dense_gather(const GjMat *__restrict__ mats, int count,
                                                       const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
                                                       const double *__restrict__ val,
                                                       const double *__restrict__ scale, double *__restrict__ W,
                                                       double *__restrict__ diag0) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 15;
     for (int mi = blockIdx.y; mi < count; mi += gridDim.y) {
         const GjMat G = mats[mi];
         const PackedTiles T{W + G.tile0 * (kCb * kCb)};
         const double *sc = scale + G.row0 * kCb;
-        for (int i = blockIdx.x * 4 + wave; i < G.nt * kCb; i += gridDim.x * 4) {
+        for (int i = blockIdx.x * 16 + (threadIdx.x >> 4); i < G.nt * kCb; i += gridDim.x * 16) {
             if (i >= G.size) {
                 if (lane == 0) {
                     T.tile(i / kCb, i / kCb)[(i % kCb) * (kCb + 1)] = 1.0;
@@ -1773,7 +1781,7 @@ __global__ __launch_bounds__(256) void k_dense_gather(const GjMat *__restrict__ 
                 continue;
             }
             const int64_t g = (int64_t)G.start + i;
-            for (int64_t e = ptr[g] + lane; e < ptr[g + 1]; e += 64) {
+            for (int64_t e = ptr[g] + lane; e < ptr[g + 1]; e += 16) {
                 const int64_t c = (int64_t)idx[e] - G.start;
                 if (c < 0 || c > i) continue;
                 const double v = (val[e] * sc[i]) * sc[c];
@@ -2680,9 +2688,9 @@ int dense_inverses(dpcg_ctx *c, Pool &pool, const int64_t *kp, const int32_t *kc
     HT(hipMemsetAsync(diag0, 0, sizeof(double) * rows[big] * kCb, s));
     HT(hipMemsetAsync(W, 0, sizeof(double) * tiles[big] * kTile, s));
     const int gy = std::min(big, 65535);
-    const dim3 rgrid(std::min(1024, (m[0].nt * kCb + 3) / 4), gy);
-    hipLaunchKernelGGL(k_dense_scale, rgrid, dim3(256), 0, s, md, big, kp, kc, kv, scale);
-    hipLaunchKernelGGL(k_dense_gather, rgrid, dim3(256), 0, s, md, big, kp, kc, kv, scale, W, diag0);
+    hipLaunchKernelGGL(k_dense_scale, dim3((m[0].nt * kCb + 255) / 256, gy), dim3(256), 0, s, md, big, kp, kc, kv,
+                       scale);
+    hipLaunchKernelGGL(k_dense_gather, dim3((m[0].nt * kCb + 15) / 16, gy), dim3(256), 0, s, md, big, kp, kc, kv, scale, W, diag0);
     hipLaunchKernelGGL(k_gjb_first_pivot, dim3(gy), dim3(256), 0, s, md, big, W, diag0, pv, orig,
                        bad_flag);
     int active = big, active2 = big;
@@ -2881,7 +2889,7 @@ int gpu_setup(dpcg_ctx *c, int64_t n, const int64_t *kp, const int32_t *kc, cons
     hipLaunchKernelGGL(k_bcol16, dim3(grid_for(nnzb)), dim3(256), 0, s, nnzb, (const int32_t *)brow,
                        (const int32_t *)c->bcol, c->bcol16, b16bad);
     if (nnzb <= (int64_t)kLongRowMean * nb)
-        hipLaunchKernelGGL(k_longest_row, dim3(grid_for(nb, 256, 256)), dim3(256), 0, s, nb,
+        hipLaunchKernelGGL(k_longest_row, dim3(grid_for(nb, 256, 64)), dim3(256), 0, s, nb,
                            (const int32_t *)c->brow_ptr, b16bad + 1);
     // The symmetry test and the small block-Jacobi inverses do not feed K Z, E or E^-1:
     // they run on the side stream beside that chain (whose kernels are latency bound and
